@@ -7,87 +7,126 @@
 //   dL/da_j = G . (T_j c_j - (S_j + T_f bg) / (1 - a_j)) - G_T T_f / (1 - a_j)
 // where S_j = sum_{k>j} a_k T_k c_k is the colour composited after j.  The
 // pass is recomputed rather than stored: walking the list front to back with
-// the forward's own arithmetic gives the same a_j and T_j, S_j is the
-// forward's colour minus the running sum, and the walk stops at the pixel's
-// n_contrib (one past its last composited entry).  Through a = min(0.99,
-// opacity exp(p)) with p = -0.5 (A dx^2 + C dy^2) - B dx dy the gradient
-// reaches the opacity, the conic and the centre; a clamped alpha passes none.
+// the forward's own arithmetic gives the same a_j and T_j, and the walk stops
+// at the pixel's n_contrib (one past its last composited entry).  Only the
+// projection of what lies behind on the loss gradient is needed,
+//   X_j = G . (S_j + T_f bg) + G_T T_f,  X_0 = G . C + G_T T_f,
+// one running value per pixel: X_j = X_{j-1} - a_j T_j (G . c_j).  Through a =
+// min(0.99, opacity exp(p)) with p = -0.5 (A dx^2 + C dy^2) - B dx dy the
+// gradient reaches the opacity, the conic and the centre; a clamped alpha
+// passes none.
+//
+// The kernel keeps one number per pixel for all of that: X = G . C + G_T T_f -
+// sum_{k<=j} a_k T_k G . c_k is G . (S_j + T_f bg) + G_T T_f, whatever the
+// background.
 //
 // Layout as the forward: one workgroup of four waves per 16x16 tile, one pixel
 // per lane, entries staged through LDS with the same per-quad reach masks.
-// Per entry, each wave sums its 64 pixels' nine gradients (a transposed
-// butterfly, below) and adds them into an LDS row of the staged entry; after
-// the batch every row with a contribution goes to HBM with nine atomic adds
-// (once per tile and entry).
+// Vector instructions bound it (92% of their issue rate), so an entry's sums
+// over a wave are taken as moments of dL/dp in dx and dy, summed with as few
+// cross-lane instructions as they need (below) and added into an LDS row of
+// the staged entry; what the moments share (the conic, the opacity, factors)
+// is applied once per tile and entry, after the batch, on the way to nine
+// atomic adds in HBM.  At 3M Gaussians and 1920x1080: 525 us, 672 with three
+// running colours, nine full gradients per pixel and a trading butterfly; four
+// 640x480 views of 300K: 352 us, 498 so; a 20K step at 317x179: 453 us, 601 so.
+// (Matrix instructions over 16 rows of moments of four entries took 246 us of
+// the matrix cores at the first size and 811 us in all: their sums leave in
+// more lanes than LDS atomics take quickly.)
 #include "blend_stage.h"
 
 namespace gsmi {
 namespace {
 
 constexpr float kLn2 = 0.69314718055994531f;
+constexpr int kBackBatch = 256;   // entries staged per batch
 
-// The value of the lane whose index differs in bit kBit: DPP quad
-// permutations for bits 0 and 1, ds_swizzle (bit-mask mode, within 32 lanes)
-// for bits 2 to 4, ds_bpermute across the two halves for bit 5.
-template <int kBit>
-__device__ __forceinline__ float lane_xor(float v)
+// The sums of an entry over a tile's pixels, with gp = dL/dp and w = a T, in
+// the order in which wave_sum9 leaves them in the lanes.
+enum { kS1, kSy, kSx, kSxx, kSxy, kSr, kSyy, kSg, kSb };   // gp, gp dy, gp dx, gp dx^2, gp dx dy, w G_r, ...
+
+struct BackLds {
+    float4 s0[kBackBatch];   // du_hi, dv_hi, du_lo, dv_lo
+    float4 s1[kBackBatch];   // A', B', C', opacity
+    float4 s2[kBackBatch];   // r, g, b, list position
+    uint32_t s_item[kBackBatch];
+    float s_acc[kBackBatch][kGrad2d];
+    uint32_t s_wave_keep[4];
+    uint8_t s_mask[kBackBatch];
+};
+
+// Half sums of two values at once: lanes 0-31 (even rows of 16 for the
+// second) get a's, the others b's.  The swap trades a's upper half for b's
+// lower one (a's odd rows for b's even ones), so one add sums both.
+__device__ __forceinline__ float half_sums32(float a, float b)
 {
-    const int x = __float_as_int(v);
-    if constexpr (kBit == 0) return __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false));
-    else if constexpr (kBit == 1) return __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false));
-    else if constexpr (kBit < 5) return __int_as_float(__builtin_amdgcn_ds_swizzle(x, 0x1F | ((1 << kBit) << 10)));
-    else return __shfl_xor(v, 32, 64);
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float half_sums16(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// One butterfly step over lane bit kBit for pairs (lo, hi): a lane whose bit
-// is clear keeps lo plus its partner's lo, the other keeps hi plus its
-// partner's hi, so one move per pair halves the values each lane carries.
-template <int kBit>
-__device__ __forceinline__ float trade(float lo, float hi, bool upper)
+// Wave sums of nine values.  Two halving steps leave eight of them in two
+// registers whose rows of 16 lanes hold one value each; DPP adds that write
+// only some banks (groups of four lanes) then sum within the rows and pack the
+// registers into one on the way: bank 0 of row r ends with value r, bank 2
+// with value 4 + r, and bank 3, whose rows are summed last, with value 8 in
+// row 3.  21 VALU instructions; the waits are the two states that DPP needs
+// between a write and its use.  (A trading butterfly with lane selects took 50
+// and five LDS exchanges, whole-row rotations of three registers 30.)
+__device__ __forceinline__ float wave_sum9(const float (&g)[9])
 {
-    return (upper ? hi : lo) + lane_xor<kBit>(upper ? lo : hi);
+    const float h0 = half_sums32(g[kS1], g[kSx]), h1 = half_sums32(g[kSy], g[kSxx]), h2 = half_sums32(g[kSxy], g[kSyy]),
+                h3 = half_sums32(g[kSr], g[kSg]);
+    const float q0 = half_sums16(h0, h1), q1 = half_sums16(h2, h3);
+    float t, u = g[kSb];
+    __asm__("s_nop 1\n\t"
+            "v_add_f32_dpp %1, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %0, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"   // banks 2, 3: the second register
+            "s_nop 1\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x8\n\t"   // bank 3: the ninth value
+            "s_nop 1\n\t"
+            "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+            "s_nop 1\n\t"
+            "v_add_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+            "s_nop 1\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0x8\n\t"
+            "s_nop 1\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0x8"
+            : "=&v"(t), "+v"(u)
+            : "v"(q0), "v"(q1));
+    return t;
 }
 
-// Wave sums of the nine values g[0..8] of every lane, with 13 cross-lane moves
-// instead of 9 x 6: four trading steps over lane bits 0-3 leave each lane one
-// value summed over its 16-lane row, two plain steps over bits 4-5 finish the
-// sum.  Returns the sum a lane holds and sets slot to the index of its value,
-// or to -1 for a padding slot; lanes 0-15 hold each of the nine sums once.
-__device__ __forceinline__ float wave_sum9(const float g[kGrad2d], int lane, int& slot)
+// Gradient c of an entry (u, v, A, B, C, opacity, r, g, b) from its sums.
+__device__ __forceinline__ float entry_gradient(int c, const float* s, const float4& e1)
 {
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
-    float a[6], c[4], d[2];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) a[i] = trade<0>(g[i], i < 4 ? g[5 + i] : 0.0f, b0);   // g0-4 | g5-8, 0
-    a[5] = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) c[i] = trade<1>(a[i], a[3 + i], b1);
-    c[3] = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) d[i] = trade<2>(c[i], c[2 + i], b2);
-    float e = trade<3>(d[0], d[1], b3);
-    e += lane_xor<4>(e);
-    e += lane_xor<5>(e);
-    const int ic = (b2 ? 2 : 0) + (b3 ? 1 : 0);    // index into c
-    const int real = b1 ? (b0 ? 1 : 2) : 3;         // c entries that hold a value
-    slot = (lane < 16 && ic < real) ? (b0 ? 5 : 0) + (b1 ? 3 : 0) + ic : -1;
-    return e;
+    switch (c) {
+    // dp/d(dx) = -(A dx + B dy) = ln2 (2 A' dx + B' dy)
+    case 0: return kLn2 * (2.0f * e1.x * s[kSx] + e1.y * s[kSy]);
+    case 1: return kLn2 * (2.0f * e1.z * s[kSy] + e1.y * s[kSx]);
+    case 2: return -0.5f * s[kSxx];
+    case 3: return -s[kSxy];
+    case 4: return -0.5f * s[kSyy];
+    case 5: return s[kS1] != 0.f ? s[kS1] / e1.w : 0.f;   // sum of dL/dp over the opacity
+    case 6: return s[kSr];
+    case 7: return s[kSg];
+    default: return s[kSb];
+    }
 }
 
-// 6 waves per SIMD (79 VGPRs, no spills; the compiler's own budget of 84
-// leaves 5): its 23.8 KB of LDS also allows 6 tiles per CU
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void blend_backward_kernel(
     BlendBackArgs a, uint64_t capacity)
 {
-    __shared__ float4 s0[256];   // du_hi, dv_hi, du_lo, dv_lo
-    __shared__ float4 s1[256];   // A', B', C', opacity
-    __shared__ float4 s2[256];   // r, g, b, list position
-    __shared__ uint32_t s_mask[256];
-    __shared__ uint32_t s_item[256];
-    __shared__ float s_acc[256][kGrad2d];
-    __shared__ uint32_t s_wave_keep[4];
-    const int tile = blend_tile(a.order, a.group);
+    __shared__ BackLds L;
+    int tile = blend_tile(a.order, a.group);
     if (tile >= a.tiles) return;
+    tile = __builtin_amdgcn_readfirstlane(tile);   // uniform: it and what follows from it stay scalar
     const ViewParams& vp = a.views[view_of_tile(a.views, a.n_views, (uint32_t)tile)];
     const int width = vp.width, height = vp.height;
     const int local = tile - (int)vp.tile_base;
@@ -96,116 +135,130 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
     const int lx = (wave & 1) * 8 + (lane & 7), ly = (wave >> 1) * 8 + (lane >> 3);
     const int px = tx * kTile + lx, py = ty * kTile + ly;
     const bool inside = px < width && py < height;
-    uint64_t start = a.tile_offsets[tile], end = a.tile_offsets[tile + 1];
-    if (end > capacity) end = capacity;
-    if (start > end) start = end;
+    const uint64_t start = min(a.tile_offsets[tile], capacity);
+    const uint32_t tail = (uint32_t)(min(a.tile_offsets[tile + 1], capacity) - start);
+    const uint32_t* const items = a.values + start;
     const double ox = (double)(tx * kTile), oy = (double)(ty * kTile);
     const float fx = (float)lx, fy = (float)ly;
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 
-    // the pixel's forward outputs and loss gradients
-    float G0 = 0.f, G1 = 0.f, G2 = 0.f, GT = 0.f, Tf = 1.f, S0 = 0.f, S1 = 0.f, S2 = 0.f;
+    // the pixel's loss gradient, n_contrib and what lies behind the first entry
+    float G0 = 0.f, G1 = 0.f, G2 = 0.f, X = 0.f;
     uint32_t nc = 0;
     if (inside) {
         const int64_t P = (int64_t)width * height, p = (int64_t)py * width + px;
         G0 = vp.grad_rgb[p];
         G1 = vp.grad_rgb[P + p];
         G2 = vp.grad_rgb[2 * P + p];
-        GT = vp.grad_T ? vp.grad_T[p] : 0.f;
-        Tf = vp.out_T[p];
         nc = vp.out_nc[p];
-        // colour composited over the whole list, without the background
-        S0 = vp.out_rgb[p] - Tf * a.bg[0];
-        S1 = vp.out_rgb[P + p] - Tf * a.bg[1];
-        S2 = vp.out_rgb[2 * P + p] - Tf * a.bg[2];
+        X = G0 * vp.out_rgb[p] + G1 * vp.out_rgb[P + p] + G2 * vp.out_rgb[2 * P + p];
+        if (vp.grad_T) X = fmaf(vp.grad_T[p], vp.out_T[p], X);
     }
-    // the part of dL/da_j that does not depend on j's colour: background and
-    // the final transmittance (both scale with T_f / (1 - a_j))
-    const float Gbg = G0 * a.bg[0] + G1 * a.bg[1] + G2 * a.bg[2] + GT;
     float Tr = 1.0f;
-    bool done = !inside || nc == 0;
+    // the last list position that a pixel of the wave, and of the tile, takes
+    uint32_t wave_last = nc;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) wave_last = max(wave_last, (uint32_t)__shfl_xor((int)wave_last, o));
+    wave_last = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_last);
+    if (lane == 0) L.s_wave_keep[wave] = wave_last;
+    __syncthreads();
+    const uint32_t tile_last = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)max(max(L.s_wave_keep[0], L.s_wave_keep[1]), max(L.s_wave_keep[2], L.s_wave_keep[3])));
+    if (tile_last == 0u) return;
+    // the lane's place among an entry's sums (wave_sum9)
+    const bool holds = (lane & 7) == 0 || lane == 63;
+    const int slot = lane == 63 ? 8 : ((lane & 8) >> 1) + (lane >> 4);
+    float* const acc = &L.s_acc[0][slot];
 
-    for (uint64_t b0 = start; b0 < end; b0 += 256) {
-        if (__syncthreads_count(!done) == 0) break;
-        const uint64_t e = b0 + tid;
-        bool keep = false;
-        uint32_t qmask = 0u, item = 0u;
+    // the forward's pipeline: the next batch's records are under way during this one
+    const uint32_t end = min(tail, tile_last);
+    float4 na = make_float4(0.f, 0.f, 0.f, 0.f), nb = na, ncl = na;
+    uint32_t item = 0u;
+    if ((uint32_t)tid < end) {
+        item = items[tid];
+        const float4* rec = reinterpret_cast<const float4*>(a.splats + item);
+        na = rec[0];
+        nb = rec[1];
+        ncl = rec[2];
+    }
+    for (uint32_t b0 = 0; b0 < end; b0 += kBackBatch) {
+        __syncthreads();   // the previous batch's rows
+        const uint32_t e = b0 + tid;
+        uint32_t qmask = 0u;
         float4 v0, v1, v2;
-        if (e < end) {
-            item = a.values[e];
-            const float4* rec = reinterpret_cast<const float4*>(a.splats + item);
-            qmask = stage_entry(rec[0], rec[1], rec[2], ox, oy, (uint32_t)(e - start), v0, v1, v2);
-            keep = qmask != 0u;
-        }
+        if (e < end) qmask = stage_entry(na, nb, ncl, ox, oy, e, v0, v1, v2);
+        const bool keep = qmask != 0u;
         const uint64_t km = __ballot(keep);
-        if (lane == 0) s_wave_keep[wave] = (uint32_t)__popcll(km);
+        if (lane == 0) L.s_wave_keep[wave] = (uint32_t)__popcll(km);
         __syncthreads();
-        uint32_t slot = (uint32_t)__popcll(km & lt);
-        for (int w = 0; w < wave; ++w) slot += s_wave_keep[w];
-        const int nk = (int)(s_wave_keep[0] + s_wave_keep[1] + s_wave_keep[2] + s_wave_keep[3]);
+        uint32_t before = 0u;
+        int nk = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            if (w == wave) before = (uint32_t)nk;
+            nk += __builtin_amdgcn_readfirstlane((int)L.s_wave_keep[w]);
+        }
         if (keep) {
-            s0[slot] = v0;
-            s1[slot] = v1;
-            s2[slot] = v2;
-            s_mask[slot] = qmask;
-            s_item[slot] = item;
+            const uint32_t at =
+                __builtin_amdgcn_mbcnt_hi((uint32_t)(km >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)km, before));
+            L.s0[at] = v0;
+            L.s1[at] = v1;
+            L.s2[at] = v2;
+            L.s_mask[at] = (uint8_t)qmask;
+            L.s_item[at] = item;
         }
-        for (int k = tid; k < 256 * kGrad2d; k += 256) (&s_acc[0][0])[k] = 0.f;
+        for (int k = tid; k < nk * kGrad2d; k += 256) (&L.s_acc[0][0])[k] = 0.f;
+        if (e + kBackBatch < end) {
+            item = items[e + kBackBatch];
+            const float4* rec = reinterpret_cast<const float4*>(a.splats + item);
+            na = rec[0];
+            nb = rec[1];
+            ncl = rec[2];
+        }
         __syncthreads();
-        uint64_t bits[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int jj = q * 64 + lane;
-            bits[q] = __ballot(jj < nk && ((s_mask[jj] >> wave) & 1u));
-        }
-        for (int j = 0; j < nk; ++j) {
-            if (!((bits[j >> 6] >> (j & 63)) & 1u)) continue;
-            if (__ballot(!done) == 0) break;   // every pixel of the wave is past its last entry
-            const float4 e0 = s0[j], e1 = s1[j], e2 = s2[j];
-            const uint32_t pos1 = (uint32_t)__float_as_int(e2.w);   // list position + 1
-            if (!done && pos1 > nc) done = true;                      // past the pixel's last entry
-            float dx, dy, E;
-            const float al = entry_alpha(e0, e1, fx, fy, dx, dy, E);
-            const float araw = e1.w * E;
-            const bool take = !done && al >= 1.0f / 255.0f;
-            float g[kGrad2d];
-#pragma unroll
-            for (int k = 0; k < kGrad2d; ++k) g[k] = 0.f;
-            if (take) {
-                const float w = al * Tr;
-                S0 -= w * e2.x;   // colour composited after this entry
-                S1 -= w * e2.y;
-                S2 -= w * e2.z;
-                g[6] = G0 * w;
-                g[7] = G1 * w;
-                g[8] = G2 * w;
-                const float inv = __builtin_amdgcn_rcpf(1.0f - al);   // 1 - al >= 0.01
-                const float ga = (G0 * e2.x + G1 * e2.y + G2 * e2.z) * Tr -
-                                 (G0 * S0 + G1 * S1 + G2 * S2 + Gbg * Tf) * inv;
-                if (araw <= 0.99f) {
-                    const float gp = ga * al;   // dL/dp, p the exponent of exp
-                    g[5] = ga * E;
-                    g[2] = -0.5f * dx * dx * gp;
-                    g[3] = -dx * dy * gp;
-                    g[4] = -0.5f * dy * dy * gp;
-                    // dp/d(dx) = -(A dx + B dy) = ln2 (2 A' dx + B' dy)
-                    g[0] = gp * kLn2 * (2.0f * e1.x * dx + e1.y * dy);
-                    g[1] = gp * kLn2 * (2.0f * e1.z * dy + e1.y * dx);
+        for (int q = 0; q < nk; q += 64) {
+            const int jj = q + lane;
+            uint64_t bits = __builtin_amdgcn_ballot_w64(jj < nk && ((L.s_mask[jj] >> wave) & 1u) &&
+                                                        (uint32_t)__float_as_int(L.s2[jj].w) <= wave_last);
+            while (bits) {
+                const int j = q + __builtin_ctzll(bits);
+                bits &= bits - 1;
+                const float4 e0 = L.s0[j], e1 = L.s1[j], e2 = L.s2[j];
+                float dx, dy, E;
+                const float al = entry_alpha(e0, e1, fx, fy, dx, dy, E);
+                // not past the pixel's last entry, and visible
+                const bool take = (uint32_t)__float_as_int(e2.w) <= nc && al >= 1.0f / 255.0f;
+                if (__builtin_amdgcn_ballot_w64(take) == 0) continue;
+                float gp = 0.f;   // dL/dp, p the exponent of exp
+                float g[9];
+                g[kSr] = g[kSg] = g[kSb] = 0.f;
+                if (take) {
+                    const float gc = G0 * e2.x + G1 * e2.y + G2 * e2.z;
+                    const float w = al * Tr;
+                    X = fmaf(-w, gc, X);   // what lies behind this entry
+                    const float inv = __builtin_amdgcn_rcpf(1.0f - al);   // 1 - al >= 0.01
+                    const float ga = fmaf(gc, Tr, -X * inv);
+                    gp = e1.w * E <= 0.99f ? ga * al : 0.f;
+                    g[kSr] = G0 * w;
+                    g[kSg] = G1 * w;
+                    g[kSb] = G2 * w;
+                    Tr = fmaf(-al, Tr, Tr);   // as the forward: Tr (1 - al), rounded once
                 }
-                Tr = fmaf(-al, Tr, Tr);   // as the forward: Tr (1 - al), rounded once
-            }
-            if (__ballot(take) != 0) {
-                int slot;
-                const float v = wave_sum9(g, lane, slot);
-                if (slot >= 0) atomicAdd(&s_acc[j][slot], v);
+                g[kS1] = gp;
+                g[kSx] = gp * dx;
+                g[kSy] = gp * dy;
+                g[kSxx] = g[kSx] * dx;
+                g[kSxy] = g[kSx] * dy;
+                g[kSyy] = g[kSy] * dy;
+                const float v = wave_sum9(g);
+                if (holds) atomicAdd(acc + j * kGrad2d, v);
             }
         }
         __syncthreads();
         // one set of atomic adds per staged entry and tile
         for (int k = tid; k < nk * kGrad2d; k += 256) {
             const int j = k / kGrad2d, c = k % kGrad2d;
-            const float v = s_acc[j][c];
-            if (v != 0.f) unsafeAtomicAdd(&a.grad2d[(int64_t)s_item[j] * kGrad2d + c], v);
+            const float v = entry_gradient(c, L.s_acc[j], L.s1[j]);
+            if (v != 0.f) unsafeAtomicAdd(&a.grad2d[(int64_t)L.s_item[j] * kGrad2d + c], v);
         }
     }
 }
@@ -215,7 +268,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
 hipError_t launch_blend_backward(const BlendBackArgs& a, uint64_t capacity, hipStream_t s)
 {
     if (a.tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(blend_backward_kernel, dim3(blend_grid(a.tiles, a.order, a.group)), dim3(256), 0, s, a, capacity);
+    hipLaunchKernelGGL(blend_backward_kernel, dim3(blend_grid(a.tiles, a.order, a.group)), dim3(256), 0, s,
+                       a, capacity);
     return hipGetLastError();
 }
 
