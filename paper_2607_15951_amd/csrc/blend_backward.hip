@@ -7,18 +7,15 @@
 //   dL/da_j = G . (T_j c_j - (S_j + T_f bg) / (1 - a_j)) - G_T T_f / (1 - a_j)
 // where S_j = sum_{k>j} a_k T_k c_k is the colour composited after j.  The
 // pass is recomputed rather than stored: walking the list front to back with
-// the forward's own arithmetic gives the same a_j and T_j, and the walk stops
-// at the pixel's n_contrib (one past its last composited entry).  Only the
-// projection of what lies behind on the loss gradient is needed,
-//   X_j = G . (S_j + T_f bg) + G_T T_f,  X_0 = G . C + G_T T_f,
-// one running value per pixel: X_j = X_{j-1} - a_j T_j (G . c_j).  Through a =
-// min(0.99, opacity exp(p)) with p = -0.5 (A dx^2 + C dy^2) - B dx dy the
-// gradient reaches the opacity, the conic and the centre; a clamped alpha
-// passes none.
-//
-// The kernel keeps one number per pixel for all of that: X = G . C + G_T T_f -
-// sum_{k<=j} a_k T_k G . c_k is G . (S_j + T_f bg) + G_T T_f, whatever the
-// background.
+// the forward's own arithmetic gives the same a_j and T_j, S_j is the
+// forward's colour minus the running sum, and the walk stops at the pixel's
+// n_contrib (one past its last composited entry).  With X_j = G . (S_j +
+// T_f bg) + G_T T_f, dL/da_j = (T_{j+1} G . c_j - X_j) / (1 - a_j): the
+// difference is rounded once.  (One running number per pixel for X_j, which
+// the three of S_j give, saves 8 us of 540 but raises the errors: its steps do
+// not mirror the forward's.)  Through a = min(0.99, opacity exp(p)) with p =
+// -0.5 (A dx^2 + C dy^2) - B dx dy the gradient reaches the opacity, the conic
+// and the centre; a clamped alpha passes none.
 //
 // Layout as the forward: one workgroup of four waves per 16x16 tile, one pixel
 // per lane, entries staged through LDS with the same per-quad reach masks.
@@ -27,9 +24,9 @@
 // cross-lane instructions as they need (below) and added into an LDS row of
 // the staged entry; what the moments share (the conic, the opacity, factors)
 // is applied once per tile and entry, after the batch, on the way to nine
-// atomic adds in HBM.  At 3M Gaussians and 1920x1080: 525 us, 672 with three
-// running colours, nine full gradients per pixel and a trading butterfly; four
-// 640x480 views of 300K: 352 us, 498 so; a 20K step at 317x179: 453 us, 601 so.
+// atomic adds in HBM.  At 3M Gaussians and 1920x1080: 525 us, 672 with nine
+// full gradients per pixel and a trading butterfly; four 640x480 views of 300K:
+// 355 us, 498 so; 20K at 317x179: 164 us, 288 so.
 // (Matrix instructions over 16 rows of moments of four entries took 246 us of
 // the matrix cores at the first size and 811 us in all: their sums leave in
 // more lanes than LDS atomics take quickly.)
@@ -141,8 +138,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
     const double ox = (double)(tx * kTile), oy = (double)(ty * kTile);
     const float fx = (float)lx, fy = (float)ly;
 
-    // the pixel's loss gradient, n_contrib and what lies behind the first entry
-    float G0 = 0.f, G1 = 0.f, G2 = 0.f, X = 0.f;
+    // the pixel's loss gradient, its n_contrib, the colour composited over the
+    // whole list without the background, and the part of X that is the same
+    // for every entry: background and final transmittance
+    float G0 = 0.f, G1 = 0.f, G2 = 0.f, S0 = 0.f, S1 = 0.f, S2 = 0.f, XT = 0.f;
     uint32_t nc = 0;
     if (inside) {
         const int64_t P = (int64_t)width * height, p = (int64_t)py * width + px;
@@ -150,8 +149,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
         G1 = vp.grad_rgb[P + p];
         G2 = vp.grad_rgb[2 * P + p];
         nc = vp.out_nc[p];
-        X = G0 * vp.out_rgb[p] + G1 * vp.out_rgb[P + p] + G2 * vp.out_rgb[2 * P + p];
-        if (vp.grad_T) X = fmaf(vp.grad_T[p], vp.out_T[p], X);
+        const float Tf = vp.out_T[p];
+        S0 = vp.out_rgb[p] - Tf * a.bg[0];
+        S1 = vp.out_rgb[P + p] - Tf * a.bg[1];
+        S2 = vp.out_rgb[2 * P + p] - Tf * a.bg[2];
+        XT = (G0 * a.bg[0] + G1 * a.bg[1] + G2 * a.bg[2] + (vp.grad_T ? vp.grad_T[p] : 0.f)) * Tf;
     }
     float Tr = 1.0f;
     // the last list position that a pixel of the wave, and of the tile, takes
@@ -234,14 +236,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
                 if (take) {
                     const float gc = G0 * e2.x + G1 * e2.y + G2 * e2.z;
                     const float w = al * Tr;
-                    X = fmaf(-w, gc, X);   // what lies behind this entry
+                    S0 -= w * e2.x;   // colour composited after this entry
+                    S1 -= w * e2.y;
+                    S2 -= w * e2.z;
+                    const float X = G0 * S0 + G1 * S1 + G2 * S2 + XT;
+                    Tr = fmaf(-al, Tr, Tr);   // as the forward: Tr (1 - al), rounded once
                     const float inv = __builtin_amdgcn_rcpf(1.0f - al);   // 1 - al >= 0.01
-                    const float ga = fmaf(gc, Tr, -X * inv);
+                    const float ga = fmaf(gc, Tr, -X) * inv;
                     gp = e1.w * E <= 0.99f ? ga * al : 0.f;
                     g[kSr] = G0 * w;
                     g[kSg] = G1 * w;
                     g[kSb] = G2 * w;
-                    Tr = fmaf(-al, Tr, Tr);   // as the forward: Tr (1 - al), rounded once
                 }
                 g[kS1] = gp;
                 g[kSx] = gp * dx;
