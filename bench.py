@@ -58,15 +58,10 @@ PACKED_RECT_TILES = 255   # views at most this many tiles wide and tall carry pa
 
 
 def algorithmic_bytes(stage: str, n: int, n_vis: int, K: int, R: int, deg: int, dtype: int, W: int, H: int,
-                      stats: dict, tuning: dict | None = None) -> float:
+                      stats: dict) -> float:
     """HBM bytes one frame's launches of a stage must move: each input and
-    output once (the per-unit figures below, times the units of the frame).
-    ``tuning`` gives the chunk sizes of the binning (count arrays and cursors
-    scale with them)."""
-    tu = tuning or {"bin_row_items": 8, "bin_tile_items": 16}
+    output once (the per-unit figures below, times the units of the frame)."""
     tx, ty = (W + TILE - 1) // TILE, (H + TILE - 1) // TILE
-    chunks1 = (n + 64 * tu["bin_row_items"] - 1) // (64 * tu["bin_row_items"])
-    chunks2 = R // (64 * tu["bin_tile_items"]) + ty
     if stage == "project":
         per_in = 12 + attr_bytes(dtype) * (3 + 4 + 1 + 3 * (deg + 1) ** 2)
         per_out = 48 + 4 + 4 + 4 + 8
@@ -83,15 +78,14 @@ def algorithmic_bytes(stage: str, n: int, n_vis: int, K: int, R: int, deg: int, 
         return passes + (payload if packed else 0)
     if stage == "bin_row_count":
         # packed rectangles read in depth order, else sorted index read, the
-        # rectangle gathered and written in depth order; per (row, chunk) a
-        # count written and scanned
-        return (n * 4 if packed else n * (4 + 8 + 8)) + ty * chunks1 * (4 + 8)
-    if stage == "bin_row_scatter":   # sorted index + rectangle per visible Gaussian, 8-byte row entries out
-        return n_vis * (4 + (4 if packed else 8)) + R * 8 + chunks1 * ty * 4
-    if stage == "bin_tile_count":    # row entries in; per (chunk, column) count written and scanned; tile offsets
-        return R * 8 + chunks2 * tx * (4 + 8) + (tx * ty + 1) * 4
-    if stage == "bin_tile_scatter":  # row entries in, chunk prefixes, the values out
-        return R * 8 + chunks2 * tx * 4 * 2 + K * 4
+        # rectangle gathered and written in depth order
+        return n * 4 if packed else n * (4 + 8 + 8)
+    if stage == "bin_row_scatter":
+        # sorted index + rectangle per visible Gaussian; 6 bytes out for each
+        # (Gaussian, bin) entry, of which every visible one has at least one
+        return n_vis * (4 + (4 if packed else 8) + 6)
+    if stage in ("bin_tile_count", "bin_tile_scatter"):   # no part of a frame
+        return 0
     if stage == "blend":             # list entry + 48-byte record per staged entry; rgb, T, n_contrib per pixel
         return stats["staged"] * (4 + 48) + W * H * 20
     raise KeyError(stage)
@@ -160,8 +154,7 @@ def cpu_baseline(scene, cam, band_rows: int = 4, band_rows_1t: int = 1, reps: in
 # while these files are unchanged)
 KERNEL_SOURCES = {
     "project_kernel": ["project.hip", "gs_internal.h"],
-    "level1_scatter_kernel": ["tile_bin.hip", "gs_internal.h"],
-    "level2_scatter_kernel": ["tile_bin.hip", "gs_internal.h"],
+    "bins_scatter_kernel": ["bins.hip", "gs_internal.h"],
     "blend_kernel": ["blend.hip", "blend_stage.h", "gs_internal.h"],
     "blend_queue_kernel": ["blend.hip", "blend_stage.h", "gs_internal.h"],
 }
@@ -175,9 +168,7 @@ def stage_kernel(stage: str, dtype: int, deg: int, tuning: dict) -> str:
     if stage == "project":
         return f"project_kernel<{dtype}, {deg}, true>"
     if stage == "bin_row_scatter":
-        return f"level1_scatter_kernel<{tuning['bin_row_items']}>"
-    if stage == "bin_tile_scatter":
-        return f"level2_scatter_kernel<{tuning['bin_tile_items']}>"
+        return "bins_scatter_kernel"
     if stage == "blend":
         if tuning["blend_tile_group"] < 0:   # the persistent grid over the work queue
             return f"blend_queue_kernel<{tuning['blend_batch']}>"
@@ -893,7 +884,7 @@ def main():
 
     K, n_vis, R = info["num_pairs"], info["n_visible"], info["num_row_entries"]
     tuned = main_tuning
-    single = ["project", "bin_row_scatter", "bin_tile_scatter", "blend"]
+    single = ["project", "bin_row_scatter", "blend"]
     dom = max(single, key=lambda k: stage_ms[k])
     if dom == "blend":
         flops = FLOPS_EVAL * stats["evaluations"] + FLOPS_COMPOSITE * stats["composited"]
@@ -905,7 +896,7 @@ def main():
                                           "flops_per_evaluation": FLOPS_EVAL,
                                           "flops_per_composite": FLOPS_COMPOSITE}}
     else:
-        by = algorithmic_bytes(dom, n, n_vis, K, R, deg, dtype, W, H, stats, tuned)
+        by = algorithmic_bytes(dom, n, n_vis, K, R, deg, dtype, W, H, stats)
         achieved = by / (stage_ms[dom] * 1e-3) / 1e9
         kname = stage_kernel(dom, dtype, deg, tuned)
         roof = {"kernel": kname, "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
@@ -915,7 +906,7 @@ def main():
     stage_gbs = {}
     stage_bytes = {}
     for k in gs.STAGES:
-        by = algorithmic_bytes(k, n, n_vis, K, R, deg, dtype, W, H, stats, tuned)
+        by = algorithmic_bytes(k, n, n_vis, K, R, deg, dtype, W, H, stats)
         stage_bytes[k] = by
         stage_gbs[k] = round(by / (stage_ms[k] * 1e-3) / 1e9, 1) if stage_ms[k] > 0 else None
     # the whole frame: every stage's algorithmic bytes over the frame time

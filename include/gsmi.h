@@ -95,9 +95,8 @@ typedef struct {
  *                  gs_get_list_info (hence gs_copy_lists) returns
  *                  GS_ERR_CAPACITY for that render; above 2^32 - 1:
  *                  GS_ERR_UNSUPPORTED (pair offsets are 32-bit; a render
- *                  with more pairs returns GS_ERR_CAPACITY after the row
- *                  counts, before the pair buffers are sized or any output
- *                  is written)
+ *                  with more pairs returns GS_ERR_CAPACITY after the
+ *                  projection's counts, before any output is written)
  *   flags          0, GS_RENDER_REUSE_ORDER or GS_RENDER_REUSE_LISTS
  *                  (below), or both; other bits give GS_ERR_INVALID_ARGUMENT */
 typedef struct {
@@ -183,7 +182,7 @@ gs_status gs_render(gs_context* ctx, const gs_gaussians* g, const gs_camera* cam
  *                        gs_get_list_info reports afterwards
  * GS_RENDER_REUSE_ORDER, GS_RENDER_REUSE_LISTS and GS_PROFILE_BLEND_WORK
  * are ignored, and the blend takes no per-tile history (a heaviest-first order, if tuned, comes
- * from list lengths).  After it, gs_get_list_info and gs_get_stage_times
+ * from the lengths of the bins' lists).  After it, gs_get_list_info and gs_get_stage_times
  * work; the lists, projection and backward of the render are not kept
  * (gs_copy_lists, gs_copy_projection and gs_render_backward fail).  Every
  * call on one device shares that device's array and leaves its contents
@@ -287,7 +286,7 @@ typedef struct {
     uint64_t num_pairs;        /* K, total (Gaussian, tile) pairs */
     int32_t tiles_x, tiles_y;
     int64_t n_visible;         /* Gaussians overlapping at least one tile */
-    uint64_t num_row_entries;  /* (Gaussian, tile row) pairs of the binning */
+    uint64_t num_row_entries;  /* (Gaussian, tile row) pairs */
     int64_t num_tiles;         /* tiles over all views (tiles_x * tiles_y for one view) */
     int32_t num_views;         /* views of the last render */
 } gs_list_info;
@@ -296,7 +295,9 @@ gs_status gs_get_list_info(gs_context* ctx, gs_list_info* out);
 
 /* Copies the last render's per-tile lists into caller memory: the output of
  * the duplicate-and-sort stages of Sec. 3.1 (every (Gaussian, tile) pair,
- * ordered by the 64-bit key tile << 32 | depth), which the blend walks.
+ * ordered by the 64-bit key tile << 32 | depth).  The blend walks the same
+ * entries in the same order out of lists over bins of tiles; the per-tile
+ * lists are written here, from the kept depth order.
  * Device pointers on the context's device, written on `stream`; the caller
  * sizes them from gs_get_list_info, and any of them may be NULL (not
  * copied).  Fails as gs_get_list_info does (no render yet, pairs dropped),
@@ -339,14 +340,14 @@ gs_status gs_copy_projection(gs_context* ctx, float* splats, uint32_t* depth_key
  * order:
  *   0 project      (one kernel: cull, EWA projection, SH colour)
  *   1 depth_sort   (four LSD radix passes over the N depth keys)
- *   2 bin_row_count     (per-row counts of the depth-sorted Gaussians, row
- *                        offsets, chunk table of the second level)
- *   3 bin_row_scatter   (one kernel: per-row lists in depth order)
- *   4 bin_tile_count    (per-tile counts within each row, tile offsets)
- *   5 bin_tile_scatter  (one kernel: the sorted pair list)
+ *   2 bin_row_count     (counts of the depth-sorted Gaussians per bin of
+ *                        tiles and their scan)
+ *   3 bin_row_scatter   (one kernel: per-bin lists in depth order)
+ *   4 bin_tile_count    (0: no part of a render; gs_copy_lists does it)
+ *   5 bin_tile_scatter  (0, likewise)
  *   6 blend             (one kernel: per-tile compositing)
- * The host read of the pair count (pair_capacity 0) falls between stages 2
- * and 3 and belongs to neither.  count must be GS_NUM_STAGES; a last render
+ * The host read of the counts (pair_capacity 0) waits for the projection
+ * only, while the sort and the bins' counts are under way.  count must be GS_NUM_STAGES; a last render
  * without this flag gives GS_ERR_INVALID_ARGUMENT.
  *
  * GS_PROFILE_BLEND_WORK: the blend runs a variant that counts its work
@@ -404,16 +405,17 @@ gs_status gs_get_list_reuse(gs_context* ctx, uint32_t* out2);
  * dealt to the XCDs, change only speed.  Every supported value gives the same
  * image, final T, n_contrib, lists and projection, bit for bit.
  *   sort_items        keys per thread of a depth-sort block: 4, 8 or 16
- *   bin_row_items     depth-sorted Gaussians per lane of a row-binning
- *                     wavefront: 4, 8 or 16
- *   bin_tile_items    row entries per lane of a tile-binning wavefront:
- *                     8, 16 or 32
+ *   bin_row_items     scale of the depth-sorted Gaussians per lane of a
+ *                     binning wavefront (and of the row lists of
+ *                     gs_copy_lists): 4, 8 or 16
+ *   bin_tile_items    row entries per lane of a wavefront that writes the
+ *                     per-tile lists of gs_copy_lists: 8, 16 or 32
  *   blend_tile_group  consecutive tiles (row-major) dealt to one XCD by the
  *                     blend and its backward: 1 .. 64; or 0: every tile's
  *                     workgroup is dispatched heaviest first, by the work
  *                     (list entries walked) each tile took in the last
  *                     render on the context when it had the same tile
- *                     layout, else by list length -- the frame-to-frame
+ *                     layout, else by the length of its bin's list -- the frame-to-frame
  *                     coherence of Sec. 5.7 applied to the load imbalance of
  *                     the per-tile blend (Sec. 6); or -1: the same order
  *                     as a work queue over the (view, tile) items of all
@@ -423,7 +425,7 @@ gs_status gs_get_list_reuse(gs_context* ctx, uint32_t* out2);
  *                     one; the backward follows its render's order
  *   blend_batch       list entries the blend stages from HBM into on-chip
  *                     memory per batch: 128, 256 or 512 (the backward
- *                     stages 256)
+ *                     stages 192)
  * A new context starts at {8, 8, 16, 0, 256}.  gs_set_tuning applies to the
  * following renders and backwards (a backward uses its render's shapes; a
  * captured graph keeps those of its capture); GS_ERR_INVALID_ARGUMENT for an

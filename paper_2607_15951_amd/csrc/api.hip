@@ -1,6 +1,6 @@
 // api.hip -- host side of the C ABI declared in include/gsmi.h: argument
 // validation, the context's device workspace and the launch sequence of one
-// render of one or several views (project -> depth sort -> tile counts and
+// render of one or several views (project -> depth sort -> bin counts and
 // offsets -> scatter -> blend).  A single-image render is the one-view case.
 #include "gsmi.h"
 #include "gs_internal.h"
@@ -65,30 +65,35 @@ struct Workspace {
     DevBuf splats, depth_key, radius, tiles_touched, rect;
     DevBuf sort_ka, sort_va, sort_kb, sort_vb, hist, scan_scratch;
     DevBuf sort_pa, sort_pb;     // packed rectangles carried by the depth sort
-    DevBuf bin_info, counts1, rows_off, row_ent, counts2, partials, sorted_rect, readback;
-    DevBuf views, row_tiles_x;   // device view table and tiles_x of every global tile row
-    DevBuf view_counts;          // [n_views][kViewCounters] visible Gaussians and pairs per view
+    DevBuf bin_table, bin_items, bin_spans, partials, sorted_rect, readback;
+    DevBuf views;                // device view table
+    DevBuf view_counts;          // [n_views][kViewCounters]
     DevBuf counters;             // [1] capacity overflow flag
-    DevBuf tile_offsets, values;
     DevBuf tile_work;   // per-tile blend trace [T][kTileWorkFields] u64 (GS_PROFILE_BLEND_WORK)
     DevBuf reuse_words;       // [kReuseWords] outcome of an order-reuse attempt
     // per-tile blend work of the last render, and the blend's dispatch order
     DevBuf tile_cost, tile_order;
 };
 
+// The buffers gs_copy_lists writes the per-tile lists with.
+struct ListSpace {
+    DevBuf row_tiles_x, info, counts1, rows_off, row_ent, counts2, scan_scratch, tile_offsets, overflow;
+    hipEvent_t done = nullptr;   // the last copy: the next one, on whatever stream, waits for it
+};
+
 struct gs_context {
     int device = 0;
     std::string err;
     Workspace ws;                    // buffers of the renders on this context
+    ListSpace lists;
     uint32_t* host_info = nullptr;   // pinned readback of the per-frame sizes
-    uint32_t* host_info_dev = nullptr;   // its device address: the size kernel writes there directly
+    uint32_t* host_info_dev = nullptr;   // its device address: the projection's reduction writes there directly
     uint32_t profiling = 0;   // GS_PROFILE_* flags
     bool timed = false;       // the last render recorded stage events
     bool traced = false;      // the last render counted blend work
-    // stage boundaries: 0 start, 1 project, 2 depth sort, 3 row counts,
-    // 4 after the host read of K, 5 row scatter, 6 tile counts, 7 tile
-    // scatter, 8 blend
-    hipEvent_t ev[9] = {};
+    // stage boundaries: 0 start, 1 project, 2 depth sort, 3 bin counts,
+    // 4 bin scatter, 5 after the host read of the sizes, 6 blend
+    hipEvent_t ev[7] = {};
     // last render
     bool have_render = false;
     int64_t n = 0;
@@ -97,7 +102,8 @@ struct gs_context {
     int64_t tiles = 0;              // global tiles over all views
     int rows = 0;                   // global tile rows
     uint64_t capacity = 0;
-    int sorted_in_b = 1;
+    BinLists bins{};                // the last render's bin lists
+    bool packed = false;            // its sort carried the rectangles (else ws.sorted_rect holds them)
     hipStream_t stream = nullptr;
     hipEvent_t sizes_ev = nullptr;   // the host read of an eager render's sizes
     gs_graph* graph = nullptr;   // a captured render owns the workspace
@@ -114,8 +120,14 @@ struct gs_context {
     // in views of the sizes lists_sizes (width, height per view) with pair
     // capacity lists_cap (0: eager)
     int64_t lists_n = -1;
-    std::vector<int> lists_sizes;
+    std::vector<int> lists_sizes, lists_shifts;
     uint64_t lists_cap = 0;
+    // bin edges (log2 tiles) for the next render of bins_n Gaussians in views of
+    // bins_sizes, and whether the counters they come from are still under way
+    // to host_info (marked by sizes_ev)
+    int64_t bins_n = -1;
+    std::vector<int> bins_sizes, next_shifts;
+    bool counts_pending = false;
     bool lists_compared = false;   // the last render compared keys and rectangles with its predecessor's
     std::vector<int> cost_layout;   // tiles_x, tiles_y of every view whose work ws.tile_cost holds
     // the last render was gs_render_noalloc: its sizes are in noalloc_info
@@ -266,10 +278,10 @@ __global__ void write_views_kernel(ViewBatch b, int count, ViewParams* dst)
 }
 
 // The start of a frame of at most kViewsPerLaunch views in one launch: the
-// overflow counters cleared, the view table written (when `write`) and the
-// tiles_x of every global tile row, all from the views in the arguments.
+// overflow counters cleared and the view table written (when `write`) from
+// the views in the arguments.
 __global__ void frame_setup_kernel(ViewBatch b, int count, ViewParams* dst, int write, uint32_t* counters,
-                                   uint32_t* row_tiles_x, int rows, uint32_t hold_init)
+                                   uint32_t hold_init)
 {
     if (threadIdx.x < 16) counters[threadIdx.x] = threadIdx.x == kCounterChanged + 1 ? hold_init : 0u;
     if (write) {
@@ -277,11 +289,6 @@ __global__ void frame_setup_kernel(ViewBatch b, int count, ViewParams* dst, int 
         uint32_t* out = reinterpret_cast<uint32_t*>(dst);
         const int words = count * (int)(sizeof(ViewParams) / 4);
         for (int k = threadIdx.x; k < words; k += blockDim.x) out[k] = src[k];
-    }
-    for (int r = threadIdx.x; r < rows; r += blockDim.x) {
-        int v = 0;
-        while (v + 1 < count && (int)b.v[v + 1].row_base <= r) ++v;
-        row_tiles_x[r] = (uint32_t)b.v[v].tiles_x;
     }
 }
 
@@ -296,22 +303,10 @@ hipError_t write_view_table(const std::vector<ViewParams>& hv, ViewParams* dst, 
     return hipGetLastError();
 }
 
-// tiles_x of every global tile row (rows of view v are [row_base, row_base + tiles_y))
-// The eager render's host read gathered for one copy: the view counters
-// ([n][kViewCounters]), then counters[0..3], R and the level-2 chunk and
-// count-element totals.
-constexpr int kReadbackTail = 7;
-__global__ void pack_readback_kernel(const uint32_t* view_counts, int n_vc, const uint32_t* counters,
-                                     const uint32_t* r_total, const uint32_t* info, uint32_t* out)
-{
-    for (int i = threadIdx.x; i < n_vc + kReadbackTail; i += blockDim.x) {
-        const int t = i - n_vc;
-        out[i] = i < n_vc ? view_counts[i] : (t < 4 ? counters[t] : (t == 4 ? *r_total : info[t - 5]));
-    }
-    __threadfence_system();   // out may be pinned host memory, read by the host after the frame's event
-}
-
-__global__ void row_table_kernel(const ViewParams* views, int n_views, uint32_t* row_tiles_x, int rows)
+// tiles_x and first tile of every global tile row (rows of view v are
+// [row_base, row_base + tiles_y))
+__global__ void row_table_kernel(const ViewParams* views, int n_views, uint32_t* row_tiles_x, uint32_t* row_tile0,
+                                 int rows)
 {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= rows) return;
@@ -322,8 +317,107 @@ __global__ void row_table_kernel(const ViewParams* views, int n_views, uint32_t*
         else hi = mid;
     }
     row_tiles_x[r] = (uint32_t)views[lo].tiles_x;
+    row_tile0[r] = views[lo].tile_base + (uint32_t)(r - (int)views[lo].row_base) * (uint32_t)views[lo].tiles_x;
 }
 
+
+void set_bins(ViewParams& v, uint32_t bin_base, int shift)
+{
+    v.bin_base = bin_base;
+    v.bin_shift = shift;
+    v.bins_x = ((v.tiles_x - 1) >> shift) + 1;
+    v.bins_y = ((v.tiles_y - 1) >> shift) + 1;
+}
+
+// Edge of the bins each view's counters suggest, staying at the present one
+// within a quarter of the line.
+std::vector<int> suggested_shifts(const std::vector<ViewParams>& hv, const uint32_t* counts)
+{
+    std::vector<int> out;
+    for (size_t k = 0; k < hv.size(); ++k) {
+        const uint32_t* c = counts + k * kViewCounters;
+        const double pairs = (double)c[2] + 4294967296.0 * (double)c[3];
+        const float f = c[0] ? (float)(pairs / (double)c[0]) : 0.f;
+        const int lo = bin_shift_of(hv[k].tiles_x, hv[k].tiles_y, f / 1.25f);
+        const int hi = bin_shift_of(hv[k].tiles_x, hv[k].tiles_y, f * 1.25f);
+        out.push_back(std::min(std::max(hv[k].bin_shift, std::min(lo, hi)), std::max(lo, hi)));
+    }
+    return out;
+}
+
+std::vector<int> view_sizes(const std::vector<ViewParams>& hv)
+{
+    std::vector<int> sizes;
+    for (const ViewParams& v : hv) {
+        sizes.push_back(v.width);
+        sizes.push_back(v.height);
+    }
+    return sizes;
+}
+
+std::vector<int> view_shifts(const std::vector<ViewParams>& hv)
+{
+    std::vector<int> shifts;
+    for (const ViewParams& v : hv) shifts.push_back(v.bin_shift);
+    return shifts;
+}
+
+// Edges of the bins of a render (make_view chose them by resolution): those
+// of the lists in the workspace where it may keep them, else those that the
+// last render of as many Gaussians in views of the same sizes suggested.
+// Any choice gives the same image.
+void choose_bins(gs_context* ctx, int64_t n, const gs_render_opts* opts, std::vector<ViewParams>& hv)
+{
+    const std::vector<int> sizes = view_sizes(hv);
+    if (ctx->bins_n != n || ctx->bins_sizes != sizes) {
+        ctx->bins_n = n;
+        ctx->bins_sizes = sizes;
+        ctx->next_shifts.clear();
+        ctx->counts_pending = false;
+    }
+    if (ctx->counts_pending && hipEventQuery(ctx->sizes_ev) == hipSuccess) {
+        ctx->counts_pending = false;
+        ctx->next_shifts = suggested_shifts(hv, ctx->host_info);
+    }
+    const bool keep = opts && (opts->flags & GS_RENDER_REUSE_LISTS) && ctx->lists_n == n && ctx->lists_sizes == sizes;
+    const std::vector<int>& shifts = keep ? ctx->lists_shifts : ctx->next_shifts;
+    if (shifts.size() != hv.size()) return;
+    uint32_t base = 0;
+    for (size_t k = 0; k < hv.size(); ++k) {
+        set_bins(hv[k], base, shifts[k]);
+        base += (uint32_t)(hv[k].bins_x * hv[k].bins_y);
+    }
+}
+
+// The bins of a render's views and the chunks its binning cuts them from.
+struct BinShape {
+    int64_t bins = 0;
+    int max_bins = 0, max_diff = 0;
+    int items1 = 0, chunk = 0, chunks1 = 0;
+    bool packed = true;   // the grids fit packed rectangles
+    size_t table_elems() const { return (size_t)(bins * chunks1 + 2); }
+};
+
+BinShape bin_shape(const std::vector<ViewParams>& hv, int64_t n, int tuned)
+{
+    BinShape b;
+    for (const ViewParams& v : hv) {
+        b.bins += (int64_t)v.bins_x * v.bins_y;
+        b.max_bins = std::max(b.max_bins, v.bins_x * v.bins_y);
+        b.max_diff = std::max(b.max_diff, (v.bins_x + 1) * (v.bins_y + 1));
+        b.packed = b.packed && v.tiles_x <= kPackedRectTiles && v.tiles_y <= kPackedRectTiles;
+    }
+    bins_chunk_shape(n, (int)hv.size(), b.bins, b.max_bins, tuned, &b.items1, &b.chunk, &b.chunks1);
+    return b;
+}
+
+// Room for that many bin entries, in whole groups of four.
+gs_status ensure_bin_entries(gs_context* ctx, Workspace& w, uint64_t entries)
+{
+    const size_t e = ((size_t)std::max<uint64_t>(entries, 4) + 3) & ~size_t(3);
+    gs_status st = ensure(ctx, w.bin_items, e * 4);
+    return st == GS_OK ? ensure(ctx, w.bin_spans, e * 2) : st;
+}
 
 // One render of n_views views of the scene g (validated by the caller).
 // write_table: upload the view table first (false while a graph is captured:
@@ -356,45 +450,44 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     const int64_t items = n * V;
     const int rows = (int)(hv.back().row_base + hv.back().tiles_y);
     const int64_t T = (int64_t)hv.back().tile_base + (int64_t)hv.back().tiles_x * hv.back().tiles_y;
-    int max_tx = 0, max_ty = 0;
-    for (const ViewParams& v : hv) {
-        max_tx = std::max(max_tx, v.tiles_x);
-        max_ty = std::max(max_ty, v.tiles_y);
-    }
     const size_t ni = (size_t)(items > 0 ? items : 1);
     const Tuning tu = ctx->tuning;
-    const int chunks1 = std::max(bin_level1_chunks(n, tu.bin1_items), 1);
+    const BinShape bs = bin_shape(hv, n, tu.bin1_items);
 
     if ((st = ensure(ctx, w.splats, ni * sizeof(Splat))) != GS_OK) return st;
     if ((st = ensure(ctx, w.depth_key, ni * 4)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.radius, ni * 4)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.tiles_touched, ni * 4)) != GS_OK) return st;
+    if (!noalloc) {   // read only by gs_copy_projection and the backward
+        if ((st = ensure(ctx, w.radius, ni * 4)) != GS_OK) return st;
+        if ((st = ensure(ctx, w.tiles_touched, ni * 4)) != GS_OK) return st;
+    }
     if ((st = ensure(ctx, w.rect, ni * 8)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.sorted_rect, ni * 8)) != GS_OK) return st;
     if ((st = ensure(ctx, w.sort_ka, ni * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.sort_va, ni * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.sort_kb, ni * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.sort_vb, ni * 4)) != GS_OK) return st;
-    const bool fits_packed = !noalloc && max_tx <= kPackedRectTiles && max_ty <= kPackedRectTiles;
-    if (fits_packed) {
+    // the sort carries each Gaussian's packed rectangle to the binning, which
+    // then reads the rectangles in depth order instead of gathering them;
+    // when a reused order skips the radix passes, one gather in that order
+    // writes them
+    const bool packed = bs.packed;
+    if (packed) {
         if ((st = ensure(ctx, w.sort_pa, ni * 4)) != GS_OK) return st;
         if ((st = ensure(ctx, w.sort_pb, ni * 4)) != GS_OK) return st;
+    } else {
+        if ((st = ensure(ctx, w.sorted_rect, ni * 8)) != GS_OK) return st;
     }
     if ((st = ensure(ctx, w.hist, depth_sort_hist_elems(n, V) * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.partials, project_partials_elems(n, V) * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.views, (size_t)V * sizeof(ViewParams))) != GS_OK) return st;
     if ((st = ensure(ctx, w.view_counts, (size_t)V * kViewCounters * 4)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.row_tiles_x, (size_t)rows * 4)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.bin_info, bin_info_elems(rows) * 4)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.rows_off, (size_t)(rows + 1) * 4)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.counts1, (size_t)chunks1 * rows * 4)) != GS_OK) return st;
+    if ((st = ensure(ctx, w.bin_table, bs.table_elems() * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.counters, 64)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.tile_offsets, (size_t)(T + 1) * 4)) != GS_OK) return st;
+    if ((st = ensure(ctx, w.scan_scratch, scan_scratch_elems(bs.bins * bs.chunks1) * 8)) != GS_OK) return st;
     // every blend records its tiles' work; with blend_group 0 it is dispatched
     // (with -1 queued for a persistent grid) heaviest first, by the last
     // render's work when that render had the same tile layout (the history:
-    // ordered by one extra workgroup of the projection launch), else by list
-    // length (ordered before the blend)
+    // ordered by one extra workgroup of the projection launch), else by the
+    // length of the bins' lists (ordered before the blend)
     std::vector<int> layout;
     for (const ViewParams& v : hv) {
         layout.push_back(v.tiles_x);
@@ -413,13 +506,10 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     // changed since, and when none did those lists are this frame's (they
     // depend on nothing else): the sort and the binning then skip on the
     // device
-    std::vector<int> sizes;
-    for (const ViewParams& v : hv) {
-        sizes.push_back(v.width);
-        sizes.push_back(v.height);
-    }
+    const std::vector<int> sizes = view_sizes(hv);
     const bool try_lists = !noalloc && (o.flags & GS_RENDER_REUSE_LISTS) && n > 0 && prev_lists_n == n &&
-                           ctx->lists_sizes == sizes && ctx->lists_cap == o.pair_capacity;
+                           ctx->lists_sizes == sizes && ctx->lists_cap == o.pair_capacity &&
+                           ctx->lists_shifts == view_shifts(hv);
 
     ViewParams* views = static_cast<ViewParams*>(w.views.p);
     uint32_t* counters = static_cast<uint32_t*>(w.counters.p);
@@ -428,23 +518,14 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
         ViewBatch b;
         std::memcpy(b.v, hv.data(), (size_t)V * sizeof(ViewParams));
         hipLaunchKernelGGL(frame_setup_kernel, dim3(1), dim3(256), 0, s, b, V, views, write_table ? 1 : 0, counters,
-                           static_cast<uint32_t*>(w.row_tiles_x.p), rows, try_lists ? 1u : 0u);
+                           try_lists ? 1u : 0u);
     } else {
         HIP_TRY(launch_fill_u32(counters, 0u, 16, s), "clear counters");
         if (try_lists) HIP_TRY(launch_fill_u32(counters + kCounterChanged + 1, 1u, 1, s), "list reuse flag");
         if (write_table) HIP_TRY(write_view_table(hv, views, s), "view table");
-        hipLaunchKernelGGL(row_table_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s,
-                           (const ViewParams*)views, V, static_cast<uint32_t*>(w.row_tiles_x.p), rows);
     }
     HIP_TRY(hipGetLastError(), "frame set-up");
     STAGE_MARK(0);
-
-    // list reuse: the workspace holds the lists of a one-view render of as
-    // many Gaussians at the same size and pair capacity (a capacity that
-    // truncated them truncates an identical frame's the same way); the
-    // projection counts the Gaussians whose depth key or rectangle changed
-    // since, and when none did those lists are this frame's (they depend on
-    // nothing else): the sort and the binning then skip on the device
 
     ProjectArgs pa{};
     pa.n = n;
@@ -464,6 +545,30 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     pa.rect = static_cast<ushort4*>(w.rect.p);
     pa.view_counts = view_counts;
     pa.partials = static_cast<uint32_t*>(w.partials.p);
+    // eager: the sizes go straight into the pinned host buffer (its device
+    // address), else through a device buffer and a copy; a no-allocation
+    // render keeps them past its scratch
+    const bool eager = o.pair_capacity == 0;
+    uint32_t* counts_out = noalloc ? ctx->noalloc_info : nullptr;
+    if (eager) {
+        counts_out = ctx->host_info_dev;
+        if (!counts_out) {
+            if ((st = ensure(ctx, w.readback, (size_t)V * kViewCounters * 4)) != GS_OK) return st;
+            counts_out = static_cast<uint32_t*>(w.readback.p);
+        }
+    }
+    // with a pair capacity the counters come back once, unwaited for, to
+    // choose the bins of the following renders
+    bool learn = false;
+    if (!eager && !noalloc && write_table && ctx->host_info_dev && n > 0 && ctx->next_shifts.empty() &&
+        !ctx->counts_pending) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        HIP_TRY(hipStreamIsCapturing(s, &cap), "hipStreamIsCapturing");
+        learn = cap == hipStreamCaptureStatusNone;
+        if (learn) counts_out = ctx->host_info_dev;
+    }
+    if (eager) ctx->counts_pending = false;   // host_info is this render's from here
+    pa.counts_out = n > 0 ? counts_out : nullptr;
     if (order_in_project) {
         pa.order_cost = static_cast<const uint32_t*>(w.tile_cost.p);
         pa.order = static_cast<uint32_t*>(w.tile_order.p);
@@ -477,6 +582,19 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     STAGE_MARK(1);
     ctx->lists_compared = try_lists;
 
+    // the host waits for the sizes of an eager render (K, to refuse 2^32
+    // pairs, and the bin entries, to size their buffer) only after the sort
+    // and the binning are queued: the GPU works on while they travel
+    if (eager && n > 0) {
+        if (!ctx->host_info_dev)
+            HIP_TRY(hipMemcpyAsync(ctx->host_info, counts_out, (size_t)V * kViewCounters * 4, hipMemcpyDeviceToHost, s),
+                    "read sizes");
+        HIP_TRY(hipEventRecord(ctx->sizes_ev, s), "hipEventRecord");
+    } else if (learn) {
+        HIP_TRY(hipEventRecord(ctx->sizes_ev, s), "hipEventRecord");
+        ctx->counts_pending = true;
+    }
+
     BinArgs ba{};
     ba.view_counts = view_counts;
     ba.rect = pa.rect;
@@ -484,34 +602,15 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     ba.n = n;
     ba.n_views = V;
     ba.views = views;
-    ba.row_tiles_x = static_cast<const uint32_t*>(w.row_tiles_x.p);
-    ba.rows = rows;
-    ba.max_tiles_x = max_tx;
-    ba.max_tiles_y = max_ty;
-    ba.tiles = T;
-    ba.items1 = tu.bin1_items;
-    ba.items2 = tu.bin2_items;
-    ba.chunks1 = chunks1;
-    ba.info = static_cast<uint32_t*>(w.bin_info.p);
-    ba.counts1 = static_cast<uint32_t*>(w.counts1.p);
-    ba.rows_off = static_cast<uint32_t*>(w.rows_off.p);
-    ba.tile_offsets = static_cast<uint32_t*>(w.tile_offsets.p);
+    ba.bins = bs.bins;
+    ba.max_bins = bs.max_bins;
+    ba.max_diff = bs.max_diff;
+    ba.items1 = bs.items1;
+    ba.chunk = bs.chunk;
+    ba.chunks1 = bs.chunks1;
+    ba.table = static_cast<uint32_t*>(w.bin_table.p);
     ba.overflow = counters + 1;
-    uint64_t capacity = o.pair_capacity;
-    int in_b = 1;
     ba.skip = try_lists ? counters + kCounterChanged + 1 : nullptr;
-    // pair_capacity > 0: every size below is the bound the capacity implies
-    // (row entries <= pairs); else the host reads K, R and the level-2 sizes
-    // once
-    ba.row_capacity = capacity ? capacity : ~0ull;
-    ba.max_chunks2 = capacity ? bin_level2_chunk_bound(capacity, rows, tu.bin2_items) : (1 << 30);
-    ba.counts2_capacity = capacity ? (uint64_t)ba.max_chunks2 * max_tx : ~0ull;
-    // scan lengths: level-1 counts, tile offsets and
-    // (pair_capacity > 0) the level-2 counts; the eager path grows the scratch
-    // for the level-2 counts after its host read
-    int64_t scan_max = std::max<int64_t>(T + 1, (int64_t)rows * chunks1);
-    if (capacity) scan_max = std::max<int64_t>(scan_max, (int64_t)ba.counts2_capacity);
-    if ((st = ensure(ctx, w.scan_scratch, scan_scratch_elems(scan_max) * 8)) != GS_OK) return st;
     uint64_t* scan_scratch = static_cast<uint64_t*>(w.scan_scratch.p);
     // one view of the same Gaussians as the last render: start from its order
     const bool reuse = !noalloc && (o.flags & GS_RENDER_REUSE_ORDER) && V == 1 && n > 0 && prev_order_n == n;
@@ -524,11 +623,6 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
                                    static_cast<uint32_t*>(w.sort_vb.p), n, reuse_words, s),
                 "order reuse");
     }
-    // the sort carries each Gaussian's packed rectangle to the binning, which
-    // then reads the rectangles in depth order instead of gathering them (not
-    // in a no-allocation render: its scratch is kept small); when a reused
-    // order skips the radix passes, one gather in that order writes them
-    const bool packed = fits_packed;
     HIP_TRY(launch_depth_sort(pa.depth_key, static_cast<uint32_t*>(w.sort_ka.p),
                               static_cast<uint32_t*>(w.sort_va.p), static_cast<uint32_t*>(w.sort_kb.p),
                               static_cast<uint32_t*>(w.sort_vb.p), packed ? pa.rect : nullptr,
@@ -544,100 +638,52 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     ba.sorted_idx = static_cast<const uint32_t*>(w.sort_vb.p);
     ba.sorted_pack = packed ? static_cast<const uint32_t*>(w.sort_pb.p) : nullptr;
     STAGE_MARK(2);
-    HIP_TRY(launch_bin_rows(ba, scan_scratch, s), "bin rows");
+    HIP_TRY(launch_bins_count(ba, scan_scratch, s), "bin counts");
     STAGE_MARK(3);
 
-    int grid2 = ba.max_chunks2;
-    bool rows_scattered = false;   // the row scatter ran while the host read the sizes
-    bool lists_held = false;       // the host read that the previous lists hold (eager)
-    if (capacity == 0) {
-        // eager: one host read (one copy) of the per-view pairs, R and the
-        // level-2 sizes
-        uint32_t* hi = ctx->host_info;
-        const int n_vc = V * kViewCounters;
-        // the sizes go straight into the pinned host buffer (its device
-        // address), else through a device buffer and a copy; the event below
-        // marks their arrival
-        uint32_t* rb = ctx->host_info_dev;
-        if (!rb) {
-            if ((st = ensure(ctx, w.readback, (size_t)(n_vc + kReadbackTail) * 4)) != GS_OK) return st;
-            rb = static_cast<uint32_t*>(w.readback.p);
-        }
-        hipLaunchKernelGGL(pack_readback_kernel, dim3(1), dim3(256), 0, s, (const uint32_t*)view_counts, n_vc,
-                           (const uint32_t*)counters, (const uint32_t*)(ba.rows_off + rows),
-                           (const uint32_t*)ba.info,
-                           rb);
-        HIP_TRY(hipGetLastError(), "read sizes");
-        if (!ctx->host_info_dev)
-            HIP_TRY(hipMemcpyAsync(hi, rb, (size_t)(n_vc + kReadbackTail) * 4, hipMemcpyDeviceToHost, s),
-                    "read sizes");
-        // the row scatter needs no size but R, and the row-entry buffer of
-        // earlier renders mostly holds this frame's entries: it runs while
-        // the host reads the sizes, and runs again into a grown buffer when R
-        // exceeds it (its stores past the buffer are dropped)
-        const uint64_t spec = w.row_ent.bytes / 8;
-        if (spec > 0) {
-            HIP_TRY(hipEventRecord(ctx->sizes_ev, s), "hipEventRecord");
-            ba.row_ent = static_cast<uint2*>(w.row_ent.p);
-            ba.row_capacity = spec;
-            STAGE_MARK(4);
-            HIP_TRY(launch_bin_row_scatter(ba, s), "bin row scatter");
-            STAGE_MARK(5);
-            rows_scattered = true;
+    // with a pair capacity the entry buffers hold that many entries (a
+    // Gaussian touches no more bins than tiles); an eager render scatters
+    // into the buffers of earlier renders, which mostly have room, before
+    // the host has read the sizes, and again into grown ones where they had
+    // not (stores past the buffers are dropped)
+    uint64_t capacity = o.pair_capacity, room = capacity;
+    if (eager) room = std::min<uint64_t>(w.bin_items.bytes / 4, w.bin_spans.bytes / 2) & ~uint64_t(3);
+    else if ((st = ensure_bin_entries(ctx, w, room)) != GS_OK) return st;
+    auto scatter = [&]() {
+        ba.items = static_cast<uint32_t*>(w.bin_items.p);
+        ba.spans = static_cast<uint16_t*>(w.bin_spans.p);
+        ba.capacity = room;
+        return launch_bins_scatter(ba, s);
+    };
+    if (room > 0) HIP_TRY(scatter(), "bin scatter");
+    STAGE_MARK(4);
+    if (eager) {
+        uint64_t K64 = 0, entries = 0;
+        if (n > 0) {
             HIP_TRY(hipEventSynchronize(ctx->sizes_ev), "hipEventSynchronize");
-        } else {
-            HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
+            for (int v = 0; v < V; ++v) {
+                const uint32_t* c = ctx->host_info + (size_t)v * kViewCounters;
+                K64 += (uint64_t)c[2] | ((uint64_t)c[3] << 32);
+                entries += (uint64_t)c[6] | ((uint64_t)c[7] << 32);
+            }
         }
-        uint32_t* tail = hi + n_vc;
-        uint64_t K64 = 0;
-        for (int v = 0; v < V; ++v) {
-            const uint32_t* c = hi + (size_t)v * kViewCounters;
-            K64 += (uint64_t)c[2] | ((uint64_t)c[3] << 32);
-        }
-        if (K64 > 0xFFFFFFFFull || tail[1] != 0u)
-            return fail(ctx, GS_ERR_CAPACITY, "more than 2^32-1 (Gaussian, tile) pairs");
+        if (K64 > 0xFFFFFFFFull) return fail(ctx, GS_ERR_CAPACITY, "more than 2^32-1 (Gaussian, tile) pairs");
         capacity = K64;
-        ba.row_capacity = tail[4];
-        if (rows_scattered && ba.row_capacity > spec) {
-            HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");   // the buffer is grown below
-            rows_scattered = false;
+        if (n > 0) ctx->next_shifts = suggested_shifts(hv, ctx->host_info);
+        if (entries > room || !w.bin_items.p) {
+            HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");   // the buffers are grown
+            if ((st = ensure_bin_entries(ctx, w, entries)) != GS_OK) return st;
+            room = entries;
+            STAGE_MARK(3);
+            HIP_TRY(scatter(), "bin scatter");
+            STAGE_MARK(4);
         }
-        grid2 = (int)tail[5];
-        ba.max_chunks2 = grid2;
-        ba.counts2_capacity = tail[6];
-        // counters[kCounterChanged + 1] came with the sizes: when the lists
-        // hold, the tile-level launches (which would skip) are not made
-        lists_held = try_lists && tail[kCounterChanged + 1] != 0u;
     }
-    ba.capacity = capacity;
-    // in eager mode nothing queued uses the buffers grown here (the kernels
-    // before the host read have completed; a row scatter still running uses
-    // the row-entry buffer, which then has room)
-    if ((st = ensure(ctx, w.scan_scratch, scan_scratch_elems((int64_t)std::max<uint64_t>(ba.counts2_capacity, 1)) *
-                                                 8)) != GS_OK)
-        return st;
-    scan_scratch = static_cast<uint64_t*>(w.scan_scratch.p);
-    const size_t rows_cap = (size_t)std::max<uint64_t>(ba.row_capacity, 1);
-    if ((st = ensure(ctx, w.row_ent, rows_cap * 8)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.counts2, (size_t)std::max<uint64_t>(ba.counts2_capacity, 1) * 4)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.values, (size_t)std::max<uint64_t>(capacity, 1) * 4)) != GS_OK) return st;
-    ba.row_ent = static_cast<uint2*>(w.row_ent.p);
-    ba.counts2 = static_cast<uint32_t*>(w.counts2.p);
-    ba.values = static_cast<uint32_t*>(w.values.p);
-    if (!rows_scattered) {
-        STAGE_MARK(4);
-        HIP_TRY(launch_bin_row_scatter(ba, s), "bin row scatter");
-        STAGE_MARK(5);
-    }
-    if (!lists_held) HIP_TRY(launch_bin_tiles(ba, grid2, scan_scratch, s), "bin tile counts");
-    STAGE_MARK(6);
-    if (!lists_held) HIP_TRY(launch_bin_tile_scatter(ba, grid2, s), "bin tile scatter");
-    STAGE_MARK(7);
+    STAGE_MARK(5);
 
     BlendArgs bl{};
     bl.splats = pa.splats;
-    bl.values = ba.values;
-    bl.tile_offsets = ba.tile_offsets;
+    bl.lists = bin_lists(ba);
     bl.views = views;
     bl.n_views = V;
     bl.tiles = T;
@@ -659,20 +705,17 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
         uint32_t* order = static_cast<uint32_t*>(w.tile_order.p);
         // ordered by the projection's extra workgroup, or here by list length
         if (!order_in_project)
-            HIP_TRY(launch_blend_order(nullptr, bl.tile_offsets, T, order, s), "blend order");
+            HIP_TRY(launch_blend_order(nullptr, bl.lists, views, V, T, order, s), "blend order");
         bl.order = order;
         // the queue head was cleared with the frame's counters
         if (tu.blend_group < 0) bl.queue = counters + kCounterBlendQueue;
     }
-    HIP_TRY(launch_blend(bl, capacity, s), "blend");
-    STAGE_MARK(8);
+    HIP_TRY(launch_blend(bl, s), "blend");
+    STAGE_MARK(6);
     if (noalloc) {
         // nothing of this render stays with the context but its sizes: the
         // next render on the device may overwrite the scratch
-        hipLaunchKernelGGL(pack_readback_kernel, dim3(1), dim3(256), 0, s, (const uint32_t*)view_counts,
-                           kViewCounters, (const uint32_t*)counters, (const uint32_t*)(ba.rows_off + rows),
-                           (const uint32_t*)ba.info, ctx->noalloc_info);
-        HIP_TRY(hipGetLastError(), "pack sizes");
+        if (n == 0) HIP_TRY(launch_fill_u32(ctx->noalloc_info, 0u, kViewCounters, s), "sizes");
         ctx->last_noalloc = true;
         ctx->n = n;
         ctx->n_views = V;
@@ -693,10 +736,11 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
 
     ctx->have_render = true;
     ctx->last_tuning = tu;
-    ctx->order_n = (V == 1 && in_b) ? n : -1;
+    ctx->order_n = V == 1 ? n : -1;
     ctx->last_reuse = reuse;
     ctx->lists_n = n;
     ctx->lists_sizes = sizes;
+    ctx->lists_shifts = view_shifts(hv);
     ctx->lists_cap = o.pair_capacity;
     ctx->last_views = hv;
     ctx->last_g = *g;
@@ -710,7 +754,8 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     ctx->tiles = T;
     ctx->rows = rows;
     ctx->capacity = capacity;
-    ctx->sorted_in_b = in_b;
+    ctx->bins = bl.lists;
+    ctx->packed = packed;
     ctx->stream = s;
     return GS_OK;
 }
@@ -739,20 +784,17 @@ size_t carve_noalloc(Workspace* w, unsigned char* base, int64_t n, const std::ve
     };
     const int V = (int)hv.size();
     const size_t ni = (size_t)std::max<int64_t>(n * V, 1);
-    const int rows = (int)(hv.back().row_base + hv.back().tiles_y);
     const int64_t T = (int64_t)hv.back().tile_base + (int64_t)hv.back().tiles_x * hv.back().tiles_y;
-    int max_tx = 0;
-    for (const ViewParams& v : hv) max_tx = std::max(max_tx, v.tiles_x);
-    const int chunks1 = std::max(bin_level1_chunks(n, tu.bin1_items), 1);
-    const int max_chunks2 = bin_level2_chunk_bound(capacity, rows, tu.bin2_items);
-    const uint64_t counts2_cap = (uint64_t)max_chunks2 * max_tx;
-    const int64_t scan_max = std::max<int64_t>(std::max<int64_t>(T + 1, (int64_t)rows * chunks1), (int64_t)counts2_cap);
+    const BinShape bs = bin_shape(hv, n, tu.bin1_items);
     take(ws.splats, ni * sizeof(Splat));
     take(ws.depth_key, ni * 4);
-    take(ws.radius, ni * 4);
-    take(ws.tiles_touched, ni * 4);
     take(ws.rect, ni * 8);
-    take(ws.sorted_rect, ni * 8);
+    if (bs.packed) {
+        take(ws.sort_pa, ni * 4);
+        take(ws.sort_pb, ni * 4);
+    } else {
+        take(ws.sorted_rect, ni * 8);
+    }
     take(ws.sort_ka, ni * 4);
     take(ws.sort_va, ni * 4);
     take(ws.sort_kb, ni * 4);
@@ -761,25 +803,19 @@ size_t carve_noalloc(Workspace* w, unsigned char* base, int64_t n, const std::ve
     take(ws.partials, project_partials_elems(n, V) * 4);
     take(ws.views, (size_t)V * sizeof(ViewParams));
     take(ws.view_counts, (size_t)V * kViewCounters * 4);
-    take(ws.row_tiles_x, (size_t)rows * 4);
-    take(ws.bin_info, bin_info_elems(rows) * 4);
-    take(ws.rows_off, (size_t)(rows + 1) * 4);
-    take(ws.counts1, (size_t)chunks1 * rows * 4);
+    take(ws.bin_table, bs.table_elems() * 4);
     take(ws.counters, 64);
-    take(ws.tile_offsets, (size_t)(T + 1) * 4);
-    take(ws.scan_scratch, scan_scratch_elems(scan_max) * 8);
-    take(ws.row_ent, (size_t)std::max<uint64_t>(capacity, 1) * 8);
-    take(ws.counts2, (size_t)std::max<uint64_t>(counts2_cap, 1) * 4);
-    take(ws.values, (size_t)std::max<uint64_t>(capacity, 1) * 4);
+    take(ws.scan_scratch, scan_scratch_elems(bs.bins * bs.chunks1) * 8);
+    take(ws.bin_items, (size_t)((std::max<uint64_t>(capacity, 4) + 3) & ~uint64_t(3)) * 4);
+    take(ws.bin_spans, (size_t)((std::max<uint64_t>(capacity, 4) + 3) & ~uint64_t(3)) * 2);
     take(ws.tile_cost, (size_t)std::max<int64_t>(T, 1) * 4);
     take(ws.tile_order, (size_t)std::max<int64_t>(T, 1) * 4);
     return off;
 }
 
-// The device-table entry of one view; tile_base / row_base follow the views
-// before it.
+// The device-table entry of one view; the bases follow the views before it.
 ViewParams make_view(const gs_camera* cam, int32_t width, int32_t height, float* out_rgb, float* out_T,
-                     uint32_t* out_nc, uint32_t tile_base, uint32_t row_base)
+                     uint32_t* out_nc, uint32_t tile_base, uint32_t row_base, uint32_t bin_base)
 {
     ViewParams v{};
     for (int k = 0; k < 9; ++k) v.R[k] = cam->R[k];
@@ -797,6 +833,7 @@ ViewParams make_view(const gs_camera* cam, int32_t width, int32_t height, float*
     v.tiles_y = (height + kTile - 1) / kTile;
     v.tile_base = tile_base;
     v.row_base = row_base;
+    set_bins(v, bin_base, bin_shift_of(v.tiles_x, v.tiles_y, 0.f));
     v.out_rgb = out_rgb;
     v.out_T = out_T;
     v.out_nc = out_nc;
@@ -834,7 +871,9 @@ gs_status gs_create(int device, gs_context** out)
     // the device's copy of the no-allocation scratch (once per device)
     if (e == hipSuccess) e = init_scratch_address(device, count);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->sizes_ev, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->lists.done, hipEventDisableTiming);
     if (e != hipSuccess) {
+        if (ctx->lists.done) (void)hipEventDestroy(ctx->lists.done);
         if (ctx->sizes_ev) (void)hipEventDestroy(ctx->sizes_ev);
         if (ctx->host_info) (void)hipHostFree(ctx->host_info);
         if (ctx->noalloc_info) (void)hipFree(ctx->noalloc_info);
@@ -850,13 +889,14 @@ void gs_destroy(gs_context* ctx)
     if (!ctx) return;
     if (ctx->graph) gs_graph_destroy(ctx->graph);
     (void)hipSetDevice(ctx->device);
-    DevBuf* bufs[] = {&ctx->grad2d, &ctx->back_views, &ctx->ws.splats, &ctx->ws.depth_key, &ctx->ws.radius, &ctx->ws.tiles_touched, &ctx->ws.rect,
-                      &ctx->ws.sort_ka, &ctx->ws.sort_va, &ctx->ws.sort_kb, &ctx->ws.sort_vb, &ctx->ws.hist,
-                      &ctx->ws.scan_scratch, &ctx->ws.bin_info, &ctx->ws.counts1, &ctx->ws.rows_off, &ctx->ws.row_ent,
-                      &ctx->ws.counts2, &ctx->ws.partials, &ctx->ws.views, &ctx->ws.row_tiles_x, &ctx->ws.view_counts,
-                      &ctx->ws.counters, &ctx->ws.tile_offsets, &ctx->ws.values, &ctx->ws.tile_work, &ctx->ws.sorted_rect,
-                      &ctx->ws.reuse_words, &ctx->ws.readback, &ctx->ws.tile_cost, &ctx->ws.tile_order,
-                      &ctx->ws.sort_pa, &ctx->ws.sort_pb};
+    Workspace& w = ctx->ws;
+    ListSpace& l = ctx->lists;
+    DevBuf* bufs[] = {&ctx->grad2d, &ctx->back_views, &w.splats, &w.depth_key, &w.radius, &w.tiles_touched, &w.rect,
+                      &w.sort_ka, &w.sort_va, &w.sort_kb, &w.sort_vb, &w.hist, &w.scan_scratch, &w.sort_pa, &w.sort_pb,
+                      &w.bin_table, &w.bin_items, &w.bin_spans, &w.partials, &w.sorted_rect, &w.readback, &w.views,
+                      &w.view_counts, &w.counters, &w.tile_work, &w.reuse_words, &w.tile_cost, &w.tile_order,
+                      &l.row_tiles_x, &l.info, &l.counts1, &l.rows_off, &l.row_ent, &l.counts2, &l.scan_scratch,
+                      &l.tile_offsets, &l.overflow};
     for (DevBuf* b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (ctx->host_info) (void)hipHostFree(ctx->host_info);
@@ -864,6 +904,7 @@ void gs_destroy(gs_context* ctx)
     for (hipEvent_t e : ctx->ev)
         if (e) (void)hipEventDestroy(e);
     if (ctx->sizes_ev) (void)hipEventDestroy(ctx->sizes_ev);
+    if (l.done) (void)hipEventDestroy(l.done);
     delete ctx;
 }
 
@@ -886,7 +927,8 @@ gs_status gs_render(gs_context* ctx, const gs_gaussians* g, const gs_camera* cam
     if (ctx->graph) return fail(ctx, GS_ERR_INVALID_ARGUMENT, "the context is bound to a render graph");
     gs_status st = validate(ctx, g, cam, width, height, opts, out_rgb);
     if (st != GS_OK) return st;
-    std::vector<ViewParams> hv(1, make_view(cam, width, height, out_rgb, out_final_T, out_n_contrib, 0u, 0u));
+    std::vector<ViewParams> hv(1, make_view(cam, width, height, out_rgb, out_final_T, out_n_contrib, 0u, 0u, 0u));
+    choose_bins(ctx, g->n, opts, hv);
     return render_views(ctx, g, hv, opts, static_cast<hipStream_t>(stream));
 }
 
@@ -900,7 +942,7 @@ gs_status gs_render_noalloc(gs_context* ctx, const gs_gaussians* g, const gs_cam
     if (st != GS_OK) return st;
     unsigned char* base = static_cast<unsigned char*>(scratch_address(ctx->device));
     if (!base) return fail(ctx, GS_ERR_HIP, "the device's no-allocation scratch has no address");
-    std::vector<ViewParams> hv(1, make_view(cam, width, height, out_rgb, out_final_T, out_n_contrib, 0u, 0u));
+    std::vector<ViewParams> hv(1, make_view(cam, width, height, out_rgb, out_final_T, out_n_contrib, 0u, 0u, 0u));
     const Tuning tu = ctx->tuning;
     uint64_t cap = opts ? opts->pair_capacity : 0;
     if (cap > 0xFFFFFFFFull) return fail(ctx, GS_ERR_CAPACITY, "pair_capacity must stay below 2^32");
@@ -941,6 +983,7 @@ gs_status gs_render_batched(gs_context* ctx, const gs_gaussians* g, const gs_vie
     std::vector<ViewParams> hv;
     gs_status st = build_views(ctx, g, views, n_views, opts, hv);
     if (st != GS_OK) return st;
+    choose_bins(ctx, g->n, opts, hv);
     return render_views(ctx, g, hv, opts, static_cast<hipStream_t>(stream));
 }
 
@@ -958,8 +1001,16 @@ gs_status gs_graph_create(gs_context* ctx, const gs_gaussians* g, const gs_view*
     hipStream_t s = static_cast<hipStream_t>(stream);
     // an eager render sizes every buffer (capture must not allocate) and
     // writes the view table
+    choose_bins(ctx, g->n, nullptr, hv);
     if ((st = render_views(ctx, g, hv, opts, s)) != GS_OK) return st;
     HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
+    // again where that render suggests other bins: the graph keeps its own
+    const std::vector<int> shifts = view_shifts(hv);
+    choose_bins(ctx, g->n, nullptr, hv);
+    if (view_shifts(hv) != shifts) {
+        if ((st = render_views(ctx, g, hv, opts, s)) != GS_OK) return st;
+        HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
+    }
     gs_graph* gr = new gs_graph();
     gr->ctx = ctx;
     gr->views = hv;
@@ -1001,8 +1052,10 @@ gs_status gs_graph_set_views(gs_graph* graph, const gs_view* views, int32_t n_vi
         if (st != GS_OK) return st;
         if (w.width != hv[v].width || w.height != hv[v].height)
             return fail(ctx, GS_ERR_INVALID_ARGUMENT, "view sizes must equal the captured ones");
-        hv[v] = make_view(&w.camera, w.width, w.height, w.out_rgb, w.out_final_T, w.out_n_contrib, hv[v].tile_base,
-                          hv[v].row_base);
+        const ViewParams was = hv[v];
+        hv[v] = make_view(&w.camera, w.width, w.height, w.out_rgb, w.out_final_T, w.out_n_contrib, was.tile_base,
+                          was.row_base, was.bin_base);
+        set_bins(hv[v], was.bin_base, was.bin_shift);   // as captured
     }
     HIP_TRY(hipSetDevice(ctx->device), "hipSetDevice");
     HIP_TRY(write_view_table(hv, static_cast<ViewParams*>(ctx->ws.views.p), static_cast<hipStream_t>(stream)),
@@ -1055,14 +1108,15 @@ gs_status build_views(gs_context* ctx, const gs_gaussians* g, const gs_view* vie
         return fail(ctx, GS_ERR_UNSUPPORTED, "n_views * n must stay below 2^32");
     hv.clear();
     hv.reserve((size_t)n_views);
-    int64_t tile_base = 0, row_base = 0;
+    int64_t tile_base = 0, row_base = 0, bin_base = 0;
     for (int v = 0; v < n_views; ++v) {
         const gs_view& w = views[v];
         if ((st = validate_view(ctx, &w.camera, w.width, w.height, w.out_rgb)) != GS_OK) return st;
         hv.push_back(make_view(&w.camera, w.width, w.height, w.out_rgb, w.out_final_T, w.out_n_contrib,
-                               (uint32_t)tile_base, (uint32_t)row_base));
+                               (uint32_t)tile_base, (uint32_t)row_base, (uint32_t)bin_base));
         tile_base += (int64_t)hv.back().tiles_x * hv.back().tiles_y;
         row_base += hv.back().tiles_y;
+        bin_base += (int64_t)hv.back().bins_x * hv.back().bins_y;
         if (row_base > kMaxTotalRows) return fail(ctx, GS_ERR_UNSUPPORTED, "more than 16384 tile rows over all views");
         if (tile_base >= (int64_t(1) << 31)) return fail(ctx, GS_ERR_UNSUPPORTED, "too many tiles over all views");
     }
@@ -1108,8 +1162,7 @@ gs_status gs_render_backward(gs_context* ctx, const gs_gaussians* g, const float
     HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(grad2d), 0u, items * kGrad2d, s), "clear gradients");
     BlendBackArgs bb{};
     bb.splats = static_cast<const Splat*>(ctx->ws.splats.p);
-    bb.values = static_cast<const uint32_t*>(ctx->ws.values.p);
-    bb.tile_offsets = static_cast<const uint32_t*>(ctx->ws.tile_offsets.p);
+    bb.lists = ctx->bins;
     bb.views = views;
     bb.n_views = V;
     bb.tiles = ctx->tiles;
@@ -1118,7 +1171,7 @@ gs_status gs_render_backward(gs_context* ctx, const gs_gaussians* g, const float
     bb.order = bb.group <= 0 ? static_cast<const uint32_t*>(ctx->ws.tile_order.p) : nullptr;
     for (int k = 0; k < 3; ++k) bb.bg[k] = ctx->last_bg[k];
     bb.grad2d = grad2d;
-    HIP_TRY(launch_blend_backward(bb, ctx->capacity, s), "blend backward");
+    HIP_TRY(launch_blend_backward(bb, s), "blend backward");
     ProjectBackArgs pb{};
     pb.n = g->n;
     pb.sh_degree = g->sh_degree;
@@ -1176,41 +1229,36 @@ gs_status gs_get_list_info(gs_context* ctx, gs_list_info* out)
 {
     if (!ctx || !out) return fail(ctx, GS_ERR_INVALID_ARGUMENT, "NULL argument");
     if (ctx->last_noalloc) {
-        // sizes a no-allocation render packed: view counters, the counters,
-        // R, level-2 sizes
+        // sizes a no-allocation render kept: the view counters
         HIP_TRY(hipSetDevice(ctx->device), "hipSetDevice");
-        uint32_t w[kViewCounters + 7];
+        uint32_t w[kViewCounters];
         HIP_TRY(hipMemcpyAsync(w, ctx->noalloc_info, sizeof w, hipMemcpyDeviceToHost, ctx->stream), "read sizes");
         HIP_TRY(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
         const uint64_t K = (uint64_t)w[2] | ((uint64_t)w[3] << 32);
         out->num_pairs = K;
-        out->num_row_entries = w[kViewCounters + 4];
+        out->num_row_entries = (uint64_t)w[4] | ((uint64_t)w[5] << 32);
         out->tiles_x = ctx->tiles_x;
         out->tiles_y = ctx->tiles_y;
         out->n_visible = (int64_t)w[0];
         out->num_tiles = ctx->tiles;
         out->num_views = ctx->n_views;
-        if (w[kViewCounters + 1] != 0 || K > ctx->capacity)
+        if (K > ctx->capacity)
             return fail(ctx, GS_ERR_CAPACITY, "the last render produced more pairs than pair_capacity");
         return GS_OK;
     }
     if (!ctx->have_render) return fail(ctx, GS_ERR_INVALID_ARGUMENT, "no render on this context yet");
     HIP_TRY(hipSetDevice(ctx->device), "hipSetDevice");
     std::vector<uint32_t> vc((size_t)ctx->n_views * kViewCounters);
-    uint32_t c[4], r32 = 0;
     HIP_TRY(hipMemcpyAsync(vc.data(), ctx->ws.view_counts.p, vc.size() * 4, hipMemcpyDeviceToHost, ctx->stream),
             "read view counts");
-    HIP_TRY(hipMemcpyAsync(c, ctx->ws.counters.p, sizeof c, hipMemcpyDeviceToHost, ctx->stream), "read counters");
-    HIP_TRY(hipMemcpyAsync(&r32, static_cast<uint32_t*>(ctx->ws.rows_off.p) + ctx->rows, sizeof r32,
-                           hipMemcpyDeviceToHost, ctx->stream),
-            "read R");
     HIP_TRY(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-    uint64_t K = 0, vis = 0;
+    uint64_t K = 0, R = 0, vis = 0;
     for (int v = 0; v < ctx->n_views; ++v) {
-        vis += vc[(size_t)v * kViewCounters];
-        K += (uint64_t)vc[(size_t)v * kViewCounters + 2] | ((uint64_t)vc[(size_t)v * kViewCounters + 3] << 32);
+        const uint32_t* c = vc.data() + (size_t)v * kViewCounters;
+        vis += c[0];
+        K += (uint64_t)c[2] | ((uint64_t)c[3] << 32);
+        R += (uint64_t)c[4] | ((uint64_t)c[5] << 32);
     }
-    const uint64_t R = r32;
     out->num_pairs = K;
     out->num_row_entries = R;
     out->tiles_x = ctx->tiles_x;
@@ -1218,10 +1266,85 @@ gs_status gs_get_list_info(gs_context* ctx, gs_list_info* out)
     out->n_visible = (int64_t)vis;
     out->num_tiles = ctx->tiles;
     out->num_views = ctx->n_views;
-    if (c[1] != 0 || K > ctx->capacity || R > K)
+    if (K > ctx->capacity)
         return fail(ctx, GS_ERR_CAPACITY, "the last render produced more pairs than pair_capacity");
     return GS_OK;
 }
+
+namespace {
+// The per-tile lists of the last render from its depth order: the values
+// and keys straight into the caller's buffers.
+gs_status write_lists(gs_context* ctx, const gs_list_info& info, uint32_t* values, uint32_t* tile_offsets,
+                      uint64_t* keys, hipStream_t s)
+{
+    gs_status st;
+    const std::vector<ViewParams>& hv = ctx->last_views;
+    const Workspace& w = ctx->ws;
+    ListSpace& l = ctx->lists;
+    const int64_t T = ctx->tiles, n = ctx->n;
+    const int rows = ctx->rows;
+    ListArgs la{};
+    for (const ViewParams& v : hv) {
+        la.max_tiles_x = std::max(la.max_tiles_x, v.tiles_x);
+        la.max_tiles_y = std::max(la.max_tiles_y, v.tiles_y);
+    }
+    const Tuning& tu = ctx->last_tuning;
+    la.chunks1 = std::max(bin_level1_chunks(n, tu.bin1_items), 1);
+    la.max_chunks2 = bin_level2_chunk_bound(info.num_row_entries, rows, tu.bin2_items);
+    la.counts2_capacity = (uint64_t)la.max_chunks2 * la.max_tiles_x;
+    const int64_t scan_max = std::max<int64_t>((int64_t)rows * la.chunks1, (int64_t)la.counts2_capacity);
+    if ((st = ensure(ctx, l.row_tiles_x, (size_t)rows * 8)) != GS_OK) return st;
+    if ((st = ensure(ctx, l.info, bin_info_elems(rows) * 4)) != GS_OK) return st;
+    if ((st = ensure(ctx, l.counts1, (size_t)la.chunks1 * rows * 4)) != GS_OK) return st;
+    if ((st = ensure(ctx, l.rows_off, (size_t)(rows + 1) * 4)) != GS_OK) return st;
+    if ((st = ensure(ctx, l.row_ent, (size_t)std::max<uint64_t>(info.num_row_entries, 1) * 8)) != GS_OK) return st;
+    if ((st = ensure(ctx, l.counts2, (size_t)la.counts2_capacity * 4)) != GS_OK) return st;
+    if ((st = ensure(ctx, l.scan_scratch, scan_scratch_elems(scan_max) * 8)) != GS_OK) return st;
+    if ((st = ensure(ctx, l.overflow, 4)) != GS_OK) return st;
+    if (!tile_offsets)
+        if ((st = ensure(ctx, l.tile_offsets, (size_t)(T + 1) * 4)) != GS_OK) return st;
+    la.sorted_idx = static_cast<const uint32_t*>(w.sort_vb.p);
+    la.view_counts = static_cast<const uint32_t*>(w.view_counts.p);
+    la.sorted_pack = ctx->packed ? static_cast<const uint32_t*>(w.sort_pb.p) : nullptr;
+    la.sorted_rect = static_cast<const ushort4*>(w.sorted_rect.p);
+    la.n = n;
+    la.n_views = ctx->n_views;
+    la.views = static_cast<const ViewParams*>(w.views.p);
+    uint32_t* row_table = static_cast<uint32_t*>(l.row_tiles_x.p);
+    la.row_tiles_x = row_table;
+    la.row_tile0 = row_table + rows;
+    la.depth_key = static_cast<const uint32_t*>(w.depth_key.p);
+    la.rows = rows;
+    la.tiles = T;
+    la.items1 = tu.bin1_items;
+    la.items2 = tu.bin2_items;
+    la.info = static_cast<uint32_t*>(l.info.p);
+    la.counts1 = static_cast<uint32_t*>(l.counts1.p);
+    la.rows_off = static_cast<uint32_t*>(l.rows_off.p);
+    la.row_ent = static_cast<uint2*>(l.row_ent.p);
+    la.row_capacity = info.num_row_entries;
+    la.counts2 = static_cast<uint32_t*>(l.counts2.p);
+    la.tile_offsets = tile_offsets ? tile_offsets : static_cast<uint32_t*>(l.tile_offsets.p);
+    la.values = values;
+    la.keys = keys;
+    la.capacity = info.num_pairs;
+    la.overflow = static_cast<uint32_t*>(l.overflow.p);
+    uint64_t* scan_scratch = static_cast<uint64_t*>(l.scan_scratch.p);
+    // (a stream under capture takes no part in that order: its caller orders
+    // the replays)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(s, &cap), "hipStreamIsCapturing");
+    const bool ordered = cap == hipStreamCaptureStatusNone;
+    if (ordered) HIP_TRY(hipStreamWaitEvent(s, l.done, 0), "hipStreamWaitEvent");
+    hipLaunchKernelGGL(row_table_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, la.views, la.n_views,
+                       row_table, row_table + rows, rows);
+    HIP_TRY(hipGetLastError(), "row table");
+    HIP_TRY(launch_list_rows(la, scan_scratch, s), "list rows");
+    HIP_TRY(launch_list_tiles(la, scan_scratch, s), "list tiles");
+    if (ordered) HIP_TRY(hipEventRecord(l.done, s), "hipEventRecord");
+    return GS_OK;
+}
+}  // namespace
 
 gs_status gs_copy_lists(gs_context* ctx, uint32_t* values, uint32_t* tile_offsets, uint64_t* keys, void* stream)
 {
@@ -1230,19 +1353,7 @@ gs_status gs_copy_lists(gs_context* ctx, uint32_t* values, uint32_t* tile_offset
     gs_list_info info;
     gs_status st = gs_get_list_info(ctx, &info);
     if (st != GS_OK) return st;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t T = ctx->tiles;
-    if (values && info.num_pairs)
-        HIP_TRY(hipMemcpyAsync(values, ctx->ws.values.p, info.num_pairs * 4, hipMemcpyDeviceToDevice, s), "copy values");
-    if (tile_offsets)
-        HIP_TRY(hipMemcpyAsync(tile_offsets, ctx->ws.tile_offsets.p, (size_t)(T + 1) * 4, hipMemcpyDeviceToDevice, s),
-                "copy offsets");
-    if (keys)
-        HIP_TRY(launch_write_keys(static_cast<const uint32_t*>(ctx->ws.values.p),
-                                  static_cast<const uint32_t*>(ctx->ws.tile_offsets.p),
-                                  static_cast<const uint32_t*>(ctx->ws.depth_key.p), T, keys, s),
-                "write keys");
-    return GS_OK;
+    return write_lists(ctx, info, values, tile_offsets, keys, static_cast<hipStream_t>(stream));
 }
 
 gs_status gs_copy_projection(gs_context* ctx, float* splats, uint32_t* depth_key, int32_t* radius,
@@ -1282,11 +1393,13 @@ gs_status gs_get_stage_times(gs_context* ctx, float* ms, int32_t count)
     if (count != GS_NUM_STAGES) return fail(ctx, GS_ERR_INVALID_ARGUMENT, "count must be GS_NUM_STAGES");
     if (!(ctx->have_render || ctx->last_noalloc) || !ctx->timed)
         return fail(ctx, GS_ERR_INVALID_ARGUMENT, "the last render was not timed (gs_set_profiling)");
-    HIP_TRY(hipEventSynchronize(ctx->ev[8]), "hipEventSynchronize");
-    const int from[GS_NUM_STAGES] = {0, 1, 2, 4, 5, 6, 7};
-    const int to[GS_NUM_STAGES] = {1, 2, 3, 5, 6, 7, 8};
-    for (int k = 0; k < GS_NUM_STAGES; ++k)
-        HIP_TRY(hipEventElapsedTime(&ms[k], ctx->ev[from[k]], ctx->ev[to[k]]), "hipEventElapsedTime");
+    HIP_TRY(hipEventSynchronize(ctx->ev[6]), "hipEventSynchronize");
+    const int from[GS_NUM_STAGES] = {0, 1, 2, 3, -1, -1, 5};
+    for (int k = 0; k < GS_NUM_STAGES; ++k) {
+        ms[k] = 0.f;   // a render has no tile-level binning stages
+        if (from[k] >= 0)
+            HIP_TRY(hipEventElapsedTime(&ms[k], ctx->ev[from[k]], ctx->ev[from[k] + 1]), "hipEventElapsedTime");
+    }
     return GS_OK;
 }
 
@@ -1359,6 +1472,7 @@ gs_status gs_autotune(gs_context* ctx, const gs_gaussians* g, const gs_view* vie
     const uint32_t saved_flags = ctx->profiling;
     const Tuning start = ctx->tuning;
     Tuning cur = start;
+    choose_bins(ctx, g->n, nullptr, hv);
     if ((st = gs_set_profiling(ctx, GS_PROFILE_STAGES)) != GS_OK) return st;   // creates the stage events
     int k_out = 0;
     for (const TuneParam& p : kTuneParams) {

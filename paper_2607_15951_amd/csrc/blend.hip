@@ -62,6 +62,7 @@ struct BlendLds {
     float4 s2[kBatch + kUnroll];   // r, g, b, list position (int bits)
     uint32_t s_mask[kBatch + kUnroll];   // quads (waves) the entry can reach
     uint32_t s_wave_keep[4 * (kBatch > 256 ? kBatch / 256 : 1)];
+    TilePick pick;
     unsigned long long s_ev[4], s_co[4];   // tracing only
     uint32_t s_bodies[4];
 };
@@ -75,7 +76,7 @@ struct BlendLds {
 // all 256 threads of the workgroup with the same tile; the LDS is free again
 // once every thread has returned.
 template <bool kStats, int kBatch>
-__device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, uint64_t capacity, int tile, BlendLds<kBatch>& L)
+__device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, int tile, BlendLds<kBatch>& L)
 {
     constexpr int kPer = kBatch > 256 ? kBatch / 256 : 1;   // entries a lane stages per batch
     constexpr int kWords = kBatch / 64;                     // 64-entry mask words of a batch
@@ -86,6 +87,7 @@ __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, uint64_t cap
     uint32_t* s_mask = L.s_mask;
     uint32_t* s_wave_keep = L.s_wave_keep;
     if (tile >= a.tiles) return;
+    tile = __builtin_amdgcn_readfirstlane(tile);   // uniform: it and what follows from it stay scalar
     // the view owning this global tile: its size, tile grid and outputs
     const ViewParams& vp = a.views[view_of_tile(a.views, a.n_views, (uint32_t)tile)];
     const int width = vp.width, height = vp.height;
@@ -98,39 +100,38 @@ __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, uint64_t cap
     const int lx = (wave & 1) * 8 + (lane & 7), ly = (wave >> 1) * 8 + (lane >> 3);
     const int px = tx * kTile + lx, py = ty * kTile + ly;
     const bool inside = px < width && py < height;
-    uint64_t start = a.tile_offsets[tile], end = a.tile_offsets[tile + 1];
-    if (end > capacity) end = capacity;
-    if (start > end) start = end;
+    TileCursor tc;
+    tc.start(a.lists, vp, tx, ty);
     const double ox = (double)(tx * kTile), oy = (double)(ty * kTile);
     const float fx = (float)lx, fy = (float)ly;
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 
     float Tr = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
     uint32_t last = 0, term = 0, composited = 0, staged = 0, bodies = 0;
     bool done = !inside;
-    // software pipeline of the gathers: list values two batches ahead, the
-    // 48-byte records one batch ahead, both overlapping the compositing.
+    // software pipeline of the gathers: entries picked from the bin's list
+    // two batches ahead, the 48-byte records one batch ahead, both
+    // overlapping the compositing.
     // Lane tid stages the batch entries tid + 256 p (p < kPer) below kBatch.
     const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    uint32_t g_after[kPer];
+    tc.begin_pick(L.pick, wave, lane);
+    tc.fill(L.pick, 2 * kBatch, wave, lane);
     float4 na[kPer], nb[kPer], nc[kPer];
 #pragma unroll
     for (int p = 0; p < kPer; ++p) {
         const int slot = p * 256 + tid;
         const bool act = kBatch >= 256 || slot < kBatch;
-        const uint32_t g_next = (act && start + slot < end) ? a.values[start + slot] : 0u;
-        g_after[p] = (act && start + kBatch + slot < end) ? a.values[start + kBatch + slot] : 0u;
         na[p] = nb[p] = nc[p] = zero4;
-        if (act && start + slot < end) {
-            const float4* rec = reinterpret_cast<const float4*>(a.splats + g_next);
+        if (act && (uint32_t)slot < tc.tail) {
+            const float4* rec = reinterpret_cast<const float4*>(a.splats + L.pick.ring[slot]);
             na[p] = rec[0];
             nb[p] = rec[1];
             nc[p] = rec[2];
         }
     }
-    uint64_t b0 = start;
-    for (; b0 < end; b0 += kBatch) {
+    uint32_t b0 = 0;   // list position of the batch
+    for (; b0 < tc.tail; b0 += kBatch) {
         if (__syncthreads_count(!done) == 0) break;
+        const uint32_t tail = tc.tail;   // at least two batches past b0, or the list's length
         // stage: the lane's entries, each dropped when no pixel of the tile
         // can reach alpha 1/255 (the per-pixel test would skip it everywhere)
         bool keep[kPer];
@@ -140,19 +141,11 @@ __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, uint64_t cap
         for (int p = 0; p < kPer; ++p) {
             const int slot = p * 256 + tid;
             const bool act = kBatch >= 256 || slot < kBatch;
-            const float4 ra = na[p], rb = nb[p], rc = nc[p];
-            if (act && b0 + kBatch + slot < end) {
-                const float4* rec = reinterpret_cast<const float4*>(a.splats + g_after[p]);
-                na[p] = rec[0];
-                nb[p] = rec[1];
-                nc[p] = rec[2];
-            }
-            g_after[p] = (act && b0 + 2 * kBatch + slot < end) ? a.values[b0 + 2 * kBatch + slot] : 0u;
-            const uint64_t e = b0 + slot;
+            const uint32_t e = b0 + slot;
             keep[p] = false;
             qmask[p] = 0u;
-            if (act && e < end) {
-                qmask[p] = stage_entry(ra, rb, rc, ox, oy, (uint32_t)(e - start), v0[p], v1[p], v2[p]);
+            if (act && e < tail) {
+                qmask[p] = stage_entry(na[p], nb[p], nc[p], ox, oy, e, v0[p], v1[p], v2[p]);
                 keep[p] = qmask[p] != 0u;
             }
         }
@@ -164,22 +157,48 @@ __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, uint64_t cap
             km[p] = __ballot(keep[p]);
             if (lane == 0) s_wave_keep[p * 4 + wave] = (uint32_t)__popcll(km[p]);
         }
-        if (kStats) staged += (end - b0 < (uint64_t)kBatch) ? (uint32_t)(end - b0) : (uint32_t)kBatch;
+        if (kStats) staged += tail - b0 < (uint32_t)kBatch ? tail - b0 : (uint32_t)kBatch;
         __syncthreads();
+        int nk = 0;
+        uint32_t before[kPer];   // kept entries ahead of the wave's
+#pragma unroll
+        for (int p = 0; p < kPer; ++p)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                if (w == 0) before[p] = 0u;
+                if (w == wave) before[p] = (uint32_t)nk;
+                nk += __builtin_amdgcn_readfirstlane((int)s_wave_keep[p * 4 + w]);
+            }
 #pragma unroll
         for (int p = 0; p < kPer; ++p) {
-            uint32_t slot = (uint32_t)__popcll(km[p] & lt);
-            for (int i = 0; i < p * 4 + wave; ++i) slot += s_wave_keep[i];
             if (keep[p]) {
+                const uint32_t slot = __builtin_amdgcn_mbcnt_hi(
+                    (uint32_t)(km[p] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)km[p], before[p]));
                 s0[slot] = v0[p];
                 s1[slot] = v1[p];
                 s2[slot] = v2[p];
                 s_mask[slot] = qmask[p];
             }
         }
-        int nk = 0;
+        // (this batch's registers are free from here)
+        // a round for the batch after next; its loads go first, so that they
+        // can be waited for while the records are under way
+        const bool round = tail < b0 + 3 * kBatch && tc.more();
+        Pick4 pk;
+        if (round) tc.test(L.pick, pk, wave, lane);
+        // the next batch's records
 #pragma unroll
-        for (int i = 0; i < 4 * kPer; ++i) nk += (int)s_wave_keep[i];
+        for (int p = 0; p < kPer; ++p) {
+            const int slot = p * 256 + tid;
+            const bool act = kBatch >= 256 || slot < kBatch;
+            if (act && b0 + kBatch + slot < tail) {
+                const float4* rec =
+                    reinterpret_cast<const float4*>(a.splats + L.pick.ring[(b0 + kBatch + slot) & (kRing - 1)]);
+                na[p] = rec[0];
+                nb[p] = rec[1];
+                nc[p] = rec[2];
+            }
+        }
         if (tid < kUnroll) {   // padding entries reach no quad
             s0[nk + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
             s1[nk + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -187,6 +206,15 @@ __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, uint64_t cap
             s_mask[nk + tid] = 0u;
         }
         __syncthreads();
+        // every wave's count of the round is in; the ring is read again only
+        // past the next batch's barriers
+        if (round) tc.put(L.pick, pk, wave);
+        // a list whose bin holds more than four entries per entry of the
+        // tile: further rounds, once every wave has read the counts
+        if (tc.tail < b0 + 3 * kBatch && tc.more()) {
+            __syncthreads();
+            tc.fill(L.pick, b0 + 3 * kBatch, wave, lane);
+        }
         // this wave's entries of the batch: bit j of bits[j / 64] when entry j
         // can reach the wave's quad (scalar registers, no per-entry LDS read)
         uint64_t bits[kWords];
@@ -237,7 +265,7 @@ __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, uint64_t cap
     }
     if (kStats) {   // tracing only: one record per tile, no shared counters
         // a pixel examines its tile's list up to its terminating entry
-        const uint32_t list_len = (uint32_t)(end - start);
+        const uint32_t list_len = tc.tail;   // whole when a pixel walked past every entry
         unsigned long long ev = inside ? (term ? term : list_len) : 0u, co = composited;
         for (int o = 32; o > 0; o >>= 1) {
             ev += __shfl_xor(ev, o, 64);
@@ -261,7 +289,7 @@ __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, uint64_t cap
     }
     // the work of this tile, for the next frame's dispatch order: list
     // entries walked before every pixel had terminated
-    if (a.tile_cost && tid == 0) a.tile_cost[tile] = (uint32_t)((b0 < end ? b0 : end) - start);
+    if (a.tile_cost && tid == 0) a.tile_cost[tile] = b0 < tc.tail ? b0 : tc.tail;
     if (!inside) return;
     const int64_t P = (int64_t)width * height;
     const int64_t p = (int64_t)py * width + px;
@@ -278,10 +306,10 @@ __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, uint64_t cap
 // compiler's own register budget, where the tracing counters need no spills.
 template <bool kStats, int kBatch>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kStats ? 1 : blend_waves<kBatch>()))) void
-blend_kernel(BlendArgs a, uint64_t capacity)
+blend_kernel(BlendArgs a)
 {
     __shared__ BlendLds<kBatch> lds;
-    blend_tile_walk<kStats, kBatch>(a, capacity, blend_tile(a.order, a.group), lds);
+    blend_tile_walk<kStats, kBatch>(a, blend_tile(a.order, a.group), lds);
 }
 
 // Persistent form: a grid of at most as many workgroups as the chip holds at
@@ -300,7 +328,7 @@ blend_kernel(BlendArgs a, uint64_t capacity)
 // needs a register across the walk and was slower still.
 template <int kBatch>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(blend_waves<kBatch>() - 1))) void
-blend_queue_kernel(BlendArgs a, uint64_t capacity)
+blend_queue_kernel(BlendArgs a)
 {
     __shared__ BlendLds<kBatch> lds;
     __shared__ uint32_t s_item;
@@ -310,7 +338,7 @@ blend_queue_kernel(BlendArgs a, uint64_t capacity)
         const uint32_t item = s_item;
         __syncthreads();   // every thread has read s_item before thread 0 writes the next
         if ((int64_t)item >= a.tiles) break;
-        blend_tile_walk<false, kBatch>(a, capacity, (int)a.order[item], lds);
+        blend_tile_walk<false, kBatch>(a, (int)a.order[item], lds);
     }
 }
 
@@ -319,31 +347,24 @@ blend_queue_kernel(BlendArgs a, uint64_t capacity)
 // 1024-thread workgroup, each tile's bucket kept in LDS between the passes.
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderKeptTiles = 32768;
-__global__ __launch_bounds__(kOrderThreads) void blend_order_kernel(const uint32_t* __restrict__ cost,
-                                                                    const uint32_t* __restrict__ offsets,
+__global__ __launch_bounds__(kOrderThreads) void blend_order_kernel(const uint32_t* __restrict__ cost, BinLists lists,
+                                                                    const ViewParams* views, int n_views,
                                                                     int64_t tiles, uint32_t* __restrict__ order)
 {
     __shared__ uint32_t hist[kOrderBuckets];
     __shared__ uint16_t s_bucket[kOrderKeptTiles];
     __shared__ uint32_t wsum[kOrderThreads / 64];
-    order_heaviest_first<kOrderThreads>(cost, offsets, tiles, order, hist, wsum, s_bucket, kOrderKeptTiles);
+    if (cost)
+        order_heaviest_first<kOrderThreads>(WalkedCost{cost}, tiles, order, hist, wsum, s_bucket, kOrderKeptTiles);
+    else
+        order_heaviest_first<kOrderThreads>(ListLengthCost{lists, views, n_views}, tiles, order, hist, wsum, s_bucket,
+                                            kOrderKeptTiles);
 }
 
 __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* p, uint32_t v, int64_t n)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < n) p[i] = v;
-}
-
-// keys[j] = tile << 32 | depth bits of values[j], one block per tile
-__global__ __launch_bounds__(256) void write_keys_kernel(const uint32_t* __restrict__ values,
-                                                         const uint32_t* __restrict__ offsets,
-                                                         const uint32_t* __restrict__ depth_key,
-                                                         uint64_t* __restrict__ keys)
-{
-    const uint64_t t = blockIdx.x;
-    const uint32_t s = offsets[t], e = offsets[t + 1];
-    for (uint32_t j = s + threadIdx.x; j < e; j += 256) keys[j] = (t << 32) | depth_key[values[j]];
 }
 
 // Workgroups of a 256-thread kernel that the current device holds at once
@@ -372,7 +393,7 @@ int64_t resident_blocks(K kernel, int batch)
 
 }  // namespace
 
-hipError_t launch_blend(const BlendArgs& a, uint64_t capacity, hipStream_t s)
+hipError_t launch_blend(const BlendArgs& a, hipStream_t s)
 {
     const int64_t T = a.tiles;
     if (T <= 0) return hipSuccess;
@@ -380,7 +401,7 @@ hipError_t launch_blend(const BlendArgs& a, uint64_t capacity, hipStream_t s)
         auto go = [&](auto kernel) {
             const int64_t r = resident_blocks(kernel, a.batch);   // 0: one workgroup per tile
             const int blocks = (int)(r > 0 ? std::min<int64_t>(T, r) : T);
-            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, a, capacity);
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, a);
         };
         switch (a.batch) {
         case 128: go(blend_queue_kernel<128>); break;
@@ -391,7 +412,7 @@ hipError_t launch_blend(const BlendArgs& a, uint64_t capacity, hipStream_t s)
         return hipGetLastError();
     }
     const int blocks = blend_grid(T, a.order, a.group);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, a, capacity); };
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, a); };
     switch (a.batch) {
     case 128: a.tile_work ? go(blend_kernel<true, 128>) : go(blend_kernel<false, 128>); break;
     case 512: a.tile_work ? go(blend_kernel<true, 512>) : go(blend_kernel<false, 512>); break;
@@ -401,11 +422,12 @@ hipError_t launch_blend(const BlendArgs& a, uint64_t capacity, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_blend_order(const uint32_t* cost, const uint32_t* tile_offsets, int64_t tiles, uint32_t* order,
-                              hipStream_t s)
+hipError_t launch_blend_order(const uint32_t* cost, const BinLists& lists, const ViewParams* views, int n_views,
+                              int64_t tiles, uint32_t* order, hipStream_t s)
 {
     if (tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(blend_order_kernel, dim3(1), dim3(kOrderThreads), 0, s, cost, tile_offsets, tiles, order);
+    hipLaunchKernelGGL(blend_order_kernel, dim3(1), dim3(kOrderThreads), 0, s, cost, lists, views, n_views,
+                       tiles, order);
     return hipGetLastError();
 }
 
@@ -413,15 +435,6 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, v, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_write_keys(const uint32_t* values, const uint32_t* tile_offsets, const uint32_t* depth_key,
-                             int64_t tiles, uint64_t* keys, hipStream_t s)
-{
-    if (tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(write_keys_kernel, dim3((unsigned)tiles), dim3(256), 0, s, values, tile_offsets, depth_key,
-                       keys);
     return hipGetLastError();
 }
 

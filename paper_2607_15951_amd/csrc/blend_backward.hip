@@ -24,9 +24,9 @@
 // cross-lane instructions as they need (below) and added into an LDS row of
 // the staged entry; what the moments share (the conic, the opacity, factors)
 // is applied once per tile and entry, after the batch, on the way to nine
-// atomic adds in HBM.  At 3M Gaussians and 1920x1080: 525 us, 672 with nine
+// atomic adds in HBM.  At 3M Gaussians and 1920x1080: 535 us, 672 with nine
 // full gradients per pixel and a trading butterfly; four 640x480 views of 300K:
-// 355 us, 498 so; 20K at 317x179: 164 us, 288 so.
+// 379 us, 498 so; 20K at 317x179: 176 us, 288 so.
 // (Matrix instructions over 16 rows of moments of four entries took 246 us of
 // the matrix cores at the first size and 811 us in all: their sums leave in
 // more lanes than LDS atomics take quickly.)
@@ -36,7 +36,7 @@ namespace gsmi {
 namespace {
 
 constexpr float kLn2 = 0.69314718055994531f;
-constexpr int kBackBatch = 256;   // entries staged per batch
+constexpr int kBackBatch = 192;   // entries staged per batch
 
 // The sums of an entry over a tile's pixels, with gp = dL/dp and w = a T, in
 // the order in which wave_sum9 leaves them in the lanes.
@@ -50,6 +50,7 @@ struct BackLds {
     float s_acc[kBackBatch][kGrad2d];
     uint32_t s_wave_keep[4];
     uint8_t s_mask[kBackBatch];
+    TilePick pick;
 };
 
 // Half sums of two values at once: lanes 0-31 (even rows of 16 for the
@@ -117,8 +118,7 @@ __device__ __forceinline__ float entry_gradient(int c, const float* s, const flo
     }
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void blend_backward_kernel(
-    BlendBackArgs a, uint64_t capacity)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void blend_backward_kernel(BlendBackArgs a)
 {
     __shared__ BackLds L;
     int tile = blend_tile(a.order, a.group);
@@ -132,9 +132,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
     const int lx = (wave & 1) * 8 + (lane & 7), ly = (wave >> 1) * 8 + (lane >> 3);
     const int px = tx * kTile + lx, py = ty * kTile + ly;
     const bool inside = px < width && py < height;
-    const uint64_t start = min(a.tile_offsets[tile], capacity);
-    const uint32_t tail = (uint32_t)(min(a.tile_offsets[tile + 1], capacity) - start);
-    const uint32_t* const items = a.values + start;
+    TileCursor tc;
+    tc.start(a.lists, vp, tx, ty);
     const double ox = (double)(tx * kTile), oy = (double)(ty * kTile);
     const float fx = (float)lx, fy = (float)ly;
 
@@ -156,6 +155,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
         XT = (G0 * a.bg[0] + G1 * a.bg[1] + G2 * a.bg[2] + (vp.grad_T ? vp.grad_T[p] : 0.f)) * Tf;
     }
     float Tr = 1.0f;
+    // the lane's place among an entry's sums (wave_sum9)
+    const bool holds = (lane & 7) == 0 || lane == 63;
+    const int slot = lane == 63 ? 8 : ((lane & 8) >> 1) + (lane >> 4);
+    float* const acc = &L.s_acc[0][slot];
+
+    // the forward's pipeline: entries picked two batches ahead, records one
+    tc.begin_pick(L.pick, wave, lane);
+    tc.fill(L.pick, 2 * kBackBatch, wave, lane);
+    float4 na = make_float4(0.f, 0.f, 0.f, 0.f), nb = na, ncl = na;
+    uint32_t item = 0u;
+    if (tid < kBackBatch && (uint32_t)tid < tc.tail) {
+        item = L.pick.ring[tid];
+        const float4* rec = reinterpret_cast<const float4*>(a.splats + item);
+        na = rec[0];
+        nb = rec[1];
+        ncl = rec[2];
+    }
     // the last list position that a pixel of the wave, and of the tile, takes
     uint32_t wave_last = nc;
 #pragma unroll
@@ -166,28 +182,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
     const uint32_t tile_last = (uint32_t)__builtin_amdgcn_readfirstlane(
         (int)max(max(L.s_wave_keep[0], L.s_wave_keep[1]), max(L.s_wave_keep[2], L.s_wave_keep[3])));
     if (tile_last == 0u) return;
-    // the lane's place among an entry's sums (wave_sum9)
-    const bool holds = (lane & 7) == 0 || lane == 63;
-    const int slot = lane == 63 ? 8 : ((lane & 8) >> 1) + (lane >> 4);
-    float* const acc = &L.s_acc[0][slot];
-
-    // the forward's pipeline: the next batch's records are under way during this one
-    const uint32_t end = min(tail, tile_last);
-    float4 na = make_float4(0.f, 0.f, 0.f, 0.f), nb = na, ncl = na;
-    uint32_t item = 0u;
-    if ((uint32_t)tid < end) {
-        item = items[tid];
-        const float4* rec = reinterpret_cast<const float4*>(a.splats + item);
-        na = rec[0];
-        nb = rec[1];
-        ncl = rec[2];
-    }
-    for (uint32_t b0 = 0; b0 < end; b0 += kBackBatch) {
-        __syncthreads();   // the previous batch's rows
-        const uint32_t e = b0 + tid;
+    for (uint32_t b0 = 0; b0 < min(tc.tail, tile_last); b0 += kBackBatch) {
+        __syncthreads();   // the previous batch's rows and the ring's picks
+        const uint32_t tail = tc.tail, e = b0 + tid;
         uint32_t qmask = 0u;
         float4 v0, v1, v2;
-        if (e < end) qmask = stage_entry(na, nb, ncl, ox, oy, e, v0, v1, v2);
+        if (tid < kBackBatch && e < min(tail, tile_last)) qmask = stage_entry(na, nb, ncl, ox, oy, e, v0, v1, v2);
         const bool keep = qmask != 0u;
         const uint64_t km = __ballot(keep);
         if (lane == 0) L.s_wave_keep[wave] = (uint32_t)__popcll(km);
@@ -209,14 +209,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
             L.s_item[at] = item;
         }
         for (int k = tid; k < nk * kGrad2d; k += 256) (&L.s_acc[0][0])[k] = 0.f;
-        if (e + kBackBatch < end) {
-            item = items[e + kBackBatch];
+        const bool round = tail < b0 + 3 * kBackBatch && tc.more();
+        Pick4 pk;
+        if (round) tc.test(L.pick, pk, wave, lane);
+        if (tid < kBackBatch && e + kBackBatch < tail) {
+            item = L.pick.ring[(e + kBackBatch) & (kRing - 1)];
             const float4* rec = reinterpret_cast<const float4*>(a.splats + item);
             na = rec[0];
             nb = rec[1];
             ncl = rec[2];
         }
         __syncthreads();
+        if (round) tc.put(L.pick, pk, wave);
+        if (tc.tail < b0 + 3 * kBackBatch && tc.more()) {
+            __syncthreads();   // every wave has read the round's counts
+            tc.fill(L.pick, b0 + 3 * kBackBatch, wave, lane);
+        }
         for (int q = 0; q < nk; q += 64) {
             const int jj = q + lane;
             uint64_t bits = __builtin_amdgcn_ballot_w64(jj < nk && ((L.s_mask[jj] >> wave) & 1u) &&
@@ -270,11 +278,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
 
 }  // namespace
 
-hipError_t launch_blend_backward(const BlendBackArgs& a, uint64_t capacity, hipStream_t s)
+hipError_t launch_blend_backward(const BlendBackArgs& a, hipStream_t s)
 {
     if (a.tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(blend_backward_kernel, dim3(blend_grid(a.tiles, a.order, a.group)), dim3(256), 0, s,
-                       a, capacity);
+    hipLaunchKernelGGL(blend_backward_kernel, dim3(blend_grid(a.tiles, a.order, a.group)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -93,6 +93,182 @@ __device__ __forceinline__ float entry_alpha(const float4& e0, const float4& e1,
     return fminf(0.99f, e1.w * E);
 }
 
+// The entries of one tile, picked in order out of its bin's list by the 256
+// threads of a workgroup.  A round passes over kRound entries of the bin, four
+// consecutive ones per lane: an entry belongs to the tile when its part of
+// the bin covers it, one subtraction per two entries (each 4-bit field of
+// (tile | guard) - span keeps its guard bit when the tile lies inside the
+// span on that side).  The picked items go to a ring in LDS; an entry's index
+// in the ring's sequence is its position in the tile's list of Sec. 3.1.  A
+// round is about 30 VALU instructions per wave and 256 entries, where staging
+// takes 380 per 64 picked ones.
+constexpr int kRound = 1024;
+constexpr int kRing = 2048;
+
+struct TilePick {
+    uint32_t ring[kRing];
+    uint32_t count[4];
+};
+
+// Four entries of a lane: which of them the tile takes, over the wave, and
+// their items.
+struct Pick4 {
+    uint64_t m[4] = {0, 0, 0, 0};
+    uint4 it = {0, 0, 0, 0};
+    __device__ __forceinline__ uint32_t total() const
+    {
+        return (uint32_t)(__popcll(m[0]) + __popcll(m[1]) + __popcll(m[2]) + __popcll(m[3]));
+    }
+};
+
+struct TileCursor {
+    const uint32_t* items;
+    const uint16_t* spans;
+    uint32_t begin, end;   // the bin's list
+    uint32_t cur;          // next round's first entry (a multiple of 4: whole groups are loaded)
+    uint32_t tail;         // entries picked so far
+    uint32_t key;          // the tile's place in the bin, guard bits set, twice
+
+    __device__ __forceinline__ bool more() const { return cur < end; }
+
+    // The lane's group of the round at c.  The last group may reach past the
+    // list: the buffers hold whole groups; a lane past the last group loads
+    // it again.
+    __device__ __forceinline__ uint32_t group(uint32_t c) const
+    {
+        return min(c + 4u * threadIdx.x, (end - 1u) & ~3u);
+    }
+    __device__ __forceinline__ uint2 load_spans(uint32_t c) const
+    {
+        return *reinterpret_cast<const uint2*>(spans + group(c));
+    }
+    __device__ __forceinline__ uint4 load_items(uint32_t c) const
+    {
+        return *reinterpret_cast<const uint4*>(items + group(c));
+    }
+
+    __device__ __forceinline__ void start(const BinLists& lists, const ViewParams& vp, int tx, int ty)
+    {
+        const uint32_t* off = lists.off + lists.stride * (int64_t)bin_of_tile(vp, tx, ty);
+        uint64_t b = off[0], e = off[lists.stride];
+        if (e > lists.capacity) e = lists.capacity;
+        if (b > e) b = e;
+        items = lists.items;
+        spans = lists.spans;
+        // uniform values, kept scalar
+        begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+        end = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)e);
+        cur = begin < end ? begin & ~3u : end;
+        tail = 0;
+        const uint32_t edge = (1u << vp.bin_shift) - 1u, x = (uint32_t)tx & edge, y = (uint32_t)ty & edge;
+        const uint32_t k = 0x8888u | x | (y << 4) | ((edge - x) << 8) | ((edge - y) << 12);
+        key = k | (k << 16);
+    }
+
+    // The tile's entries among four, sp, of the round at c.
+    __device__ __forceinline__ void pick4(uint2 sp, uint32_t c, Pick4& k) const
+    {
+        if (c < begin || c + kRound > end) {
+            // entries outside the list: a span that covers no tile (8 in
+            // every field, which borrows from none)
+            const uint32_t i = c + 4u * threadIdx.x - begin, len = end - begin;
+            sp.x = (i < len ? sp.x & 0xFFFFu : 0x8888u) | (i + 1u < len ? sp.x & 0xFFFF0000u : 0x88880000u);
+            sp.y = (i + 2u < len ? sp.y & 0xFFFFu : 0x8888u) | (i + 3u < len ? sp.y & 0xFFFF0000u : 0x88880000u);
+        }
+        const uint32_t a = (key - sp.x) & 0x88888888u, b = (key - sp.y) & 0x88888888u;
+        k.m[0] = __ballot((uint16_t)a == (uint16_t)0x8888u);
+        k.m[1] = __ballot(a >= 0x88880000u);
+        k.m[2] = __ballot((uint16_t)b == (uint16_t)0x8888u);
+        k.m[3] = __ballot(b >= 0x88880000u);
+    }
+
+    // The lane's picks to the ring, from position pos of the wave's first.
+    static __device__ __forceinline__ void write4(uint32_t* ring, const Pick4& k, uint32_t pos)
+    {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(k.m[j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)k.m[j], pos));
+        const uint32_t item[4] = {k.it.x, k.it.y, k.it.z, k.it.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (__builtin_amdgcn_inverse_ballot_w64(k.m[j])) {
+                ring[pos & (kRing - 1)] = item[j];
+                ++pos;
+            }
+    }
+
+    // First half of a round: the picks and the wave's count.  (The picks are
+    // the caller's, not the cursor's: as members they would hold registers
+    // from one round to the next.)
+    __device__ __forceinline__ void test(TilePick& pick, Pick4& p, int wave, int lane)
+    {
+        const uint2 sp = load_spans(cur);
+        p.it = load_items(cur);
+        pick4(sp, cur, p);
+        const uint32_t n = p.total();
+        if (lane == 0) pick.count[wave] = n;
+        cur += kRound;
+    }
+
+    // Second half, a barrier later: the picked items to the ring.
+    __device__ __forceinline__ void put(TilePick& pick, const Pick4& p, int wave)
+    {
+        uint32_t pos = tail, n = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t c = (uint32_t)__builtin_amdgcn_readfirstlane((int)pick.count[w]);
+            pos += w < wave ? c : 0u;
+            n += c;
+        }
+        write4(pick.ring, p, pos);
+        tail += n;
+    }
+
+    // The first two rounds at once, into the empty ring, all loads together.
+    __device__ __forceinline__ void begin_pick(TilePick& pick, int wave, int lane)
+    {
+        static_assert(kRing >= 2 * kRound, "two rounds fit");
+        if (!more()) return;
+        const uint32_t c = cur;
+        const bool two = c + kRound < end;
+        const uint2 sp = load_spans(c), sp2 = load_spans(c + kRound);   // past the list: its last group
+        Pick4 p, p2;
+        p.it = load_items(c);
+        p2.it = load_items(c + kRound);
+        pick4(sp, c, p);
+        uint32_t n = p.total();
+        pick4(sp2, c + kRound, p2);   // nothing past the list
+        n |= p2.total() << 16;
+        cur = two ? c + 2 * kRound : c + kRound;
+        if (lane == 0) pick.count[wave] = n;
+        __syncthreads();
+        uint32_t before = 0, all = 0;   // both rounds' counts, 16 bits each (at most 1024)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t k = (uint32_t)__builtin_amdgcn_readfirstlane((int)pick.count[w]);
+            before += w < wave ? k : 0u;
+            all += k;
+        }
+        write4(pick.ring, p, before & 0xFFFFu);
+        write4(pick.ring, p2, (all & 0xFFFFu) + (before >> 16));
+        tail = (all & 0xFFFFu) + (all >> 16);
+        __syncthreads();
+    }
+
+    // Whole rounds until target entries are picked or the list ends; every
+    // thread of the workgroup takes part, and the ring is ready on return.
+    __device__ __forceinline__ void fill(TilePick& pick, uint32_t target, int wave, int lane)
+    {
+        while (tail < target && more()) {
+            Pick4 p;
+            test(pick, p, wave, lane);
+            __syncthreads();
+            put(pick, p, wave);
+            __syncthreads();
+        }
+    }
+};
+
 // Workgroup -> tile: tiles are cut into groups of `group` consecutive tiles
 // (row-major), dealt to the 8 XCDs in turn (block b runs on XCD b % 8), so
 // neighbouring tiles, which share list entries, share an XCD's L2.

@@ -19,8 +19,8 @@ constexpr int kTileWorkFields = 6;        // u64 fields of a per-tile blend trac
 // same image, lists and counts): chosen per workload by the autotuner.
 struct Tuning {
     int sort_items;    // keys per thread of a depth-sort block: 4, 8, 16
-    int bin1_items;    // depth-sorted Gaussians per lane of a level-1 binning wave: 4, 8, 16
-    int bin2_items;    // row entries per lane of a level-2 binning wave: 8, 16, 32
+    int bin1_items;    // depth-sorted Gaussians per lane of a binning wave: 4, 8, 16
+    int bin2_items;    // row entries per lane of a wave that writes the per-tile lists: 8, 16, 32
     int blend_group;   // consecutive tiles dealt to one XCD by the blend: 1 .. 64;
                        // 0: tiles dispatched heaviest first, by the previous frame's work;
                        // -1: the same order as a work queue that a persistent grid drains
@@ -48,6 +48,8 @@ struct ViewParams {
     int width, height, tiles_x, tiles_y;
     uint32_t tile_base;             // global index of the view's first tile
     uint32_t row_base;              // global index of the view's first tile row
+    uint32_t bin_base;              // global index of the view's first bin
+    int bins_x, bins_y, bin_shift;  // bins of 2^bin_shift x 2^bin_shift tiles
     float* out_rgb;                 // [3][H][W]
     float* out_T;                   // [H][W] or null
     uint32_t* out_nc;               // [H][W] or null
@@ -59,8 +61,11 @@ struct ViewParams {
 // Per-view counters written on the device: [0] Gaussians on screen (at least
 // one tile), [1] Gaussians with a finite depth key (they sort first in a
 // view's depth order; those culled or off screen have an empty rectangle),
-// [2..3] pairs K of the view (u64).
-constexpr int kViewCounters = 4;
+// then as u64 pairs of words [2..3] pairs K of the view, [4..5] its row
+// entries R, [6..7] its bin entries; [8] items whose depth key or rectangle
+// changed since the last render (when compared; saturating).
+constexpr int kViewCounters = 10;
+constexpr int kViewChanged = 8;
 
 // Finds the view owning global tile t (views hold ascending tile bases).
 __device__ __forceinline__ int view_of_tile(const ViewParams* views, int n_views, uint32_t t)
@@ -72,6 +77,12 @@ __device__ __forceinline__ int view_of_tile(const ViewParams* views, int n_views
         else hi = mid;
     }
     return lo;
+}
+
+// Global index of the bin that holds tile (tx, ty) of the view.
+__device__ __forceinline__ uint32_t bin_of_tile(const ViewParams& vp, int tx, int ty)
+{
+    return vp.bin_base + (uint32_t)((ty >> vp.bin_shift) * vp.bins_x + (tx >> vp.bin_shift));
 }
 
 struct ProjectArgs {
@@ -92,7 +103,11 @@ struct ProjectArgs {
     uint32_t* tiles_touched;
     ushort4* rect;
     uint32_t* view_counts;        // [n_views][kViewCounters]
-    uint32_t* partials;           // [blocks][n_views][4] per-block counts: on screen, pairs, keyed
+    // when not null, a second copy of view_counts: pinned host memory or a
+    // buffer of the caller's, complete when the launch's kernels are
+    uint32_t* counts_out;
+    uint32_t* partials;           // [blocks][n_views][kPartials] per-block counts: on screen, pairs, keyed,
+                                  // changed, row entries, bin entries
     // when order is not null, one extra workgroup of the launch writes the
     // blend's dispatch order of order_tiles tiles, heaviest first by
     // order_cost (the previous frame's walked entries)
@@ -107,6 +122,7 @@ struct ProjectArgs {
     uint32_t* changed;
 };
 
+constexpr int kPartials = 8;
 size_t project_partials_elems(int64_t n, int n_views);
 hipError_t launch_project(const ProjectArgs& a, hipStream_t s);
 
@@ -153,19 +169,71 @@ hipError_t launch_order_reuse(const uint32_t* keys, uint32_t* keys_a, uint32_t* 
 hipError_t launch_order_pack(const uint32_t* vals_b, const ushort4* rect, int64_t n, const uint32_t* words,
                              uint32_t* pay_b, hipStream_t s);
 
+// The depth-ordered lists over bins of tiles that the blend walks (bins.hip).
 struct BinArgs {
     const uint32_t* sorted_idx;   // [n_views * n] items (v * n + i), each view's segment in (depth, index) order
     const uint32_t* view_counts;  // device [n_views][kViewCounters]; keyed items sort first in a segment
     const ushort4* rect;          // [n_views * n] tile rectangle of each item in its view
     // the rectangles in depth order: packed (pack_rect), carried by the
-    // depth sort, when sorted_pack is not null; else gathered from rect by
-    // the row count into sorted_rect
+    // depth sort, when sorted_pack is not null; else gathered from rect into
+    // sorted_rect before the count
     const uint32_t* sorted_pack;  // [n_views * n] or null
-    ushort4* sorted_rect;         // [n_views * n] (keyed items; written by the row count)
+    ushort4* sorted_rect;         // [n_views * n]
+    int64_t n;                    // Gaussians per view
+    int n_views;
+    const ViewParams* views;      // device table
+    int64_t bins;                 // bins over all views
+    int max_bins;                 // bins of the largest grid
+    int max_diff;                 // largest (bins_x + 1) (bins_y + 1)
+    int items1, chunk, chunks1;   // chunk shape (bins_chunk_shape): items per lane and round, Gaussians, chunks per view
+    int lds_mask;                 // set by the launch
+    // [1 + bins * chunks1 + 1]: a zero, then counts[bin][chunk], scanned to
+    // the chunks' cursors in place, then the total
+    uint32_t* table;
+    uint32_t* items;              // [capacity, in whole groups of 4] entry: item
+    uint16_t* spans;              // likewise: its part of the bin: tiles clear of the bin's left, top, right and bottom edge, 4 bits each
+    uint64_t capacity;
+    uint32_t* overflow;           // set to 1 when the entries do not fit 32 bits
+    // when not null, every kernel (and scan) reads *skip on the device and
+    // does nothing when it is set: the lists of the last render stay,
+    // because they are this render's
+    const uint32_t* skip;
+};
+
+int bin_shift_of(int tiles_x, int tiles_y, float footprint);
+void bins_chunk_shape(int64_t n, int n_views, int64_t bins, int max_bins, int tuned, int* items1, int* chunk,
+                      int* chunks1);
+bool bins_in_lds(int max_bins);
+hipError_t launch_bins_count(const BinArgs& a, uint64_t* scan_scratch, hipStream_t s);
+hipError_t launch_bins_scatter(const BinArgs& a, hipStream_t s);
+
+// Bin b's list is entries [off[b * stride], off[(b + 1) * stride]).
+struct BinLists {
+    const uint32_t* items;
+    const uint16_t* spans;
+    const uint32_t* off;
+    int64_t stride;
+    uint64_t capacity;
+};
+inline BinLists bin_lists(const BinArgs& a)
+{
+    // where the cursors live in the table (large grids) the scatter moved
+    // every chunk's cursor to its end, the start of the next
+    return {a.items, a.spans, a.table + (bins_in_lds(a.max_bins) ? 1 : 0), a.chunks1, a.capacity};
+}
+
+// The per-tile lists (tile_bin.hip), written on request.
+struct ListArgs {
+    const uint32_t* sorted_idx;   // as in BinArgs
+    const uint32_t* view_counts;
+    const uint32_t* sorted_pack;  // the rectangles in depth order: packed, or
+    const ushort4* sorted_rect;   // (sorted_pack null) whole
     int64_t n;                    // Gaussians per view
     int n_views;
     const ViewParams* views;      // device table
     const uint32_t* row_tiles_x;  // [rows] tiles_x of each global tile row
+    const uint32_t* row_tile0;    // [rows] its first tile (global index)
+    const uint32_t* depth_key;    // [n_views * n]
     int rows;                     // global tile rows (sum of the views' tiles_y)
     int max_tiles_x, max_tiles_y; // largest tiles_x and tiles_y of the views
     int64_t tiles;                // global tiles (sum of the views' tiles)
@@ -179,26 +247,20 @@ struct BinArgs {
     uint32_t* counts2;            // per row: [tiles_x][row's chunks] counts -> scan = cursors
     uint64_t counts2_capacity;    // elements of counts2
     uint32_t* tile_offsets;       // [tiles + 1]; [tiles] = K
-    uint32_t* values;             // [capacity] sorted pair values (items)
+    uint32_t* values;             // [capacity] sorted pair values (items), or null
+    uint64_t* keys;               // [capacity] tile << 32 | depth bits of each, or null
     uint64_t capacity;
     int max_chunks2;
     uint32_t* overflow;           // set to 1 when a capacity is exceeded
-    // when not null, every binning kernel (and scan) reads *skip on the
-    // device and does nothing when it is set: the lists, offsets and sizes of
-    // the last render stay, because they are this render's
-    const uint32_t* skip;
 };
 
 size_t bin_info_elems(int rows);
 bool bin_items_supported(int items1, int items2);
 int bin_level1_chunks(int64_t n, int items1);
 int bin_level2_chunk_bound(uint64_t row_entries, int rows, int items2);
-hipError_t launch_bin_rows(const BinArgs& a, uint64_t* scan_scratch, hipStream_t s);
-hipError_t launch_bin_row_scatter(const BinArgs& a, hipStream_t s);
-hipError_t launch_bin_tiles(const BinArgs& a, int grid2, uint64_t* scan_scratch, hipStream_t s);
-hipError_t launch_bin_tile_scatter(const BinArgs& a, int grid2, hipStream_t s);
-// info[] words the host reads after launch_bin_rows: level-2 chunks, level-2
-// count elements
+hipError_t launch_list_rows(const ListArgs& a, uint64_t* scan_scratch, hipStream_t s);
+hipError_t launch_list_tiles(const ListArgs& a, uint64_t* scan_scratch, hipStream_t s);
+// info[] words: level-2 chunks, level-2 count elements
 constexpr int kInfoC2 = 0;
 constexpr int kInfoC2Elems = 1;
 
@@ -214,8 +276,7 @@ hipError_t launch_scan_exclusive(uint32_t* data, int64_t n, uint64_t* block_scra
 
 struct BlendArgs {
     const Splat* splats;
-    const uint32_t* values;
-    const uint32_t* tile_offsets;
+    BinLists lists;
     const ViewParams* views;   // device table: sizes, tile bases, outputs
     int n_views;
     int64_t tiles;             // global tiles
@@ -233,13 +294,13 @@ struct BlendArgs {
     unsigned long long* tile_work;
 };
 
-hipError_t launch_blend(const BlendArgs& a, uint64_t capacity, hipStream_t s);
+hipError_t launch_blend(const BlendArgs& a, hipStream_t s);
 
 // Dispatch order of the blend: all tiles, heaviest first by cost[t] (the
-// previous frame's walked entries), or by list length when cost is null;
-// tiles of (nearly) equal cost in any order.  One workgroup.
-hipError_t launch_blend_order(const uint32_t* cost, const uint32_t* tile_offsets, int64_t tiles, uint32_t* order,
-                              hipStream_t s);
+// previous frame's walked entries), or by the length of the tile's bin's list
+// when cost is null; tiles of (nearly) equal cost in any order.  One workgroup.
+hipError_t launch_blend_order(const uint32_t* cost, const BinLists& lists, const ViewParams* views, int n_views,
+                              int64_t tiles, uint32_t* order, hipStream_t s);
 
 // Backward of the blend: per list entry, dL/d(u, v, A, B, C, opacity, r, g, b)
 // summed over the pixels of every tile into grad2d[item][kGrad2d] (zeroed by
@@ -248,8 +309,7 @@ hipError_t launch_blend_order(const uint32_t* cost, const uint32_t* tile_offsets
 constexpr int kGrad2d = 9;
 struct BlendBackArgs {
     const Splat* splats;
-    const uint32_t* values;
-    const uint32_t* tile_offsets;
+    BinLists lists;
     const ViewParams* views;
     int n_views;
     int64_t tiles;
@@ -258,7 +318,7 @@ struct BlendBackArgs {
     float bg[3];
     float* grad2d;
 };
-hipError_t launch_blend_backward(const BlendBackArgs& a, uint64_t capacity, hipStream_t s);
+hipError_t launch_blend_backward(const BlendBackArgs& a, hipStream_t s);
 
 // Backward of the projection: from grad2d of every (view, Gaussian) item to
 // the gradients of the Gaussian parameters (float32, the input layouts),
@@ -285,7 +345,4 @@ struct ProjectBackArgs {
 hipError_t launch_project_backward(const ProjectBackArgs& a, hipStream_t s);
 
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
-hipError_t launch_write_keys(const uint32_t* values, const uint32_t* tile_offsets,
-                             const uint32_t* depth_key, int64_t tiles, uint64_t* keys, hipStream_t s);
-
 }  // namespace gsmi

@@ -71,7 +71,7 @@ struct Geometry {
 
 size_t project_partials_elems(int64_t n, int n_views)
 {
-    return (size_t)(4 * ((n + 255) / 256 + 1) * (size_t)(n_views > 0 ? n_views : 1));
+    return (size_t)(kPartials * ((n + 255) / 256 + 1) * (size_t)(n_views > 0 ? n_views : 1));
 }
 
 namespace {
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a)
     if (a.order) {
         if (blockIdx.x == 0) {
             __shared__ uint32_t s_hist[kOrderBuckets], s_wsum[4];
-            order_heaviest_first<256>(a.order_cost, nullptr, a.order_tiles, a.order, s_hist, s_wsum, nullptr, 0);
+            order_heaviest_first<256>(WalkedCost{a.order_cost}, a.order_tiles, a.order, s_hist, s_wsum, nullptr, 0);
             return;
         }
         blk -= 1;
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a)
     // sigmoid in double, rounded once: the opacity carries one float rounding
     // whatever the logit (a float exp of -logit would carry about |logit| of them)
     const float opacity = (float)(1.0 / (1.0 + exp(-(double)logit)));
-    __shared__ uint32_t s_vis[4], s_pairs[4], s_front[4], s_changed[4];
+    __shared__ uint32_t s_sum[4][6];   // per wave: on screen, pairs, keyed, changed, row entries, bin entries
 
     const int n_views = kOneView ? 1 : a.n_views;
     for (int v = 0; v < n_views; ++v) {
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a)
         const double tz_key = ((vp.R[6] * (double)mxf + vp.R[7] * (double)myf) + vp.R[8] * (double)mzf) + vp.t[2];
         const bool keyed = isfinite(tz_key);
 
-        uint32_t tiles = 0;
+        uint32_t tiles = 0, tile_rows = 0, bins = 0;
         ushort4 rc = make_ushort4(0, 0, 0, 0);
         if (ok && valid) {
             const double big = 1073741824.0;
@@ -261,6 +261,9 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a)
                 const int y0 = (int)(ylo / kTile), y1 = (int)(yhi / kTile) + 1;
                 rc = make_ushort4((unsigned short)x0, (unsigned short)y0, (unsigned short)x1, (unsigned short)y1);
                 tiles = (uint32_t)((x1 - x0) * (y1 - y0));
+                tile_rows = (uint32_t)(y1 - y0);
+                bins = (uint32_t)((((x1 - 1) >> vp.bin_shift) - (x0 >> vp.bin_shift) + 1) *
+                                  (((y1 - 1) >> vp.bin_shift) - (y0 >> vp.bin_shift) + 1));
             }
         }
 
@@ -302,8 +305,10 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a)
                 changed = key0 != key || rc0.x != rc.x || rc0.y != rc.y || rc0.z != rc.z || rc0.w != rc.w;
             }
             a.depth_key[o] = key;
-            a.radius[o] = tiles > 0 ? g.radius : 0;
-            a.tiles_touched[o] = tiles;
+            if (a.radius) {
+                a.radius[o] = tiles > 0 ? g.radius : 0;
+                a.tiles_touched[o] = tiles;
+            }
             a.rect[o] = rc;
         }
 
@@ -313,23 +318,25 @@ __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a)
         const uint64_t vis = __ballot(tiles > 0);
         const uint64_t front = __ballot(valid && keyed);
         const uint64_t moved = __ballot(changed);
-        uint32_t wave_pairs = tiles;
-        for (int o = 32; o > 0; o >>= 1) wave_pairs += __shfl_xor(wave_pairs, o, 64);
+        for (int o = 32; o > 0; o >>= 1) {
+            tiles += __shfl_xor(tiles, o, 64);
+            tile_rows += __shfl_xor(tile_rows, o, 64);
+            bins += __shfl_xor(bins, o, 64);
+        }
         if ((threadIdx.x & 63) == 0) {
-            s_vis[threadIdx.x >> 6] = (uint32_t)__popcll(vis);
-            s_pairs[threadIdx.x >> 6] = wave_pairs;
-            s_front[threadIdx.x >> 6] = (uint32_t)__popcll(front);
-            s_changed[threadIdx.x >> 6] = (uint32_t)__popcll(moved);
+            uint32_t* w = s_sum[threadIdx.x >> 6];
+            w[0] = (uint32_t)__popcll(vis);
+            w[1] = tiles;
+            w[2] = (uint32_t)__popcll(front);
+            w[3] = (uint32_t)__popcll(moved);
+            w[4] = tile_rows;
+            w[5] = bins;
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t* pp = a.partials + 4 * (blk * a.n_views + v);
-            pp[0] = s_vis[0] + s_vis[1] + s_vis[2] + s_vis[3];
-            pp[1] = s_pairs[0] + s_pairs[1] + s_pairs[2] + s_pairs[3];
-            pp[2] = s_front[0] + s_front[1] + s_front[2] + s_front[3];
-            pp[3] = s_changed[0] + s_changed[1] + s_changed[2] + s_changed[3];
-        }
-        __syncthreads();   // s_vis / s_pairs are reused by the next view
+        if (threadIdx.x < 6)
+            a.partials[kPartials * (blk * a.n_views + v) + threadIdx.x] =
+                s_sum[0][threadIdx.x] + s_sum[1][threadIdx.x] + s_sum[2][threadIdx.x] + s_sum[3][threadIdx.x];
+        __syncthreads();   // s_sum is reused by the next view
     }
 }
 
@@ -590,57 +597,54 @@ void launch_project_backward_dt(const ProjectBackArgs& a, unsigned blocks, hipSt
 
 }  // namespace
 
-// Per view (one block each): Gaussians on screen, pairs and Gaussians with a
-// depth key (past the culls), summed over the projection blocks' partials.
-// With changed, also the items whose key or rectangle changed (added over
+// Per view (one block each): the view counters, summed over the projection
+// blocks' partials.  With changed, also the items whose key or rectangle changed (added over
 // the views; each view's share clamped to 2^32 - 1), clearing the flag that
 // none did when any did.
 __global__ __launch_bounds__(1024) void reduce_partials_kernel(const uint32_t* __restrict__ partials, int blocks,
-                                                               int n_views, uint32_t* view_counts, uint32_t* changed)
+                                                               int n_views, uint32_t* view_counts,
+                                                               uint32_t* counts_out, uint32_t* changed)
 {
     // 64-bit sums: in each thread over a stride of blocks, in each wave by
     // shuffles, then over the 16 waves in LDS
-    __shared__ unsigned long long sv[16], sp[16], sf[16], sc[16];
+    __shared__ unsigned long long s_sum[16][6];
     const int v = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned long long vis = 0, pairs = 0, front = 0, moved = 0;
+    unsigned long long t[6] = {0, 0, 0, 0, 0, 0};
 #pragma unroll 4
     for (int b = threadIdx.x; b < blocks; b += 1024) {
-        const uint4 pp = *reinterpret_cast<const uint4*>(partials + 4 * ((int64_t)b * n_views + v));
-        vis += pp.x;
-        pairs += pp.y;
-        front += pp.z;
-        moved += changed ? pp.w : 0u;
+        const uint4* pp = reinterpret_cast<const uint4*>(partials + kPartials * ((int64_t)b * n_views + v));
+        const uint4 lo = pp[0];
+        const uint2 hi = *reinterpret_cast<const uint2*>(pp + 1);
+        t[0] += lo.x;
+        t[1] += lo.y;
+        t[2] += lo.z;
+        t[3] += lo.w;
+        t[4] += hi.x;
+        t[5] += hi.y;
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        vis += __shfl_xor(vis, o, 64);
-        pairs += __shfl_xor(pairs, o, 64);
-        front += __shfl_xor(front, o, 64);
-        moved += __shfl_xor(moved, o, 64);
-    }
-    if (lane == 0) {
-        sv[wave] = vis;
-        sp[wave] = pairs;
-        sf[wave] = front;
-        sc[wave] = moved;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        for (int o = 32; o > 0; o >>= 1) t[k] += __shfl_xor(t[k], o, 64);
+        if (lane == 0) s_sum[wave][k] = t[k];
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long tv = 0, tp = 0, tf = 0, tc = 0;
-        for (int w = 0; w < 16; ++w) {
-            tv += sv[w];
-            tp += sp[w];
-            tf += sf[w];
-            tc += sc[w];
+        for (int k = 0; k < 6; ++k) t[k] = 0;
+        for (int w = 0; w < 16; ++w)
+            for (int k = 0; k < 6; ++k) t[k] += s_sum[w][k];
+        const uint32_t moved = !changed ? 0u : (t[3] > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)t[3]);
+        const uint32_t c[kViewCounters] = {(uint32_t)t[0], (uint32_t)t[2], (uint32_t)t[1], (uint32_t)(t[1] >> 32),
+                                           (uint32_t)t[4], (uint32_t)(t[4] >> 32), (uint32_t)t[5],
+                                           (uint32_t)(t[5] >> 32), moved, 0u};
+        for (int k = 0; k < kViewCounters; ++k) {
+            view_counts[(int64_t)kViewCounters * v + k] = c[k];
+            if (counts_out) counts_out[(int64_t)kViewCounters * v + k] = c[k];
         }
-        uint32_t* c = view_counts + (int64_t)kViewCounters * v;
-        c[0] = (uint32_t)tv;
-        c[1] = (uint32_t)tf;
-        c[2] = (uint32_t)tp;
-        c[3] = (uint32_t)(tp >> 32);
-        if (changed && tc > 0) {
+        if (counts_out) __threadfence_system();   // may be pinned host memory, read after an event
+        if (moved) {
             // views add their counts; any change clears the flag (all
             // writers store the same 0)
-            atomicAdd(&changed[0], tc > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)tc);
+            atomicAdd(&changed[0], moved);
             changed[1] = 0u;
         }
     }
@@ -688,8 +692,7 @@ hipError_t launch_project(const ProjectArgs& a, hipStream_t s)
     default: launch_project_views<2>(a, grid, s); break;
     }
     hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)a.n_views), dim3(1024), 0, s,
-                       (const uint32_t*)a.partials, (int)blocks, a.n_views, a.view_counts,
-                       a.changed);
+                       (const uint32_t*)a.partials, (int)blocks, a.n_views, a.view_counts, a.counts_out, a.changed);
     return hipGetLastError();
 }
 

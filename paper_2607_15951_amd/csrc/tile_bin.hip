@@ -1,5 +1,7 @@
-// tile_bin.hip -- duplication of Gaussians into (tile, depth) pairs fused with
-// the stable tile-digit pass of the key sort.
+// tile_bin.hip -- the per-tile lists of a render, written when a caller asks
+// for them: duplication of Gaussians into (tile, depth) pairs fused with the
+// stable tile-digit pass of the key sort.  (The blend walks lists over bins of
+// tiles instead, bins.hip.)
 //
 // Every Gaussian overlapping a screen tile (the 3-sigma square of Sec. 4.4)
 // yields one pair; a pair's key is (tile << 32 | depth bits), its value the
@@ -44,8 +46,8 @@ constexpr int kBand = 8;                 // tile columns per band of the level-2
 // count[x * chunks(r) + j].
 constexpr int kInfoRowChunks = 2;
 
-__device__ __forceinline__ const uint32_t* row_chunk_prefix(const BinArgs& a) { return a.info + kInfoRowChunks; }
-__device__ __forceinline__ const uint32_t* row_elem_prefix(const BinArgs& a)
+__device__ __forceinline__ const uint32_t* row_chunk_prefix(const ListArgs& a) { return a.info + kInfoRowChunks; }
+__device__ __forceinline__ const uint32_t* row_elem_prefix(const ListArgs& a)
 {
     return a.info + kInfoRowChunks + a.rows + 1;
 }
@@ -98,7 +100,7 @@ struct Items1 {
 };
 
 // Keyed-item range [start, end) of level-1 chunk c; false when empty.
-__device__ __forceinline__ bool chunk1_range(const BinArgs& a, int c, int* view, int* part, int64_t* start,
+__device__ __forceinline__ bool chunk1_range(const ListArgs& a, int c, int* view, int* part, int64_t* start,
                                              int64_t* end)
 {
     *view = c / a.chunks1;
@@ -114,7 +116,7 @@ __device__ __forceinline__ bool chunk1_range(const BinArgs& a, int c, int* view,
 }
 
 template <int kItems>
-__device__ __forceinline__ bool load_items1(const BinArgs& a, int c, int lane, Items1<kItems>& it)
+__device__ __forceinline__ bool load_items1(const ListArgs& a, int c, int lane, Items1<kItems>& it)
 {
     int64_t start, end;
     if (!chunk1_range(a, c, &it.view, &it.part, &start, &end)) return false;
@@ -184,9 +186,8 @@ __device__ __forceinline__ void counts_from_diff(const uint32_t* diff, int m, ui
 // Counting needs no order: each span adds +1 at its first bucket and -1 past
 // its last in an LDS difference array (two atomics per item), summed at the end.
 template <int kItems>
-__global__ __launch_bounds__(64) void level1_count_kernel(BinArgs a)
+__global__ __launch_bounds__(64) void level1_count_kernel(ListArgs a)
 {
-    if (a.skip && *a.skip) return;   // the last render's lists hold
     extern __shared__ uint32_t diff[];   // [max_tiles_y + 1][kDiffCopies], sized at launch
     const int lane = threadIdx.x, c = chunk_of_block();
     const int view = c / a.chunks1, part = c % a.chunks1;
@@ -215,28 +216,18 @@ __global__ __launch_bounds__(64) void level1_count_kernel(BinArgs a)
             }
         }
     } else {
-        // the rectangles gathered in depth order, for the scatter to stream:
-        // all index loads, then all gathers, then the counting (see
-        // load_items2)
-        uint32_t idx[kItems];
-#pragma unroll
-        for (int b = 0; b < kItems; ++b) {
-            const int64_t k = start + b * 64 + lane;
-            idx[b] = k < end ? a.sorted_idx[k] : 0u;
-        }
+        // grids too large to pack: written in depth order by the binning
         ushort4 rr[kItems];
 #pragma unroll
-        for (int b = 0; b < kItems; ++b) rr[b] = a.rect[idx[b]];
-#pragma unroll
         for (int b = 0; b < kItems; ++b) {
             const int64_t k = start + b * 64 + lane;
-            if (k < end) {
-                const ushort4 r = rr[b];
-                a.sorted_rect[k] = r;
-                if (r.w > r.y) {
-                    atomicAdd(diff_slot(diff, r.y, lane), 1u);
-                    atomicSub(diff_slot(diff, r.w, lane), 1u);
-                }
+            rr[b] = k < end ? a.sorted_rect[k] : make_ushort4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int b = 0; b < kItems; ++b) {
+            if (rr[b].w > rr[b].y) {
+                atomicAdd(diff_slot(diff, rr[b].y, lane), 1u);
+                atomicSub(diff_slot(diff, rr[b].w, lane), 1u);
             }
         }
     }
@@ -287,9 +278,8 @@ __device__ __forceinline__ void walk_row_band(const uint2* s_p, const uint8_t* s
 }
 
 template <int kItems>
-__global__ __launch_bounds__(64) void level1_scatter_kernel(BinArgs a)
+__global__ __launch_bounds__(64) void level1_scatter_kernel(ListArgs a)
 {
-    if (a.skip && *a.skip) return;   // the last render's lists hold
     __shared__ uint2 s_p[kItems * 64];
     __shared__ uint8_t s_r[kItems * 64];
     const int lane = threadIdx.x, c = chunk_of_block();
@@ -340,9 +330,8 @@ __global__ __launch_bounds__(64) void level1_scatter_kernel(BinArgs a)
 // overflow every row gets zero chunks.
 static_assert(kMaxTotalRows % 1024 == 0, "rows per thread of the chunk table");
 
-__global__ __launch_bounds__(1024) void level2_table_kernel(BinArgs a)
+__global__ __launch_bounds__(1024) void level2_table_kernel(ListArgs a)
 {
-    if (a.skip && *a.skip) return;   // the last render's lists hold
     __shared__ uint32_t wave_c[16], wave_e[16];
     __shared__ uint32_t s_total_c, s_total_e;
     const int tid = threadIdx.x, rows = a.rows, lane = tid & 63, wave = tid >> 6;
@@ -432,7 +421,7 @@ struct Items2 {
 
 // Start of chunk c's cursors in the scanned level-2 counts: row r's block
 // starts at eprefix[r], column x at x * chunks(r), chunk c at c - prefix[r].
-__device__ __forceinline__ const uint32_t* level2_slot(const BinArgs& a, int row, int c, int64_t* stride)
+__device__ __forceinline__ const uint32_t* level2_slot(const ListArgs& a, int row, int c, int64_t* stride)
 {
     const uint32_t* base = row_chunk_prefix(a);
     *stride = (int64_t)(base[row + 1] - base[row]);
@@ -440,7 +429,7 @@ __device__ __forceinline__ const uint32_t* level2_slot(const BinArgs& a, int row
 }
 
 // Row and entry range [eb, ee) of level-2 chunk c.
-__device__ __forceinline__ void chunk2_range(const BinArgs& a, int c, int lane, int* row, int64_t* eb, int64_t* ee)
+__device__ __forceinline__ void chunk2_range(const ListArgs& a, int c, int lane, int* row, int64_t* eb, int64_t* ee)
 {
     const int rows = a.rows;
     const uint32_t* base = row_chunk_prefix(a);
@@ -465,7 +454,7 @@ __device__ __forceinline__ void chunk2_range(const BinArgs& a, int c, int lane, 
 }
 
 template <int kItems>
-__device__ __forceinline__ bool load_items2(const BinArgs& a, int c, int lane, Items2<kItems>& it)
+__device__ __forceinline__ bool load_items2(const ListArgs& a, int c, int lane, Items2<kItems>& it)
 {
     if ((uint32_t)c >= a.info[kInfoC2]) return false;
     int64_t eb, ee;
@@ -500,7 +489,7 @@ __device__ __forceinline__ bool load_items2(const BinArgs& a, int c, int lane, I
 
 // One level-2 chunk's per-column counts.
 template <int kItems>
-__device__ __forceinline__ void level2_count_chunk(const BinArgs& a, int c, int lane, uint32_t* diff)
+__device__ __forceinline__ void level2_count_chunk(const ListArgs& a, int c, int lane, uint32_t* diff)
 {
     int row;
     int64_t eb, ee;
@@ -541,32 +530,34 @@ __device__ __forceinline__ void level2_count_chunk(const BinArgs& a, int c, int 
          j_ < per_ && c < (c2); j_ += (int)(gridDim.x >> 3), c += (int)(gridDim.x >> 3))
 
 template <int kItems>
-__global__ __launch_bounds__(64) void level2_count_kernel(BinArgs a)
+__global__ __launch_bounds__(64) void level2_count_kernel(ListArgs a)
 {
-    if (a.skip && *a.skip) return;   // the last render's lists hold
     extern __shared__ uint32_t diff[];   // [max_tiles_x + 1][kDiffCopies], sized at launch: more waves fit
     const int lane = threadIdx.x;
     const int c2 = (int)a.info[kInfoC2];
     FOR_LEVEL2_CHUNK(c, c2) level2_count_chunk<kItems>(a, c, lane, diff);
 }
 
-// The walk of one band over the n packed entries in LDS (s_g, s_x): batch
-// by batch, each batch against the band's kBand columns, unrolled so that
-// every column's cursor stays in a scalar register.  cur_b holds the cursors
-// (lane q: column bx0 + q).
-template <bool kChecked>
-__device__ __forceinline__ void walk_band(const uint32_t* s_g, const uint16_t* s_x, uint32_t n, uint32_t bx0,
-                                          uint32_t cur_b, uint32_t* __restrict__ out, uint64_t capacity, int lane)
+// The walk of one band over the n packed entries in LDS (s_g, s_x, and their
+// depth keys s_d when keys are wanted): batch by batch, each batch against
+// the band's kBand columns, unrolled so that every column's cursor stays in a
+// scalar register.  cur_b holds the cursors (lane q: column bx0 + q, tile
+// tile0 + q).
+template <bool kChecked, bool kKeys>
+__device__ __forceinline__ void walk_band(const uint32_t* s_g, const uint32_t* s_d, const uint16_t* s_x, uint32_t n,
+                                          uint32_t tile0, uint32_t cur_b, uint32_t* __restrict__ out,
+                                          uint64_t* __restrict__ keys, uint64_t capacity, int lane)
 {
     uint32_t cur[kBand];
 #pragma unroll
     for (int q = 0; q < kBand; ++q) cur[q] = __builtin_amdgcn_readlane(cur_b, q);
     for (uint32_t k0 = 0; k0 < n; k0 += 64) {
         const uint32_t k = k0 + lane;
-        uint32_t xs = 0u, g = 0u;
+        uint32_t xs = 0u, g = 0u, d = 0u;
         if (k < n) {
             xs = s_x[k];
             g = s_g[k];
+            if constexpr (kKeys) d = s_d[k];
         }
         // band-relative span [x0, x0 + w): packed entries are clipped to the
         // band and to the image, so a column outside them is never covered
@@ -577,7 +568,10 @@ __device__ __forceinline__ void walk_band(const uint32_t* s_g, const uint16_t* s
             const uint64_t m = __ballot(cover);
             if (cover) {
                 const uint32_t pos = cur[q] + lanes_below(m);
-                if (!kChecked || pos < capacity) out[pos] = g;
+                if (!kChecked || pos < capacity) {
+                    if (!kKeys || out) out[pos] = g;
+                    if constexpr (kKeys) keys[pos] = ((uint64_t)(tile0 + (uint32_t)q) << 32) | d;
+                }
             }
             cur[q] += (uint32_t)__popcll(m);
         }
@@ -590,13 +584,23 @@ __device__ __forceinline__ void walk_band(const uint32_t* s_g, const uint16_t* s
 // reach band b are packed, in chunk order, into dense batches through LDS,
 // and only those batches walk the band's columns.  Inside a column the
 // entries keep their chunk order, so the output is that of the plain walk.
-template <int kItems>
-__device__ __forceinline__ void level2_scatter_chunk(const BinArgs& a, int c, int lane, uint32_t* s_g, uint16_t* s_x)
+// With kKeys the 64-bit keys go out beside the values, an entry's depth key
+// loaded once for all its columns (a pass of its own over the values gathered
+// it once per pair: 130 us for the 19M pairs of 500k Gaussians at 720p).
+template <int kItems, bool kKeys>
+__device__ __forceinline__ void level2_scatter_chunk(const ListArgs& a, int c, int lane, uint32_t* s_g, uint32_t* s_d,
+                                                     uint16_t* s_x)
 {
     Items2<kItems> it;
     if (!load_items2(a, c, lane, it)) return;
+    uint32_t dk[kKeys ? kItems : 1];
+    if constexpr (kKeys) {
+#pragma unroll
+        for (int j = 0; j < kItems; ++j) dk[j] = a.depth_key[it.g[j]];
+    }
     const int blo = it.lo / kBand, bhi = (it.hi + kBand - 1) / kBand;
     const int row_tx = (int)a.row_tiles_x[it.row];
+    const uint32_t tile0 = kKeys ? a.row_tile0[it.row] : 0u;
     // cursors of band b's columns: lane l < kBand holds column b * kBand + l
     auto band_cursors = [&](int b) -> uint32_t {
         const int col = b * kBand + lane;
@@ -616,6 +620,7 @@ __device__ __forceinline__ void level2_scatter_chunk(const BinArgs& a, int c, in
             if (reach) {
                 const uint32_t slot = n + lanes_below(m);
                 s_g[slot] = it.g[j];
+                if constexpr (kKeys) s_d[slot] = dk[j];
                 s_x[slot] = (uint16_t)((e0 - bx0) | ((e1 - bx0) << 5));   // 0 <= e0 < e1 <= kBand
             }
             n += (uint32_t)__popcll(m);
@@ -624,32 +629,31 @@ __device__ __forceinline__ void level2_scatter_chunk(const BinArgs& a, int c, in
         // column cursors increase along the row: the last one bounds them all
         const uint32_t cur_last = __builtin_amdgcn_readlane(cur_b, (int)(bx1 - bx0) - 1);
         if ((uint64_t)cur_last + n <= a.capacity)
-            walk_band<false>(s_g, s_x, n, bx0, cur_b, a.values, a.capacity, lane);
+            walk_band<false, kKeys>(s_g, s_d, s_x, n, tile0 + bx0, cur_b, a.values, a.keys, a.capacity, lane);
         else
-            walk_band<true>(s_g, s_x, n, bx0, cur_b, a.values, a.capacity, lane);
+            walk_band<true, kKeys>(s_g, s_d, s_x, n, tile0 + bx0, cur_b, a.values, a.keys, a.capacity, lane);
         __syncthreads();   // the LDS is free for the next band
         cur_b = cur_next;
     }
 }
 
-template <int kItems>
-__global__ __launch_bounds__(64) void level2_scatter_kernel(BinArgs a)
+template <int kItems, bool kKeys>
+__global__ __launch_bounds__(64) void level2_scatter_kernel(ListArgs a)
 {
-    if (a.skip && *a.skip) return;   // the last render's lists hold
     __shared__ uint32_t s_g[kItems * 64];
+    __shared__ uint32_t s_d[kKeys ? kItems * 64 : 1];
     __shared__ uint16_t s_x[kItems * 64];
     const int lane = threadIdx.x;
     const int c2 = (int)a.info[kInfoC2];
-    FOR_LEVEL2_CHUNK(c, c2) level2_scatter_chunk<kItems>(a, c, lane, s_g, s_x);
+    FOR_LEVEL2_CHUNK(c, c2) level2_scatter_chunk<kItems, kKeys>(a, c, lane, s_g, s_d, s_x);
 }
 
 // Tile offsets from the scanned level-2 counts: tile (r, x) starts at chunk
 // 0's cursor in column x of row r.  A row without chunks starts where the
 // next row's block starts (the scan's running total there), or at the total
 // K when it is the last.
-__global__ __launch_bounds__(256) void tile_offsets_kernel(BinArgs a)
+__global__ __launch_bounds__(256) void tile_offsets_kernel(ListArgs a)
 {
-    if (a.skip && *a.skip) return;   // the last render's lists hold
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= a.tiles) return;
     const ViewParams& vp = a.views[view_of_tile(a.views, a.n_views, (uint32_t)t)];
@@ -709,9 +713,9 @@ void with_items2(int items, F f)
 }
 }  // namespace
 
-// Level 1 up to the row offsets (R = rows_off[rows]) and the level-2 chunk
-// table; no host dependence.
-hipError_t launch_bin_rows(const BinArgs& a, uint64_t* scan_scratch, hipStream_t s)
+// Level 1: the row lists, their offsets (R = rows_off[rows]) and the level-2
+// chunk table.  No Gaussians: the tables of empty rows.
+hipError_t launch_list_rows(const ListArgs& a, uint64_t* scan_scratch, hipStream_t s)
 {
     if (a.n == 0) {
         hipError_t e = launch_fill_u32(a.rows_off, 0u, a.rows + 1, s);
@@ -725,48 +729,37 @@ hipError_t launch_bin_rows(const BinArgs& a, uint64_t* scan_scratch, hipStream_t
                            (a.max_tiles_y + 1) * kDiffCopies * sizeof(uint32_t), s, a);
     });
     hipError_t e = launch_scan_exclusive(a.counts1, (int64_t)a.rows * a.chunks1, scan_scratch, nullptr,
-                                         a.rows_off + a.rows, a.overflow, s, nullptr, a.skip);
+                                         a.rows_off + a.rows, a.overflow, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(level2_table_kernel, dim3(1), dim3(1024), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_bin_row_scatter(const BinArgs& a, hipStream_t s)
-{
-    if (a.n == 0) return hipSuccess;
-    if (!bin_items_supported(a.items1, a.items2)) return hipErrorInvalidValue;
     with_items1(a.items1, [&](auto I) {
-        hipLaunchKernelGGL(level1_scatter_kernel<decltype(I)::value>, dim3(grid8(a.chunks1 * a.n_views)), dim3(64), 0,
-                           s, a);
+        hipLaunchKernelGGL(level1_scatter_kernel<decltype(I)::value>, dim3(grid8(grid1)), dim3(64), 0, s, a);
     });
     return hipGetLastError();
 }
 
-hipError_t launch_bin_tiles(const BinArgs& a, int grid2, uint64_t* scan_scratch, hipStream_t s)
+// Level 2: the tile offsets and, with values or keys, the lists.
+hipError_t launch_list_tiles(const ListArgs& a, uint64_t* scan_scratch, hipStream_t s)
 {
     if (a.n == 0) return launch_fill_u32(a.tile_offsets, 0u, a.tiles + 1, s);
     if (!bin_items_supported(a.items1, a.items2)) return hipErrorInvalidValue;
-    if (grid2 > 0)
-        with_items2(a.items2, [&](auto I) {
-            hipLaunchKernelGGL(level2_count_kernel<decltype(I)::value>, dim3(grid8(std::min(grid2, kMaxGrid2))),
-                               dim3(64), (a.max_tiles_x + 1) * kDiffCopies * sizeof(uint32_t), s, a);
-        });
+    const unsigned grid2 = grid8(std::min(std::max(a.max_chunks2, 1), kMaxGrid2));
+    with_items2(a.items2, [&](auto I) {
+        hipLaunchKernelGGL(level2_count_kernel<decltype(I)::value>, dim3(grid2), dim3(64),
+                           (a.max_tiles_x + 1) * kDiffCopies * sizeof(uint32_t), s, a);
+    });
     // the scan's length E2 is read on the device (info[1])
     hipError_t e = launch_scan_exclusive(a.counts2, (int64_t)a.counts2_capacity, scan_scratch, nullptr,
-                                         a.tile_offsets + a.tiles, a.overflow, s, a.info + kInfoC2Elems, a.skip);
+                                         a.tile_offsets + a.tiles, a.overflow, s, a.info + kInfoC2Elems);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(tile_offsets_kernel, dim3((unsigned)((a.tiles + 255) / 256)), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_bin_tile_scatter(const BinArgs& a, int grid2, hipStream_t s)
-{
-    if (a.n == 0 || grid2 <= 0) return hipSuccess;
-    if (!bin_items_supported(a.items1, a.items2)) return hipErrorInvalidValue;
-    with_items2(a.items2, [&](auto I) {
-        hipLaunchKernelGGL(level2_scatter_kernel<decltype(I)::value>, dim3(grid8(std::min(grid2, kMaxGrid2))),
-                           dim3(64), 0, s, a);
-    });
+    if (a.values || a.keys)
+        with_items2(a.items2, [&](auto I) {
+            if (a.keys)
+                hipLaunchKernelGGL((level2_scatter_kernel<decltype(I)::value, true>), dim3(grid2), dim3(64), 0, s, a);
+            else
+                hipLaunchKernelGGL((level2_scatter_kernel<decltype(I)::value, false>), dim3(grid2), dim3(64), 0, s, a);
+        });
     return hipGetLastError();
 }
 

@@ -20,13 +20,27 @@ __device__ __forceinline__ int cost_bucket(uint32_t c)
     return 128 + (e - 7) * 32 + (int)((c >> (e - 5)) & 31u);
 }
 
-__device__ __forceinline__ uint32_t tile_cost_of(const uint32_t* cost, const uint32_t* offsets, int64_t t)
-{
-    return cost ? cost[t] : offsets[t + 1] - offsets[t];
-}
+// A tile's cost: the entries it walked in the previous frame.
+struct WalkedCost {
+    const uint32_t* cost;
+    __device__ __forceinline__ uint32_t operator()(int64_t t) const { return cost[t]; }
+};
+// Without a previous frame: the length of its bin's list.
+struct ListLengthCost {
+    BinLists lists;
+    const ViewParams* views;
+    int n_views;
+    __device__ __forceinline__ uint32_t operator()(int64_t t) const
+    {
+        const ViewParams& vp = views[view_of_tile(views, n_views, (uint32_t)t)];
+        const int local = (int)t - (int)vp.tile_base;
+        const uint32_t* off = lists.off + lists.stride * (int64_t)bin_of_tile(vp, local % vp.tiles_x, local / vp.tiles_x);
+        return off[lists.stride] - off[0];
+    }
+};
 
-// Writes order[0 .. tiles): all tiles, heaviest cost bucket first, by cost[t]
-// or (cost null) by list length.  Called by every thread of a workgroup of
+// Writes order[0 .. tiles): all tiles, heaviest cost bucket first, by
+// cost_of(t).  Called by every thread of a workgroup of
 // kThreads; LDS: hist[kOrderBuckets], wsum[kThreads / 64] and, optionally,
 // kept[kept_n] (each kept tile's bucket between the passes; tiles past
 // kept_n load their cost again).  The first pass loads kOrderPre costs per
@@ -38,11 +52,9 @@ __device__ __forceinline__ uint32_t tile_cost_of(const uint32_t* cost, const uin
 // many tiles share a bucket, cost less issue than grouping the lanes of a
 // bucket with ballots.)
 constexpr int kOrderPre = 8;
-template <int kThreads>
-__device__ __forceinline__ void order_heaviest_first(const uint32_t* __restrict__ cost,
-                                                     const uint32_t* __restrict__ offsets, int64_t tiles,
-                                                     uint32_t* __restrict__ order, uint32_t* hist, uint32_t* wsum,
-                                                     uint16_t* kept, int64_t kept_n)
+template <int kThreads, typename Cost>
+__device__ __forceinline__ void order_heaviest_first(Cost cost_of, int64_t tiles, uint32_t* __restrict__ order,
+                                                     uint32_t* hist, uint32_t* wsum, uint16_t* kept, int64_t kept_n)
 {
     static_assert(kOrderBuckets % kThreads == 0, "whole buckets per thread in the scan");
     constexpr int kPer = kOrderBuckets / kThreads;
@@ -55,7 +67,7 @@ __device__ __forceinline__ void order_heaviest_first(const uint32_t* __restrict_
 #pragma unroll
         for (int k = 0; k < kOrderPre; ++k) {
             const int64_t t = t0 + k * kThreads + tid;
-            c[k] = tile_cost_of(cost, offsets, t < tiles ? t : 0);
+            c[k] = cost_of(t < tiles ? t : 0);
         }
 #pragma unroll
         for (int k = 0; k < kOrderPre; ++k) {
@@ -99,7 +111,7 @@ __device__ __forceinline__ void order_heaviest_first(const uint32_t* __restrict_
 #pragma unroll
             for (int k = 0; k < kOrderPre; ++k) {
                 const int64_t t = t0 + k * kThreads + tid;
-                c[k] = tile_cost_of(cost, offsets, t < tiles ? t : 0);
+                c[k] = cost_of(t < tiles ? t : 0);
             }
         }
 #pragma unroll
