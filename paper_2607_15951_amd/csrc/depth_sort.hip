@@ -7,6 +7,8 @@
 // K ~ 80 N pairs.  The tile digit is then one stable counting pass
 // (tile_bin.hip) that writes each pair straight to its sorted position.
 //
+// Few keys take fewer launches (below).
+//
 // Several views are sorted at once as segments of one array (one segment per
 // view, items v * n + i); no block straddles two segments.
 //
@@ -22,9 +24,9 @@
 // depths as numbers (negative ones, behind the camera, first); keys of
 // Gaussians without a finite depth are 0xFFFFFFFF and sink to the end.
 // Values start as the Gaussian index, so ties in depth stay in index order.
-// A segment that fits one block takes one launch per pass: the scatter
-// counts its block's digits itself (no histogram, no offset table).
 #include "gs_internal.h"
+
+#include <algorithm>
 
 namespace gsmi {
 namespace {
@@ -53,6 +55,19 @@ __device__ __forceinline__ uint32_t sort_key(uint32_t b)
 {
     if (b == 0xFFFFFFFFu) return b;
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+
+// Valid lanes of this wave that hold the lane's digit.
+__device__ __forceinline__ uint64_t same_digit_lanes(uint32_t d, bool valid)
+{
+    uint64_t m = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const bool bit = (d >> b) & 1u;
+        const uint64_t bb = __ballot(bit);
+        m &= bit ? bb : ~bb;
+    }
+    return m;
 }
 
 template <int kItems>
@@ -205,14 +220,7 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
         const bool valid = idx < end;
         if (!valid) key[k] = val[k] = 0u;
         const uint32_t d = (sort_key(key[k]) >> shift) & 255u;
-        // lanes of this wave holding the same digit
-        uint64_t m = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const uint64_t bb = __ballot(bit);
-            m &= bit ? bb : ~bb;
-        }
+        const uint64_t m = same_digit_lanes(d, valid);
         digit[k] = valid ? d : 256u;
         rank[k] = (uint32_t)__popcll(m & lt);
         // the group's first lane records its size (groups are disjoint)
@@ -233,9 +241,7 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
                 cnt[k][w][tid] = (uint16_t)run;
                 run += c;
             }
-        // the segment's count of digit d: from the digit totals, or, when the
-        // block is the whole segment (no totals), the block's own count
-        seg_total = totals ? totals[v * 256 + tid] : run;
+        seg_total = totals[v * 256 + tid];   // the segment's count of digit d
         incl = run;
         seg_incl = seg_total;
 #pragma unroll
@@ -259,7 +265,7 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
             seg_before += s_ssum[w];
         }
         s_start[tid] = before + incl - run;
-        s_base[tid] = seg_before + seg_incl - seg_total + (offsets ? offsets[row + (int64_t)tid * bpv] : 0u);
+        s_base[tid] = seg_before + seg_incl - seg_total + offsets[row + (int64_t)tid * bpv];
     }
     __syncthreads();
     uint32_t local[kItems];
@@ -301,15 +307,10 @@ void launch_sort_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, 
     uint32_t* totals = counts;
     uint32_t* table = counts + (int64_t)256 * n_views;
     uint32_t* hist = table + (int64_t)256 * nblocks;
-    if (bpv > 1) {
-        hipLaunchKernelGGL(radix_hist_kernel<kItems>, dim3(nblocks), dim3(kSortBlock), 0, s, kin, n, shift, hist,
-                           bpv, skip);
-        hipLaunchKernelGGL(radix_row_scan_kernel, dim3(256u * (unsigned)n_views), dim3(256), 0, s,
-                           (const uint32_t*)hist, table, totals, bpv, skip);
-    } else {
-        // one block per segment: the scatter counts the digits itself
-        totals = table = nullptr;
-    }
+    hipLaunchKernelGGL(radix_hist_kernel<kItems>, dim3(nblocks), dim3(kSortBlock), 0, s, kin, n, shift, hist, bpv,
+                       skip);
+    hipLaunchKernelGGL(radix_row_scan_kernel, dim3(256u * (unsigned)n_views), dim3(256), 0, s, (const uint32_t*)hist,
+                       table, totals, bpv, skip);
     // the scatter of a 16-key part runs as 1024 threads of 4 keys: the same
     // part, ranked by 16 waves of 4 rounds instead of 4 waves of 16 (0.161
     // against 0.165 ms for the four passes at 3M keys; parts of 8192 keys,
@@ -324,6 +325,278 @@ void launch_sort_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, 
         hipLaunchKernelGGL((radix_scatter_kernel<kPer, false, kThreads>), dim3(nblocks), dim3(kThreads), 0, s, kin,
                            vin, kout, vout, rect, pin, pout, n, shift, (const uint32_t*)table, (const uint32_t*)totals,
                            bpv, skip);
+}
+
+// ------------------------------------------------------- few keys
+// Up to kCountedKeys keys sort in five launches, not twelve: a pass's scatter
+// sums its segment's part histograms itself (at most 96 rows of 1 KB) and
+// counts, while it writes its items, the next pass's digits per part of where
+// they land.  Such a sort costs its launches and their latency: 5000 keys 35
+// us (65 with three launches per pass), 40000 keys 41 (68), 65536 keys 49
+// (67).  The counting adds up to one atomic per key and pass: 131072 keys
+// would take 70 us (69), 262144 keys 89 (72).
+// A segment of up to 4 x 1024 keys sorts in one launch, all four passes in LDS
+// (1000 keys: 8.4 us, 33 with a launch per pass).
+constexpr int kFusedThreads = 1024, kFusedWaves = kFusedThreads / 64;
+constexpr int64_t kCountedKeys = 98304;
+
+// One pass over a block's items in registers: ranks them by digit and leaves
+// keys, values (and payloads) in LDS in the block's stable digit order.  Item
+// (k, thread) is the block's item k * kFusedThreads + thread; valid[k] holds
+// for the first count of them.
+template <int kItems, bool kPay>
+struct FusedLds {
+    static constexpr int kPart = kItems * kFusedThreads;
+    // in digit order; before that the ranking counts cnt[k][wave][digit]
+    uint32_t buf[(kPay ? 3 : 2) * kPart];
+    uint32_t start[256];    // the block's first item of a digit
+    uint32_t total[256];    // and its items
+    uint32_t wsum[4];
+    __device__ __forceinline__ uint32_t* keys() { return buf; }
+    __device__ __forceinline__ uint32_t* vals() { return buf + kPart; }
+    __device__ __forceinline__ uint32_t* pays() { return buf + 2 * kPart; }
+};
+
+template <int kItems, bool kPay>
+__device__ __forceinline__ void fused_order(FusedLds<kItems, kPay>& L, const uint32_t (&key)[kItems],
+                                            const uint32_t (&val)[kItems], const uint32_t* pay, int count, int shift)
+{
+    uint16_t(*cnt)[kFusedWaves][256] = reinterpret_cast<uint16_t(*)[kFusedWaves][256]>(L.buf);
+    static_assert(kItems * kFusedWaves * 256 * sizeof(uint16_t) <= sizeof(L.buf), "ranking counts fit");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int i = 0; i < 2 * kItems; ++i) L.buf[i * kFusedThreads + tid] = 0u;
+    __syncthreads();
+    uint32_t digit[kItems], rank[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const bool valid = k * kFusedThreads + tid < count;
+        const uint32_t d = (sort_key(key[k]) >> shift) & 255u;
+        const uint64_t m = same_digit_lanes(d, valid);
+        digit[k] = valid ? d : 256u;
+        rank[k] = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (valid && rank[k] == 0u) cnt[k][wave][d] = (uint16_t)__popcll(m);
+    }
+    __syncthreads();
+    uint32_t run = 0u, incl = 0u;
+    if (tid < 256) {
+        uint32_t c[kItems * kFusedWaves];
+#pragma unroll
+        for (int j = 0; j < kItems * kFusedWaves; ++j) c[j] = cnt[j / kFusedWaves][j % kFusedWaves][tid];
+#pragma unroll
+        for (int j = 0; j < kItems * kFusedWaves; ++j) {
+            cnt[j / kFusedWaves][j % kFusedWaves][tid] = (uint16_t)run;
+            run += c[j];
+        }
+        L.total[tid] = run;
+        incl = run;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t t = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += t;
+        }
+        if (lane == 63) L.wsum[wave] = incl;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        uint32_t before = 0u;
+        for (int w = 0; w < wave; ++w) before += L.wsum[w];
+        L.start[tid] = before + incl - run;
+    }
+    __syncthreads();
+    uint32_t local[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k)
+        local[k] = digit[k] < 256u ? L.start[digit[k]] + cnt[k][wave][digit[k]] + rank[k] : ~0u;
+    __syncthreads();   // the counts' bytes are reused
+#pragma unroll
+    for (int k = 0; k < kItems; ++k)
+        if (local[k] != ~0u) {
+            L.keys()[local[k]] = key[k];
+            L.vals()[local[k]] = val[k];
+            if constexpr (kPay) L.pays()[local[k]] = pay[k];
+        }
+    __syncthreads();
+}
+
+// One block per segment of at most kItems * kFusedThreads keys.
+template <int kItems, bool kPay>
+__global__ __launch_bounds__(kFusedThreads) void radix_segment_kernel(const uint32_t* __restrict__ keys_in,
+                                                                      uint32_t* __restrict__ vals_out,
+                                                                      const ushort4* __restrict__ rect_in,
+                                                                      uint32_t* __restrict__ pay_out, int n,
+                                                                      const uint32_t* skip)
+{
+    if (skip && *skip) return;
+    __shared__ FusedLds<kItems, kPay> L;
+    const int tid = threadIdx.x;
+    const int64_t begin = (int64_t)blockIdx.x * n;
+    uint32_t key[kItems], val[kItems], pay[kPay ? kItems : 1];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const int i = k * kFusedThreads + tid;
+        const int64_t ic = begin + (i < n ? i : 0);
+        key[k] = keys_in[ic];
+        val[k] = (uint32_t)ic;
+        if constexpr (kPay) pay[k] = pack_rect(rect_in[ic]);
+    }
+    for (int shift = 0; shift < 32; shift += 8) {
+        fused_order<kItems, kPay>(L, key, val, pay, n, shift);
+        if (shift == 24) break;
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            const int i = k * kFusedThreads + tid;
+            key[k] = L.keys()[i];   // past n: whatever is there, never used
+            val[k] = L.vals()[i];
+            if constexpr (kPay) pay[k] = L.pays()[i];
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        const int i = k * kFusedThreads + tid;
+        if (i < n) {
+            vals_out[begin + i] = L.vals()[i];
+            if constexpr (kPay) pay_out[begin + i] = L.pays()[i];
+        }
+    }
+}
+
+// Counts the first digit of every part, hist[part][digit], and clears the
+// tables of the three passes that follow, which lie behind it.
+__global__ __launch_bounds__(kFusedThreads) void radix_first_hist_kernel(const uint32_t* __restrict__ keys, int64_t n,
+                                                                         uint32_t* __restrict__ hist, int bpv,
+                                                                         const uint32_t* skip)
+{
+    if (skip && *skip) return;
+    __shared__ uint32_t h[4][256];
+    const int tid = threadIdx.x;
+    h[tid >> 8][tid & 255] = 0u;
+    __syncthreads();
+    int64_t begin, end, row;
+    sort_block_range<kFusedThreads / kSortBlock>(n, bpv, &begin, &end, &row);
+    if (begin + tid < end) atomicAdd(&h[tid >> 8][sort_key(keys[begin + tid]) & 255u], 1u);
+    __syncthreads();
+    const int64_t at = (int64_t)blockIdx.x * 256, table = (int64_t)gridDim.x * 256;
+    const int t = tid >> 8, d = tid & 255;
+    hist[t * table + at + d] = t == 0 ? h[0][d] + h[1][d] + h[2][d] + h[3][d] : 0u;
+}
+
+// One pass: stable scatter of the block's part by the digit at shift, whose
+// counts per part are in hist; hist_next (null in the last pass) gets the
+// counts of the next digit over the parts of the output.
+template <bool kPay>
+__global__ __launch_bounds__(kFusedThreads) void radix_fused_kernel(
+    const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in, uint32_t* __restrict__ keys_out,
+    uint32_t* __restrict__ vals_out, const ushort4* __restrict__ rect_in, const uint32_t* __restrict__ pay_in,
+    uint32_t* __restrict__ pay_out, int64_t n, int shift, const uint32_t* __restrict__ hist,
+    uint32_t* __restrict__ hist_next, int bpv, const uint32_t* skip)
+{
+    if (skip && *skip) return;
+    constexpr int kPart = kFusedThreads;
+    __shared__ FusedLds<1, kPay> L;
+    __shared__ uint32_t s_total[4][256], s_before[4][256], s_base[256], s_ssum[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int64_t begin, end, row;
+    sort_block_range<kPart / kSortBlock>(n, bpv, &begin, &end, &row);
+    const int v = (int)(blockIdx.x / (unsigned)bpv), lb = (int)(blockIdx.x % (unsigned)bpv);
+    const int count = (int)(end - begin);
+    const int64_t ic = tid < count ? begin + tid : begin;
+    uint32_t key[1] = {keys_in[ic]}, val[1] = {vals_in ? vals_in[ic] : (uint32_t)ic}, pay[1];
+    if constexpr (kPay) pay[0] = pay_in ? pay_in[ic] : pack_rect(rect_in[ic]);
+    {   // digit d's count over the segment and over the parts before this one: every fourth part
+        const int q = tid >> 8, d = tid & 255;
+        const uint32_t* h = hist + (int64_t)v * bpv * 256 + d;
+        uint32_t total = 0u, before = 0u;
+#pragma unroll 8
+        for (int b = q; b < bpv; b += 4) {
+            const uint32_t c = h[b * 256];
+            total += c;
+            before += b < lb ? c : 0u;
+        }
+        s_total[q][d] = total;
+        s_before[q][d] = before;
+    }
+    fused_order<1, kPay>(L, key, val, pay, count, shift);   // synchronises before and after
+    uint32_t total = 0u, incl = 0u;
+    if (tid < 256) {
+        total = s_total[0][tid] + s_total[1][tid] + s_total[2][tid] + s_total[3][tid];
+        incl = total;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t t = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += t;
+        }
+        if (lane == 63) s_ssum[wave] = incl;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        uint32_t at = (uint32_t)((int64_t)v * n);
+        for (int w = 0; w < wave; ++w) at += s_ssum[w];
+        // less the block's start of the digit: item i goes to s_base[d] + i
+        s_base[tid] = at + incl - total + s_before[0][tid] + s_before[1][tid] + s_before[2][tid] + s_before[3][tid] -
+                      L.start[tid];
+    }
+    __syncthreads();
+    uint32_t* next = hist_next ? hist_next + (int64_t)v * bpv * 256 : nullptr;
+    const bool valid = tid < count;
+    const uint32_t kk = L.keys()[valid ? tid : 0];
+    const uint32_t sk = sort_key(kk) >> shift;
+    const uint32_t pos = s_base[sk & 255u] + (uint32_t)tid;
+    if (valid) {
+        if (keys_out) keys_out[pos] = kk;
+        vals_out[pos] = L.vals()[tid];
+        if constexpr (kPay) pay_out[pos] = L.pays()[tid];
+    }
+    if (next) {
+        // a few digits often hold most of a wave's items: those are counted
+        // together, the rest lane by lane
+        const uint32_t slot = (pos - (uint32_t)((int64_t)v * n)) / kPart * 256u + ((sk >> 8) & 255u);
+        uint64_t left = __ballot(valid);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if (!left) break;
+            const int f = __builtin_ctzll(left);
+            const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)slot, f);
+            const uint64_t m = __ballot(slot == first) & left;
+            if (lane == f) atomicAdd(&next[first], (uint32_t)__popcll(m));
+            left &= ~m;
+        }
+        if ((left >> lane) & 1u) atomicAdd(&next[slot], 1u);
+    }
+}
+
+// Items per thread with which a segment of n keys sorts in one launch, and
+// whether n_views segments do in five.
+int segment_items(int64_t n) { return n <= kFusedThreads ? 1 : (n <= 2 * kFusedThreads ? 2 : (n <= 4 * kFusedThreads ? 4 : 0)); }
+bool fused_sort(int64_t n, int64_t n_views) { return n * n_views <= kCountedKeys; }
+
+template <int kItems, bool kPay>
+void launch_segment_sort(const uint32_t* keys_in, uint32_t* vals, const ushort4* rect, uint32_t* pay, int64_t n,
+                         int n_views, const uint32_t* skip, hipStream_t s)
+{
+    hipLaunchKernelGGL((radix_segment_kernel<kItems, kPay>), dim3((unsigned)n_views), dim3(kFusedThreads), 0, s,
+                       keys_in, vals, rect, pay, (int)n, skip);
+}
+
+template <bool kPay>
+void launch_fused_sort(const uint32_t* keys_in, uint32_t* const (&keys)[2], uint32_t* const (&vals)[2],
+                       const ushort4* rect, uint32_t* const (&pay)[2], uint32_t* counts, int64_t n, int n_views,
+                       const uint32_t* skip, hipStream_t s)
+{
+    const int bpv = (int)((n + kFusedThreads - 1) / kFusedThreads);
+    const unsigned blocks = (unsigned)bpv * (unsigned)n_views;
+    const int64_t table = (int64_t)blocks * 256;
+    hipLaunchKernelGGL(radix_first_hist_kernel, dim3(blocks), dim3(kFusedThreads), 0, s, keys_in, n, counts,
+                       bpv, skip);
+    for (int pass = 0; pass < 4; ++pass) {
+        const int to = pass & 1, from = to ^ 1;
+        hipLaunchKernelGGL(radix_fused_kernel<kPay>, dim3(blocks), dim3(kFusedThreads), 0, s,
+                           pass ? (const uint32_t*)keys[from] : keys_in, pass ? (const uint32_t*)vals[from] : nullptr,
+                           pass < 3 ? keys[to] : nullptr, vals[to], rect, pass ? (const uint32_t*)pay[from] : nullptr,
+                           pay[to], n, 8 * pass, (const uint32_t*)(counts + pass * table),
+                           pass < 3 ? counts + (pass + 1) * table : nullptr, bpv, skip);
+    }
 }
 
 // ------------------------------------------------- reuse of the previous order
@@ -514,7 +787,9 @@ size_t depth_sort_hist_elems(int64_t n, int n_views)
     const int64_t bpv = (n + tile - 1) / tile;
     const int64_t V = n_views > 0 ? n_views : 1;
     const int64_t nb = bpv * V;
-    return (size_t)(256 * (V + 2 * (nb > 0 ? nb : 1)));
+    const size_t passes = (size_t)(256 * (V + 2 * (nb > 0 ? nb : 1)));
+    // few keys: one table per pass
+    return fused_sort(n, V) ? std::max(passes, (size_t)(4 * 256 * V * ((n + kFusedThreads - 1) / kFusedThreads))) : passes;
 }
 
 hipError_t launch_order_reuse(const uint32_t* keys, uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
@@ -543,6 +818,11 @@ hipError_t launch_order_reuse(const uint32_t* keys, uint32_t* keys_a, uint32_t* 
     return hipGetLastError();
 }
 
+// From here on 8 keys per thread, the default, stand for 16: a digit's runs
+// are twice as long.  Four passes of 8 and of 16: 104 and 108 us at 1.2M keys,
+// 130 and 118 at 2M, 180 and 165 at 3M, 699 and 588 at 16M.
+constexpr int64_t kWideKeys = 1500000;
+
 // Sorts each of the n_views segments keys_in[v * n .. (v + 1) * n) (not
 // modified) with values v * n + i, items keys per thread of a block.  Four
 // passes: in -> a -> b -> a -> b, so the sorted values (and payloads) end in
@@ -556,6 +836,7 @@ hipError_t launch_depth_sort(const uint32_t* keys_in, uint32_t* keys_a, uint32_t
 {
     if (n == 0 || n_views <= 0) return hipSuccess;
     if (!depth_sort_items_supported(items)) return hipErrorInvalidValue;
+    if (items == 8 && n * n_views >= kWideKeys) items = 16;
     const int64_t tile = (int64_t)kSortBlock * items;
     const int bpv = (int)((n + tile - 1) / tile);
     const unsigned nblocks = (unsigned)bpv * (unsigned)n_views;
@@ -563,6 +844,21 @@ hipError_t launch_depth_sort(const uint32_t* keys_in, uint32_t* keys_a, uint32_t
     const uint32_t* vin = nullptr;
     const uint32_t* pin = nullptr;   // the first pass packs from rect
     const uint32_t* skip = reuse_words;
+    uint32_t* const keys[2] = {keys_a, keys_b};
+    uint32_t* const vals[2] = {vals_a, vals_b};
+    uint32_t* const pay[2] = {pay_a, pay_b};
+    if (const int k = segment_items(n)) {
+        const auto launch = k == 1   ? (rect ? launch_segment_sort<1, true> : launch_segment_sort<1, false>)
+                            : k == 2 ? (rect ? launch_segment_sort<2, true> : launch_segment_sort<2, false>)
+                                     : (rect ? launch_segment_sort<4, true> : launch_segment_sort<4, false>);
+        launch(keys_in, vals_b, rect, pay_b, n, n_views, skip, s);
+        return hipGetLastError();
+    }
+    if (fused_sort(n, n_views)) {
+        (rect ? launch_fused_sort<true> : launch_fused_sort<false>)(keys_in, keys, vals, rect, pay, counts, n, n_views,
+                                                                    skip, s);
+        return hipGetLastError();
+    }
     for (int pass = 0; pass < 4; ++pass) {
         const int shift = 8 * pass;
         const bool to_b = pass % 2 == 1;
