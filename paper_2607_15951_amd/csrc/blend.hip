@@ -75,7 +75,16 @@ struct BlendLds {
 // where every pixel has terminated, a larger one fewer barriers.  Called by
 // all 256 threads of the workgroup with the same tile; the LDS is free again
 // once every thread has returned.
-template <bool kStats, int kBatch>
+//
+// kFew: the form for grids of few tiles, where a SIMD has one wave or two and
+// a wave waits for each entry's LDS reads, masks and branches.  Four entries
+// at a time are read and their alphas computed together, and a pixel's state
+// holds its termination (Tr = 0, the kept transmittance in Tf), so that
+// compositing an entry is a chain of vector selects without scalar masks: 33
+// vector instructions an entry, not 27, but about 140 cycles, not 260.  At 273
+// tiles (40K Gaussians, 333x197) 123 us, 146 in the plain form; at 240 tiles
+// (20K, 317x179) 80 and 97; at 64 tiles (1000, 128x128) 16 and 20.
+template <bool kStats, int kBatch, bool kFew = false>
 __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, int tile, BlendLds<kBatch>& L)
 {
     constexpr int kPer = kBatch > 256 ? kBatch / 256 : 1;   // entries a lane stages per batch
@@ -108,6 +117,8 @@ __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, int tile, Bl
     float Tr = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
     uint32_t last = 0, term = 0, composited = 0, staged = 0, bodies = 0;
     bool done = !inside;
+    float Tf = 0.0f;   // kFew: the transmittance of a pixel that has terminated, whose Tr is 0
+    if (kFew && !inside) Tr = 0.0f;
     // software pipeline of the gathers: entries picked from the bin's list
     // two batches ahead, the 48-byte records one batch ahead, both
     // overlapping the compositing.
@@ -215,54 +226,95 @@ __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, int tile, Bl
             __syncthreads();
             tc.fill(L.pick, b0 + 3 * kBatch, wave, lane);
         }
-        // this wave's entries of the batch: bit j of bits[j / 64] when entry j
-        // can reach the wave's quad (scalar registers, no per-entry LDS read)
-        uint64_t bits[kWords];
+        if constexpr (kFew) {
+            constexpr int kGroup = 4;
+            for (int q = 0; q < nk; q += 64) {
+                const int jj = q + lane;
+                uint64_t bits = __builtin_amdgcn_ballot_w64(jj < nk && ((s_mask[jj] >> wave) & 1u));
+                while (bits && __builtin_amdgcn_ballot_w64(Tr > 0.0f) != 0) {
+                    float4 e0[kGroup], e1[kGroup], e2[kGroup];
+                    float al[kGroup];
 #pragma unroll
-        for (int q = 0; q < kWords; ++q) {
-            const int jj = q * 64 + lane;
-            bits[q] = __ballot(jj < nk && ((s_mask[jj] >> wave) & 1u));
-        }
-        for (int j0 = 0; j0 < nk; j0 += kUnroll) {
-            if (__ballot(!done) == 0) break;   // whole wave finished
-            const uint64_t word = bits[j0 >> 6] >> (j0 & 63);
-            if ((word & kGroupMask) == 0) continue;   // none of the next kUnroll reaches the quad
-            // the group's LDS byte offset in a VGPR: every entry below reads
-            // at a constant offset from it (no per-entry address move)
-            uint32_t gofs = (uint32_t)j0 * (uint32_t)sizeof(float4);
-            __asm__ volatile("" : "+v"(gofs));
-            const char* g0 = reinterpret_cast<const char*>(s0) + gofs;
-            const char* g1 = reinterpret_cast<const char*>(s1) + gofs;
-            const char* g2 = reinterpret_cast<const char*>(s2) + gofs;
+                    for (int g = 0; g < kGroup; ++g) {
+                        const int j = bits ? q + __builtin_ctzll(bits) : nk;   // nk: a padding entry
+                        bits &= bits - 1;
+                        e0[g] = s0[j];
+                        e1[g] = s1[j];
+                        e2[g] = s2[j];
+                    }
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                // an entry out of this quad's reach is skipped by the whole wave
-                if (!((word >> u) & 1u)) continue;
-                if (kStats) ++bodies;
-                const float4 e0 = reinterpret_cast<const float4*>(g0)[u];
-                const float4 e1 = reinterpret_cast<const float4*>(g1)[u];
-                const float4 e2 = reinterpret_cast<const float4*>(g2)[u];
-                float dx, dy, E;
-                const float al = entry_alpha(e0, e1, fx, fy, dx, dy, E);
-                const float tn = fmaf(-al, Tr, Tr);   // Tr (1 - al), rounded once
-                const bool pass = al >= 1.0f / 255.0f;
-                const bool stop = pass && tn < 1e-4f && !done;
-                const bool take = pass && !stop && !done;
-                const uint32_t pos1 = (uint32_t)__float_as_int(e2.w);   // list position + 1
-                if (kStats) term = stop ? pos1 : term;
-                done = done || stop;
-                if (take) {   // under the lane mask: no selects
-                    const float wt = al * Tr;
-                    c0 = fmaf(wt, e2.x, c0);
-                    c1 = fmaf(wt, e2.y, c1);
-                    c2 = fmaf(wt, e2.z, c2);
-                    Tr = tn;
-                    last = pos1;
+                    for (int g = 0; g < kGroup; ++g) {
+                        float dx, dy, E;
+                        const float x = entry_alpha(e0[g], e1[g], fx, fy, dx, dy, E);
+                        al[g] = x >= 1.0f / 255.0f ? x : 0.0f;
+                    }
+#pragma unroll
+                    for (int g = 0; g < kGroup; ++g) {
+                        const float tn = fmaf(-al[g], Tr, Tr);   // Tr (1 - al), rounded once; Tr when skipped
+                        const bool stop = tn < 1e-4f;            // now or earlier (Tr is 0 then)
+                        const float wt = stop ? 0.0f : al[g] * Tr;
+                        Tf = stop ? fmaxf(Tf, Tr) : Tf;
+                        Tr = stop ? 0.0f : tn;
+                        const bool take = wt > 0.0f;
+                        c0 = take ? fmaf(wt, e2[g].x, c0) : c0;
+                        c1 = take ? fmaf(wt, e2[g].y, c1) : c1;
+                        c2 = take ? fmaf(wt, e2[g].z, c2) : c2;
+                        last = take ? (uint32_t)__float_as_int(e2[g].w) : last;   // list position + 1
+                    }
                 }
-                if (kStats) composited += take ? 1u : 0u;
+            }
+            done = !(Tr > 0.0f);
+        } else {
+            // this wave's entries of the batch: bit j of bits[j / 64] when entry j
+            // can reach the wave's quad (scalar registers, no per-entry LDS read)
+            uint64_t bits[kWords];
+    #pragma unroll
+            for (int q = 0; q < kWords; ++q) {
+                const int jj = q * 64 + lane;
+                bits[q] = __ballot(jj < nk && ((s_mask[jj] >> wave) & 1u));
+            }
+            for (int j0 = 0; j0 < nk; j0 += kUnroll) {
+                if (__ballot(!done) == 0) break;   // whole wave finished
+                const uint64_t word = bits[j0 >> 6] >> (j0 & 63);
+                if ((word & kGroupMask) == 0) continue;   // none of the next kUnroll reaches the quad
+                // the group's LDS byte offset in a VGPR: every entry below reads
+                // at a constant offset from it (no per-entry address move)
+                uint32_t gofs = (uint32_t)j0 * (uint32_t)sizeof(float4);
+                __asm__ volatile("" : "+v"(gofs));
+                const char* g0 = reinterpret_cast<const char*>(s0) + gofs;
+                const char* g1 = reinterpret_cast<const char*>(s1) + gofs;
+                const char* g2 = reinterpret_cast<const char*>(s2) + gofs;
+    #pragma unroll
+                for (int u = 0; u < kUnroll; ++u) {
+                    // an entry out of this quad's reach is skipped by the whole wave
+                    if (!((word >> u) & 1u)) continue;
+                    if (kStats) ++bodies;
+                    const float4 e0 = reinterpret_cast<const float4*>(g0)[u];
+                    const float4 e1 = reinterpret_cast<const float4*>(g1)[u];
+                    const float4 e2 = reinterpret_cast<const float4*>(g2)[u];
+                    float dx, dy, E;
+                    const float al = entry_alpha(e0, e1, fx, fy, dx, dy, E);
+                    const float tn = fmaf(-al, Tr, Tr);   // Tr (1 - al), rounded once
+                    const bool pass = al >= 1.0f / 255.0f;
+                    const bool stop = pass && tn < 1e-4f && !done;
+                    const bool take = pass && !stop && !done;
+                    const uint32_t pos1 = (uint32_t)__float_as_int(e2.w);   // list position + 1
+                    if (kStats) term = stop ? pos1 : term;
+                    done = done || stop;
+                    if (take) {   // under the lane mask: no selects
+                        const float wt = al * Tr;
+                        c0 = fmaf(wt, e2.x, c0);
+                        c1 = fmaf(wt, e2.y, c1);
+                        c2 = fmaf(wt, e2.z, c2);
+                        Tr = tn;
+                        last = pos1;
+                    }
+                    if (kStats) composited += take ? 1u : 0u;
+                }
             }
         }
     }
+    if (kFew) Tr = fmaxf(Tr, Tf);
     if (kStats) {   // tracing only: one record per tile, no shared counters
         // a pixel examines its tile's list up to its terminating entry
         const uint32_t list_len = tc.tail;   // whole when a pixel walked past every entry
@@ -310,6 +362,18 @@ blend_kernel(BlendArgs a)
 {
     __shared__ BlendLds<kBatch> lds;
     blend_tile_walk<kStats, kBatch>(a, blend_tile(a.order, a.group), lds);
+}
+
+// The form for grids of few tiles.  The line: plain and few, 131 and 114 us at
+// 2560 tiles (300K, 1024x640), 186 and 169 (500K), 105 and 107 at 3600 (500K,
+// 1280x720), 151 and 145 (1M), 129 and 154 at 5700 (1M, 1600x900), 214 and 253
+// at 8160 (1M, 1920x1080): more tiles fill the SIMDs, and the plain form's
+// fewer instructions count.
+constexpr int64_t kFewTiles = 3072;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void blend_few_kernel(BlendArgs a)
+{
+    __shared__ BlendLds<256> lds;
+    blend_tile_walk<false, 256, true>(a, blend_tile(a.order, a.group), lds);
 }
 
 // Persistent form: a grid of at most as many workgroups as the chip holds at
@@ -416,7 +480,10 @@ hipError_t launch_blend(const BlendArgs& a, hipStream_t s)
     switch (a.batch) {
     case 128: a.tile_work ? go(blend_kernel<true, 128>) : go(blend_kernel<false, 128>); break;
     case 512: a.tile_work ? go(blend_kernel<true, 512>) : go(blend_kernel<false, 512>); break;
-    case 256: a.tile_work ? go(blend_kernel<true, 256>) : go(blend_kernel<false, 256>); break;
+    case 256:
+        if (a.tile_work) go(blend_kernel<true, 256>);
+        else T <= kFewTiles ? go(blend_few_kernel) : go(blend_kernel<false, 256>);
+        break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
