@@ -704,8 +704,15 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     if (tu.blend_group <= 0) {
         uint32_t* order = static_cast<uint32_t*>(w.tile_order.p);
         // ordered by the projection's extra workgroup, or here by list length
-        if (!order_in_project)
+        // (a render that leaves no history orders every frame by list length:
+        // while the chip holds all its tiles at once that is a launch, 6 us,
+        // for nothing)
+        if (noalloc && tu.blend_group == 0 && T <= 512) {
+            bl.group = 1;
+            order = nullptr;
+        } else if (!order_in_project) {
             HIP_TRY(launch_blend_order(nullptr, bl.lists, views, V, T, order, s), "blend order");
+        }
         bl.order = order;
         // the queue head was cleared with the frame's counters
         if (tu.blend_group < 0) bl.queue = counters + kCounterBlendQueue;

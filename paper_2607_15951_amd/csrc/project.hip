@@ -610,7 +610,7 @@ __global__ __launch_bounds__(1024) void reduce_partials_kernel(const uint32_t* _
     __shared__ unsigned long long s_sum[16][6];
     const int v = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     unsigned long long t[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll 4
+#pragma unroll 8
     for (int b = threadIdx.x; b < blocks; b += 1024) {
         const uint4* pp = reinterpret_cast<const uint4*>(partials + kPartials * ((int64_t)b * n_views + v));
         const uint4 lo = pp[0];
@@ -628,19 +628,18 @@ __global__ __launch_bounds__(1024) void reduce_partials_kernel(const uint32_t* _
         if (lane == 0) s_sum[wave][k] = t[k];
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 0; k < 6; ++k) t[k] = 0;
-        for (int w = 0; w < 16; ++w)
-            for (int k = 0; k < 6; ++k) t[k] += s_sum[w][k];
-        const uint32_t moved = !changed ? 0u : (t[3] > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)t[3]);
-        const uint32_t c[kViewCounters] = {(uint32_t)t[0], (uint32_t)t[2], (uint32_t)t[1], (uint32_t)(t[1] >> 32),
-                                           (uint32_t)t[4], (uint32_t)(t[4] >> 32), (uint32_t)t[5],
-                                           (uint32_t)(t[5] >> 32), moved, 0u};
-        for (int k = 0; k < kViewCounters; ++k) {
-            view_counts[(int64_t)kViewCounters * v + k] = c[k];
-            if (counts_out) counts_out[(int64_t)kViewCounters * v + k] = c[k];
-        }
-        if (counts_out) __threadfence_system();   // may be pinned host memory, read after an event
+    if (threadIdx.x < kViewCounters) {   // one thread per counter
+        // its sum, and whether the counter is that sum's upper half
+        const int k = threadIdx.x, of = k == 0 ? 0 : (k == 1 ? 2 : (k < 4 ? 1 : (k < 6 ? 4 : (k < 8 ? 5 : 3))));
+        unsigned long long sum = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) sum += s_sum[w][of];
+        uint32_t c = (k == 3 || k == 5 || k == 7) ? (uint32_t)(sum >> 32) : (uint32_t)sum;
+        const uint32_t moved = !changed || k != 8 ? 0u : (sum > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)sum);
+        if (k >= 8) c = moved;   // the last counter is spare
+        view_counts[(int64_t)kViewCounters * v + k] = c;
+        // may be pinned host memory, read after an event past the kernel
+        if (counts_out) counts_out[(int64_t)kViewCounters * v + k] = c;
         if (moved) {
             // views add their counts; any change clears the flag (all
             // writers store the same 0)

@@ -23,6 +23,7 @@ TILE = 16
     (129, 65, 63, 2.5),        # 9 x 5 tiles: bins cut on both sides; fewer than a wave's Gaussians
     (641, 487, 3000, 2.0),     # large rectangles: bin by bin
     (641, 487, 20011, -1.5),   # about a tile each: entry by entry
+    (333, 197, 40000, 0.0),    # 13K counts: one scan launch
     (4097, 33, 1500, 1.0),     # 257 tiles wide: rectangles gathered
     (12288, 1088, 800, 1.0),   # 864 bins of 8x8 tiles: more than 768
     (32768, 2064, 600, 1.0),   # 4352 bins: cursors in the count table
