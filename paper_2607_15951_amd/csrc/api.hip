@@ -392,7 +392,7 @@ void choose_bins(gs_context* ctx, int64_t n, const gs_render_opts* opts, std::ve
 // The bins of a render's views and the chunks its binning cuts them from.
 struct BinShape {
     int64_t bins = 0;
-    int max_bins = 0, max_diff = 0;
+    int max_bins = 0, max_diff = 0, min_shift = 3;
     int items1 = 0, chunk = 0, chunks1 = 0;
     bool packed = true;   // the grids fit packed rectangles
     size_t table_elems() const { return (size_t)(bins * chunks1 + 2); }
@@ -405,6 +405,7 @@ BinShape bin_shape(const std::vector<ViewParams>& hv, int64_t n, int tuned)
         b.bins += (int64_t)v.bins_x * v.bins_y;
         b.max_bins = std::max(b.max_bins, v.bins_x * v.bins_y);
         b.max_diff = std::max(b.max_diff, (v.bins_x + 1) * (v.bins_y + 1));
+        b.min_shift = std::min(b.min_shift, v.bin_shift);
         b.packed = b.packed && v.tiles_x <= kPackedRectTiles && v.tiles_y <= kPackedRectTiles;
     }
     bins_chunk_shape(n, (int)hv.size(), b.bins, b.max_bins, tuned, &b.items1, &b.chunk, &b.chunks1);
@@ -605,6 +606,7 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     ba.bins = bs.bins;
     ba.max_bins = bs.max_bins;
     ba.max_diff = bs.max_diff;
+    ba.min_shift = bs.min_shift;
     ba.items1 = bs.items1;
     ba.chunk = bs.chunk;
     ba.chunks1 = bs.chunks1;

@@ -41,10 +41,17 @@ namespace {
 constexpr int kWaves = 4;
 constexpr int kMaxBins4 = 768, kMaxBins1 = 4096;
 
-// Entries that a round of the scatter stages in LDS, and its Gaussians.
-constexpr int kStage = 4096, kRoundItems = 512;
-static_assert(kWaves * kMaxBins4 <= kStage, "one Gaussian per wave fits a round");
-static_assert(kMaxBins4 <= 1024 && kRoundItems <= 1024, "staged words hold 10 bits of each");
+// Entries that a round of the scatter stages in LDS, and its Gaussians, as
+// multiples of these.  Twice as many where the bins are at their largest (so
+// Gaussians take several each) and more than kLongBins: eight entries a bin and
+// round are runs of half a cache line.  At 6M Gaussians and 3840x2160 (510
+// bins of 8x8 tiles) 480 us so, 412 with twice as many; elsewhere the LDS costs
+// more than the runs give (3M at 1080p, 135 bins, 75 and 76 us; 2M small ones,
+// 510 bins of 4x4 tiles, 72 and 94).
+constexpr int kStage0 = 4096, kRoundItems0 = 512;
+constexpr int kLongBins = 384;
+static_assert(kWaves * kMaxBins4 <= kStage0, "one Gaussian per wave fits a round");
+static_assert(kMaxBins4 <= 1024 && 2 * kRoundItems0 <= 1024, "staged words hold 10 bits of each");
 
 // A batch of 64 items goes bin by bin when each bin of its common rectangle
 // is touched by more than this many of them on average.
@@ -434,8 +441,10 @@ __device__ __forceinline__ void place_batch(uint2 w, int bx, int shift, int lane
 // kernel (10M entries in 0.12 ms, 46M in 0.75 ms).  A round is 4 p
 // consecutive Gaussians, p per wave; p halves while they do not fit and
 // doubles while they would.
+template <int kTimes>
 __global__ __launch_bounds__(64 * kWaves) void bins_scatter_kernel(BinArgs a)
 {
+    constexpr int kStage = kTimes * kStage0, kRoundItems = kTimes * kRoundItems0;
     if (a.skip && *a.skip) return;   // the last render's lists hold
     // each wave's masks (whose bytes first hold its difference array), each
     // wave's cursors, then each bin's place in its list
@@ -729,7 +738,8 @@ hipError_t launch_bins_scatter(const BinArgs& a0, hipStream_t s)
     const dim3 grid(grid_of((int64_t)a.chunks1 * a.n_views));
     switch (bin_waves(a.max_bins)) {
     case kWaves:
-        hipLaunchKernelGGL(bins_scatter_kernel, grid, dim3(64 * kWaves),
+        hipLaunchKernelGGL(a.min_shift == 3 && a.max_bins > kLongBins ? bins_scatter_kernel<2> : bins_scatter_kernel<1>,
+                           grid, dim3(64 * kWaves),
                            (size_t)kWaves * a.lds_mask * 8 + (size_t)(kWaves + 2) * a.max_bins * 4, s, a);
         break;
     case 1:

@@ -185,6 +185,7 @@ struct BinArgs {
     int64_t bins;                 // bins over all views
     int max_bins;                 // bins of the largest grid
     int max_diff;                 // largest (bins_x + 1) (bins_y + 1)
+    int min_shift;                // smallest bin edge (log2 tiles)
     int items1, chunk, chunks1;   // chunk shape (bins_chunk_shape): items per lane and round, Gaussians, chunks per view
     int lds_mask;                 // set by the launch
     // [1 + bins * chunks1 + 1]: a zero, then counts[bin][chunk], scanned to

@@ -25,6 +25,7 @@ TILE = 16
     (641, 487, 20011, -1.5),   # about a tile each: entry by entry
     (333, 197, 40000, 0.0),    # 13K counts: one scan launch
     (4097, 33, 1500, 1.0),     # 257 tiles wide: rectangles gathered
+    (6144, 2040, 900, 1.0),    # 768 bins of 8x8 tiles: the long rounds
     (12288, 1088, 800, 1.0),   # 864 bins of 8x8 tiles: more than 768
     (32768, 2064, 600, 1.0),   # 4352 bins: cursors in the count table
 ])
