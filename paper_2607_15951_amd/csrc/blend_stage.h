@@ -217,6 +217,9 @@ struct TileCursor {
         const uint32_t n = p.total();
         if (lane == 0) pick.count[wave] = n;
         cur += kRound;
+        // the items are here before the caller issues its gathers: waited for
+        // in put(), they would make it wait for those as well
+        __asm__ volatile("" : "+v"(p.it.x), "+v"(p.it.y), "+v"(p.it.z), "+v"(p.it.w));
     }
 
     // Second half, a barrier later: the picked items to the ring.
