@@ -427,7 +427,7 @@ gs_status gs_get_list_reuse(gs_context* ctx, uint32_t* out2);
  *                     one; the backward follows its render's order
  *   blend_batch       list entries the blend stages from HBM into on-chip
  *                     memory per batch: 128, 256 or 512 (the backward
- *                     stages 192)
+ *                     stages 128)
  * A new context starts at {8, 8, 16, 0, 256}.  gs_set_tuning applies to the
  * following renders and backwards (a backward uses its render's shapes; a
  * captured graph keeps those of its capture); GS_ERR_INVALID_ARGUMENT for an

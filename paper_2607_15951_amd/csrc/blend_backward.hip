@@ -20,13 +20,14 @@
 // Layout as the forward: one workgroup of four waves per 16x16 tile, one pixel
 // per lane, entries staged through LDS with the same per-quad reach masks.
 // Vector instructions bound it (92% of their issue rate), so an entry's sums
-// over a wave are taken as moments of dL/dp in dx and dy, summed with as few
+// over a wave are taken before what they share (the opacity, the factors, for
+// the conic all but the second moments of dL/dp), summed with as few
 // cross-lane instructions as they need (below) and added into an LDS row of
-// the staged entry; what the moments share (the conic, the opacity, factors)
-// is applied once per tile and entry, after the batch, on the way to nine
-// atomic adds in HBM.  At 3M Gaussians and 1920x1080: 535 us, 672 with nine
-// full gradients per pixel and a trading butterfly; four 640x480 views of 300K:
-// 379 us, 498 so; 20K at 317x179: 176 us, 288 so.
+// the staged entry; the rest is applied once per tile and entry, after the
+// batch, on the way to nine atomic adds in HBM.  At 3M Gaussians and
+// 1920x1080: 541 us, 672 with nine full gradients per pixel and a trading
+// butterfly; four 640x480 views of 300K: 362 us, 498 so; 20K at 317x179: 163 us,
+// 288 so.
 // (Matrix instructions over 16 rows of moments of four entries took 246 us of
 // the matrix cores at the first size and 811 us in all: their sums leave in
 // more lanes than LDS atomics take quickly.)
@@ -36,11 +37,14 @@ namespace gsmi {
 namespace {
 
 constexpr float kLn2 = 0.69314718055994531f;
-constexpr int kBackBatch = 192;   // entries staged per batch
+// Entries staged per batch: 20 KB of LDS with their sums, for seven workgroups a
+// CU (192 and six: 1 to 3% slower at the three sizes above).
+constexpr int kBackBatch = 128;
+constexpr int kFlush = 256 / kGrad2d;   // entries whose sums are flushed at once
 
 // The sums of an entry over a tile's pixels, with gp = dL/dp and w = a T, in
 // the order in which wave_sum9 leaves them in the lanes.
-enum { kS1, kSy, kSx, kSxx, kSxy, kSr, kSyy, kSg, kSb };   // gp, gp dy, gp dx, gp dx^2, gp dx dy, w G_r, ...
+enum { kS1, kSv, kSu, kSxx, kSxy, kSr, kSyy, kSg, kSb };   // gp, gp dp/dv / ln2, gp dp/du / ln2, gp dx^2, ...
 
 struct BackLds {
     float4 s0[kBackBatch];   // du_hi, dv_hi, du_lo, dv_lo
@@ -77,7 +81,7 @@ __device__ __forceinline__ float half_sums16(float a, float b)
 // and five LDS exchanges, whole-row rotations of three registers 30.)
 __device__ __forceinline__ float wave_sum9(const float (&g)[9])
 {
-    const float h0 = half_sums32(g[kS1], g[kSx]), h1 = half_sums32(g[kSy], g[kSxx]), h2 = half_sums32(g[kSxy], g[kSyy]),
+    const float h0 = half_sums32(g[kS1], g[kSu]), h1 = half_sums32(g[kSv], g[kSxx]), h2 = half_sums32(g[kSxy], g[kSyy]),
                 h3 = half_sums32(g[kSr], g[kSg]);
     const float q0 = half_sums16(h0, h1), q1 = half_sums16(h2, h3);
     float t, u = g[kSb];
@@ -101,24 +105,7 @@ __device__ __forceinline__ float wave_sum9(const float (&g)[9])
     return t;
 }
 
-// Gradient c of an entry (u, v, A, B, C, opacity, r, g, b) from its sums.
-__device__ __forceinline__ float entry_gradient(int c, const float* s, const float4& e1)
-{
-    switch (c) {
-    // dp/d(dx) = -(A dx + B dy) = ln2 (2 A' dx + B' dy)
-    case 0: return kLn2 * (2.0f * e1.x * s[kSx] + e1.y * s[kSy]);
-    case 1: return kLn2 * (2.0f * e1.z * s[kSy] + e1.y * s[kSx]);
-    case 2: return -0.5f * s[kSxx];
-    case 3: return -s[kSxy];
-    case 4: return -0.5f * s[kSyy];
-    case 5: return s[kS1] != 0.f ? s[kS1] / e1.w : 0.f;   // sum of dL/dp over the opacity
-    case 6: return s[kSr];
-    case 7: return s[kSg];
-    default: return s[kSb];
-    }
-}
-
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void blend_backward_kernel(BlendBackArgs a)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void blend_backward_kernel(BlendBackArgs a)
 {
     __shared__ BackLds L;
     int tile = blend_tile(a.order, a.group);
@@ -159,6 +146,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
     const bool holds = (lane & 7) == 0 || lane == 63;
     const int slot = lane == 63 ? 8 : ((lane & 8) >> 1) + (lane >> 4);
     float* const acc = &L.s_acc[0][slot];
+    // the thread's gradient when the sums are flushed: which one, from which
+    // sum, times what
+    const int flush_j = tid / kGrad2d, flush_c = tid % kGrad2d;
+    constexpr int kOf[kGrad2d] = {kSu, kSv, kSxx, kSxy, kSyy, kS1, kSr, kSg, kSb};
+    int flush_of = 0;
+#pragma unroll
+    for (int c = 0; c < kGrad2d; ++c) flush_of = flush_c == c ? kOf[c] : flush_of;
+    const float flush_by = flush_c < 2 ? kLn2 : (flush_c == 3 ? -1.0f : (flush_c < 5 ? -0.5f : 1.0f));
 
     // the forward's pipeline: entries picked two batches ahead, records one
     tc.begin_pick(L.pick, wave, lane);
@@ -257,21 +252,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
                     g[kSb] = G2 * w;
                 }
                 g[kS1] = gp;
-                g[kSx] = gp * dx;
-                g[kSy] = gp * dy;
-                g[kSxx] = g[kSx] * dx;
-                g[kSxy] = g[kSx] * dy;
-                g[kSyy] = g[kSy] * dy;
+                // dp/d(dx) = -(A dx + B dy) = ln2 (2 A' dx + B' dy): formed per
+                // pixel, since for a needle its two terms cancel (from the sums
+                // of dx and dy, 25 us less at 3M, the centres' errors are 2%
+                // larger)
+                const float cy = e1.z * dy;
+                g[kSu] = gp * fmaf(e1.x, dx, fmaf(e1.x, dx, e1.y * dy));
+                g[kSv] = gp * fmaf(e1.y, dx, cy + cy);
+                const float gx = gp * dx, gy = gp * dy;
+                g[kSxx] = gx * dx;
+                g[kSxy] = gx * dy;
+                g[kSyy] = gy * dy;
                 const float v = wave_sum9(g);
-                if (holds) atomicAdd(acc + j * kGrad2d, v);
+                // (the row's offset stays scalar: as part of the address it
+                // becomes a 64-bit multiply-add)
+                int row = j * kGrad2d;
+                __asm__("" : "+s"(row));
+                if (holds) atomicAdd(acc + row, v);
             }
         }
         __syncthreads();
-        // one set of atomic adds per staged entry and tile
-        for (int k = tid; k < nk * kGrad2d; k += 256) {
-            const int j = k / kGrad2d, c = k % kGrad2d;
-            const float v = entry_gradient(c, L.s_acc[j], L.s1[j]);
-            if (v != 0.f) unsafeAtomicAdd(&a.grad2d[(int64_t)L.s_item[j] * kGrad2d + c], v);
+        // one set of atomic adds per staged entry and tile: thread 9 i + c adds
+        // gradient c (u, v, A, B, C, opacity, r, g, b) of entries i, i + 28, ...
+        if (tid < kFlush * kGrad2d) {
+            for (int j = flush_j; j < nk; j += kFlush) {
+                float v = L.s_acc[j][flush_of];
+                if (flush_c == 5) v = v != 0.f ? v / L.s1[j].w : 0.f;   // sum of dL/dp over the opacity
+                else v *= flush_by;
+                if (v != 0.f) unsafeAtomicAdd(&a.grad2d[(int64_t)L.s_item[j] * kGrad2d + flush_c], v);
+            }
         }
     }
 }
