@@ -579,22 +579,27 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     // previous lists hold, which every kernel of the sort and the binning
     // reads on the device
     pa.changed = try_lists ? counters + kCounterChanged : nullptr;
-    HIP_TRY(launch_project(pa, s), "project");
+    // the first launch of the sort sums the projection's counts: 5 us less a
+    // frame up to 500K Gaussians, while at 3M its one workgroup of 256 threads
+    // takes 8 us more than the launch of 1024 that it saves.  Not where
+    // something reads them before it (list reuse: the flag; order reuse; a
+    // copy to the host).
+    const bool reuse = !noalloc && (o.flags & GS_RENDER_REUSE_ORDER) && V == 1 && n > 0 && prev_order_n == n;
+    const bool sort_sums = n > 0 && n <= 1000000 && !try_lists && !reuse && !(eager && !ctx->host_info_dev);
+    HIP_TRY(launch_project(pa, !sort_sums, s), "project");
     STAGE_MARK(1);
     ctx->lists_compared = try_lists;
 
     // the host waits for the sizes of an eager render (K, to refuse 2^32
     // pairs, and the bin entries, to size their buffer) only after the sort
     // and the binning are queued: the GPU works on while they travel
-    if (eager && n > 0) {
-        if (!ctx->host_info_dev)
-            HIP_TRY(hipMemcpyAsync(ctx->host_info, counts_out, (size_t)V * kViewCounters * 4, hipMemcpyDeviceToHost, s),
-                    "read sizes");
-        HIP_TRY(hipEventRecord(ctx->sizes_ev, s), "hipEventRecord");
-    } else if (learn) {
-        HIP_TRY(hipEventRecord(ctx->sizes_ev, s), "hipEventRecord");
-        ctx->counts_pending = true;
-    }
+    const bool sizes_event = (eager && n > 0) || learn;
+    if (eager && n > 0 && !ctx->host_info_dev)
+        HIP_TRY(hipMemcpyAsync(ctx->host_info, counts_out, (size_t)V * kViewCounters * 4, hipMemcpyDeviceToHost, s),
+                "read sizes");
+    if (sizes_event && !sort_sums) HIP_TRY(hipEventRecord(ctx->sizes_ev, s), "hipEventRecord");
+    if (learn) ctx->counts_pending = true;
+    const PartialSums sums = partial_sums(pa);
 
     BinArgs ba{};
     ba.view_counts = view_counts;
@@ -615,7 +620,6 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     ba.skip = try_lists ? counters + kCounterChanged + 1 : nullptr;
     uint64_t* scan_scratch = static_cast<uint64_t*>(w.scan_scratch.p);
     // one view of the same Gaussians as the last render: start from its order
-    const bool reuse = !noalloc && (o.flags & GS_RENDER_REUSE_ORDER) && V == 1 && n > 0 && prev_order_n == n;
     uint32_t* reuse_words = nullptr;
     if (reuse) {
         if ((st = ensure(ctx, w.reuse_words, order_reuse_words(n) * 4)) != GS_OK) return st;
@@ -631,7 +635,8 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
                               static_cast<uint32_t*>(packed ? w.sort_pa.p : nullptr),
                               static_cast<uint32_t*>(packed ? w.sort_pb.p : nullptr),
                               static_cast<uint32_t*>(w.hist.p),
-                              n, V, tu.sort_items, reuse ? reuse_words : ba.skip, s),
+                              n, V, tu.sort_items, reuse ? reuse_words : ba.skip, s,
+                              sort_sums ? &sums : nullptr, sort_sums && sizes_event ? ctx->sizes_ev : nullptr),
             "depth sort");
     if (reuse && packed)
         HIP_TRY(launch_order_pack(static_cast<const uint32_t*>(w.sort_vb.p), pa.rect, n, reuse_words,

@@ -25,6 +25,7 @@
 // Gaussians without a finite depth are 0xFFFFFFFF and sink to the end.
 // Values start as the Gaussian index, so ties in depth stay in index order.
 #include "gs_internal.h"
+#include "partials.h"
 
 #include <algorithm>
 
@@ -36,10 +37,11 @@ namespace {
 // The count buffer holds the digit totals [segment][digit], the offset
 // table [segment][digit][part], then the block histograms [block][digit].
 template <int kItems>
-__device__ __forceinline__ void sort_block_range(int64_t n, int bpv, int64_t* begin, int64_t* end, int64_t* row)
+__device__ __forceinline__ void sort_block_range(unsigned block, int64_t n, int bpv, int64_t* begin, int64_t* end,
+                                                 int64_t* row)
 {
     constexpr int64_t tile = (int64_t)kSortBlock * kItems;
-    const int v = (int)(blockIdx.x / (unsigned)bpv), lb = (int)(blockIdx.x % (unsigned)bpv);
+    const int v = (int)(block / (unsigned)bpv), lb = (int)(block % (unsigned)bpv);
     *begin = (int64_t)v * n + (int64_t)lb * tile;
     const int64_t seg_end = (int64_t)(v + 1) * n;
     *end = (*begin + tile < seg_end) ? *begin + tile : seg_end;
@@ -73,16 +75,22 @@ __device__ __forceinline__ uint64_t same_digit_lanes(uint32_t d, bool valid)
 template <int kItems>
 __global__ __launch_bounds__(kSortBlock) void radix_hist_kernel(const uint32_t* __restrict__ keys, int64_t n,
                                                                  int shift, uint32_t* __restrict__ hist, int bpv,
-                                                                 const uint32_t* skip)
+                                                                 const uint32_t* skip, PartialSums sums)
 {
     if (skip && *skip) return;   // the previous frame's order was reused
+    // the first sums.n_views workgroups sum the projection's partials
+    if ((int)blockIdx.x < sums.n_views) {
+        sum_partials<kSortBlock>(sums, (int)blockIdx.x);
+        return;
+    }
+    const unsigned block = blockIdx.x - (unsigned)sums.n_views;
     __shared__ uint32_t h[4][256];   // one private histogram per wave
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
 #pragma unroll
     for (int w = 0; w < 4; ++w) h[w][tid] = 0;
     __syncthreads();
     int64_t begin, end, row;
-    sort_block_range<kItems>(n, bpv, &begin, &end, &row);
+    sort_block_range<kItems>(block, n, bpv, &begin, &end, &row);
     // every key load issued before any is used (a load under its own branch
     // is waited for before the next one issues); past end, key begin is
     // loaded and dropped
@@ -111,7 +119,7 @@ __global__ __launch_bounds__(kSortBlock) void radix_hist_kernel(const uint32_t* 
     }
     __syncthreads();
     (void)row;   // the histogram goes to the block's own row of 256 counts, not to the offset table
-    hist[(int64_t)blockIdx.x * 256 + tid] = h[0][tid] + h[1][tid] + h[2][tid] + h[3][tid];
+    hist[(int64_t)block * 256 + tid] = h[0][tid] + h[1][tid] + h[2][tid] + h[3][tid];
 }
 
 // Workgroup (v, d): exclusive scan of digit d's counts over the bpv blocks of
@@ -199,7 +207,7 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
     __shared__ uint32_t s_start[256], s_base[256], s_wsum[4], s_ssum[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int64_t begin, end, row;
-    sort_block_range<kBlockItems / kSortBlock>(n, bpv, &begin, &end, &row);
+    sort_block_range<kBlockItems / kSortBlock>(blockIdx.x, n, bpv, &begin, &end, &row);
     for (int i = tid; i < kItems * kWaves * 128; i += kThreads) s_buf[i] = 0u;   // cnt, two counts per word
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     __syncthreads();
@@ -302,13 +310,15 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
 template <int kItems>
 void launch_sort_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const ushort4* rect,
                       const uint32_t* pin, uint32_t* pout, uint32_t* counts, int64_t n, int n_views, int shift,
-                      int bpv, unsigned nblocks, const uint32_t* skip, hipStream_t s)
+                      int bpv, unsigned nblocks, const uint32_t* skip, hipStream_t s, const PartialSums& sums,
+                      hipEvent_t sums_done)
 {
     uint32_t* totals = counts;
     uint32_t* table = counts + (int64_t)256 * n_views;
     uint32_t* hist = table + (int64_t)256 * nblocks;
-    hipLaunchKernelGGL(radix_hist_kernel<kItems>, dim3(nblocks), dim3(kSortBlock), 0, s, kin, n, shift, hist, bpv,
-                       skip);
+    hipLaunchKernelGGL(radix_hist_kernel<kItems>, dim3(nblocks + (unsigned)sums.n_views), dim3(kSortBlock), 0, s, kin,
+                       n, shift, hist, bpv, skip, sums);
+    if (sums_done) (void)hipEventRecord(sums_done, s);
     hipLaunchKernelGGL(radix_row_scan_kernel, dim3(256u * (unsigned)n_views), dim3(256), 0, s, (const uint32_t*)hist,
                        table, totals, bpv, skip);
     // the scatter of a 16-key part runs as 1024 threads of 4 keys: the same
@@ -425,12 +435,16 @@ __global__ __launch_bounds__(kFusedThreads) void radix_segment_kernel(const uint
                                                                       uint32_t* __restrict__ vals_out,
                                                                       const ushort4* __restrict__ rect_in,
                                                                       uint32_t* __restrict__ pay_out, int n,
-                                                                      const uint32_t* skip)
+                                                                      const uint32_t* skip, PartialSums sums)
 {
     if (skip && *skip) return;
+    if ((int)blockIdx.x < sums.n_views) {
+        sum_partials<kFusedThreads>(sums, (int)blockIdx.x);
+        return;
+    }
     __shared__ FusedLds<kItems, kPay> L;
     const int tid = threadIdx.x;
-    const int64_t begin = (int64_t)blockIdx.x * n;
+    const int64_t begin = (int64_t)(blockIdx.x - (unsigned)sums.n_views) * n;
     uint32_t key[kItems], val[kItems], pay[kPay ? kItems : 1];
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
@@ -466,18 +480,23 @@ __global__ __launch_bounds__(kFusedThreads) void radix_segment_kernel(const uint
 // tables of the three passes that follow, which lie behind it.
 __global__ __launch_bounds__(kFusedThreads) void radix_first_hist_kernel(const uint32_t* __restrict__ keys, int64_t n,
                                                                          uint32_t* __restrict__ hist, int bpv,
-                                                                         const uint32_t* skip)
+                                                                         const uint32_t* skip, PartialSums sums)
 {
     if (skip && *skip) return;
+    if ((int)blockIdx.x < sums.n_views) {
+        sum_partials<kFusedThreads>(sums, (int)blockIdx.x);
+        return;
+    }
+    const unsigned block = blockIdx.x - (unsigned)sums.n_views;
     __shared__ uint32_t h[4][256];
     const int tid = threadIdx.x;
     h[tid >> 8][tid & 255] = 0u;
     __syncthreads();
     int64_t begin, end, row;
-    sort_block_range<kFusedThreads / kSortBlock>(n, bpv, &begin, &end, &row);
+    sort_block_range<kFusedThreads / kSortBlock>(block, n, bpv, &begin, &end, &row);
     if (begin + tid < end) atomicAdd(&h[tid >> 8][sort_key(keys[begin + tid]) & 255u], 1u);
     __syncthreads();
-    const int64_t at = (int64_t)blockIdx.x * 256, table = (int64_t)gridDim.x * 256;
+    const int64_t at = (int64_t)block * 256, table = (int64_t)(gridDim.x - (unsigned)sums.n_views) * 256;
     const int t = tid >> 8, d = tid & 255;
     hist[t * table + at + d] = t == 0 ? h[0][d] + h[1][d] + h[2][d] + h[3][d] : 0u;
 }
@@ -498,7 +517,7 @@ __global__ __launch_bounds__(kFusedThreads) void radix_fused_kernel(
     __shared__ uint32_t s_total[4][256], s_before[4][256], s_base[256], s_ssum[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int64_t begin, end, row;
-    sort_block_range<kPart / kSortBlock>(n, bpv, &begin, &end, &row);
+    sort_block_range<kPart / kSortBlock>(blockIdx.x, n, bpv, &begin, &end, &row);
     const int v = (int)(blockIdx.x / (unsigned)bpv), lb = (int)(blockIdx.x % (unsigned)bpv);
     const int count = (int)(end - begin);
     const int64_t ic = tid < count ? begin + tid : begin;
@@ -573,22 +592,25 @@ bool fused_sort(int64_t n, int64_t n_views) { return n * n_views <= kCountedKeys
 
 template <int kItems, bool kPay>
 void launch_segment_sort(const uint32_t* keys_in, uint32_t* vals, const ushort4* rect, uint32_t* pay, int64_t n,
-                         int n_views, const uint32_t* skip, hipStream_t s)
+                         int n_views, const uint32_t* skip, hipStream_t s, const PartialSums& sums,
+                         hipEvent_t sums_done)
 {
-    hipLaunchKernelGGL((radix_segment_kernel<kItems, kPay>), dim3((unsigned)n_views), dim3(kFusedThreads), 0, s,
-                       keys_in, vals, rect, pay, (int)n, skip);
+    hipLaunchKernelGGL((radix_segment_kernel<kItems, kPay>), dim3((unsigned)(n_views + sums.n_views)),
+                       dim3(kFusedThreads), 0, s, keys_in, vals, rect, pay, (int)n, skip, sums);
+    if (sums_done) (void)hipEventRecord(sums_done, s);
 }
 
 template <bool kPay>
 void launch_fused_sort(const uint32_t* keys_in, uint32_t* const (&keys)[2], uint32_t* const (&vals)[2],
                        const ushort4* rect, uint32_t* const (&pay)[2], uint32_t* counts, int64_t n, int n_views,
-                       const uint32_t* skip, hipStream_t s)
+                       const uint32_t* skip, hipStream_t s, const PartialSums& sums, hipEvent_t sums_done)
 {
     const int bpv = (int)((n + kFusedThreads - 1) / kFusedThreads);
     const unsigned blocks = (unsigned)bpv * (unsigned)n_views;
     const int64_t table = (int64_t)blocks * 256;
-    hipLaunchKernelGGL(radix_first_hist_kernel, dim3(blocks), dim3(kFusedThreads), 0, s, keys_in, n, counts,
-                       bpv, skip);
+    hipLaunchKernelGGL(radix_first_hist_kernel, dim3(blocks + (unsigned)sums.n_views), dim3(kFusedThreads), 0, s,
+                       keys_in, n, counts, bpv, skip, sums);
+    if (sums_done) (void)hipEventRecord(sums_done, s);
     for (int pass = 0; pass < 4; ++pass) {
         const int to = pass & 1, from = to ^ 1;
         hipLaunchKernelGGL(radix_fused_kernel<kPay>, dim3(blocks), dim3(kFusedThreads), 0, s,
@@ -832,10 +854,11 @@ constexpr int64_t kWideKeys = 1500000;
 hipError_t launch_depth_sort(const uint32_t* keys_in, uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
                              uint32_t* vals_b, const ushort4* rect, uint32_t* pay_a, uint32_t* pay_b,
                              uint32_t* counts, int64_t n, int n_views, int items, const uint32_t* reuse_words,
-                             hipStream_t s)
+                             hipStream_t s, const PartialSums* sums, hipEvent_t sums_done)
 {
     if (n == 0 || n_views <= 0) return hipSuccess;
-    if (!depth_sort_items_supported(items)) return hipErrorInvalidValue;
+    if (!depth_sort_items_supported(items) || (sums && reuse_words)) return hipErrorInvalidValue;
+    const PartialSums no_sums{};
     if (items == 8 && n * n_views >= kWideKeys) items = 16;
     const int64_t tile = (int64_t)kSortBlock * items;
     const int bpv = (int)((n + tile - 1) / tile);
@@ -851,12 +874,12 @@ hipError_t launch_depth_sort(const uint32_t* keys_in, uint32_t* keys_a, uint32_t
         const auto launch = k == 1   ? (rect ? launch_segment_sort<1, true> : launch_segment_sort<1, false>)
                             : k == 2 ? (rect ? launch_segment_sort<2, true> : launch_segment_sort<2, false>)
                                      : (rect ? launch_segment_sort<4, true> : launch_segment_sort<4, false>);
-        launch(keys_in, vals_b, rect, pay_b, n, n_views, skip, s);
+        launch(keys_in, vals_b, rect, pay_b, n, n_views, skip, s, sums ? *sums : no_sums, sums_done);
         return hipGetLastError();
     }
     if (fused_sort(n, n_views)) {
         (rect ? launch_fused_sort<true> : launch_fused_sort<false>)(keys_in, keys, vals, rect, pay, counts, n, n_views,
-                                                                    skip, s);
+                                                                    skip, s, sums ? *sums : no_sums, sums_done);
         return hipGetLastError();
     }
     for (int pass = 0; pass < 4; ++pass) {
@@ -865,10 +888,12 @@ hipError_t launch_depth_sort(const uint32_t* keys_in, uint32_t* keys_a, uint32_t
         uint32_t* kout = pass == 3 ? nullptr : (to_b ? keys_b : keys_a);
         uint32_t* vout = to_b ? vals_b : vals_a;
         uint32_t* pout = rect ? (to_b ? pay_b : pay_a) : nullptr;
+        const PartialSums& ps = pass == 0 && sums ? *sums : no_sums;
+        const hipEvent_t ev = pass == 0 ? sums_done : nullptr;
         switch (items) {
-        case 4: launch_sort_pass<4>(kin, vin, kout, vout, rect, pin, pout, counts, n, n_views, shift, bpv, nblocks, skip, s); break;
-        case 8: launch_sort_pass<8>(kin, vin, kout, vout, rect, pin, pout, counts, n, n_views, shift, bpv, nblocks, skip, s); break;
-        default: launch_sort_pass<16>(kin, vin, kout, vout, rect, pin, pout, counts, n, n_views, shift, bpv, nblocks, skip, s); break;
+        case 4: launch_sort_pass<4>(kin, vin, kout, vout, rect, pin, pout, counts, n, n_views, shift, bpv, nblocks, skip, s, ps, ev); break;
+        case 8: launch_sort_pass<8>(kin, vin, kout, vout, rect, pin, pout, counts, n, n_views, shift, bpv, nblocks, skip, s, ps, ev); break;
+        default: launch_sort_pass<16>(kin, vin, kout, vout, rect, pin, pout, counts, n, n_views, shift, bpv, nblocks, skip, s, ps, ev); break;
         }
         kin = kout;
         vin = vout;

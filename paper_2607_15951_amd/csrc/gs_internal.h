@@ -124,7 +124,18 @@ struct ProjectArgs {
 
 constexpr int kPartials = 8;
 size_t project_partials_elems(int64_t n, int n_views);
-hipError_t launch_project(const ProjectArgs& a, hipStream_t s);
+// The sums of the projection blocks' partials that give the view counters
+// (partials.h).
+struct PartialSums {
+    const uint32_t* partials;
+    int blocks, n_views;
+    uint32_t* view_counts;
+    uint32_t* counts_out;   // as in ProjectArgs
+    uint32_t* changed;
+};
+PartialSums partial_sums(const ProjectArgs& a);
+// Without sum the counters are left to the depth sort (launch_depth_sort).
+hipError_t launch_project(const ProjectArgs& a, bool sum, hipStream_t s);
 
 // A tile rectangle (x0, y0, x1, y1; exclusive ends) packed in one word,
 // x0 | x1 << 8 | y0 << 16 | y1 << 24, for views at most kPackedRectTiles
@@ -145,13 +156,15 @@ __device__ __forceinline__ ushort4 unpack_rect(uint32_t p)
 // the item index v * n + i).  The sorted values end in vals_b; the sorted
 // keys are not written (nothing reads them).  With rect (else null) each
 // item carries its packed rectangle (pack_rect of rect[item]) through the
-// passes, which ends in pay_b in the sorted order.
+// passes, which ends in pay_b in the sorted order.  With sums (and no
+// reuse_words) the first launch also sums the projection's partials; the
+// event sums_done, if any, is recorded behind it.
 bool depth_sort_items_supported(int items);
 size_t depth_sort_hist_elems(int64_t n, int n_views);   // enough for every supported width
 hipError_t launch_depth_sort(const uint32_t* keys_in, uint32_t* keys_a, uint32_t* vals_a,
                              uint32_t* keys_b, uint32_t* vals_b, const ushort4* rect, uint32_t* pay_a, uint32_t* pay_b,
                              uint32_t* counts, int64_t n, int n_views, int items, const uint32_t* reuse_words,
-                             hipStream_t s);
+                             hipStream_t s, const PartialSums* sums = nullptr, hipEvent_t sums_done = nullptr);
 // Reuse of the previous frame's order (one view, n items): reads the previous
 // order from vals_b and this frame's keys; leaves in vals_b this frame's
 // order when it can reach it cheaply, and in words[kReuseWords]: [0] 1 when

@@ -13,6 +13,7 @@
 // this kernel is bound by HBM reads (up to 236 B per Gaussian), so the double
 // arithmetic costs no frame time.  Colour and opacity are FP32.
 #include "gs_internal.h"
+#include "partials.h"
 #include "tile_order.h"
 
 #include <hip/hip_fp16.h>
@@ -597,57 +598,7 @@ void launch_project_backward_dt(const ProjectBackArgs& a, unsigned blocks, hipSt
 
 }  // namespace
 
-// Per view (one block each): the view counters, summed over the projection
-// blocks' partials.  With changed, also the items whose key or rectangle changed (added over
-// the views; each view's share clamped to 2^32 - 1), clearing the flag that
-// none did when any did.
-__global__ __launch_bounds__(1024) void reduce_partials_kernel(const uint32_t* __restrict__ partials, int blocks,
-                                                               int n_views, uint32_t* view_counts,
-                                                               uint32_t* counts_out, uint32_t* changed)
-{
-    // 64-bit sums: in each thread over a stride of blocks, in each wave by
-    // shuffles, then over the 16 waves in LDS
-    __shared__ unsigned long long s_sum[16][6];
-    const int v = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned long long t[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll 8
-    for (int b = threadIdx.x; b < blocks; b += 1024) {
-        const uint4* pp = reinterpret_cast<const uint4*>(partials + kPartials * ((int64_t)b * n_views + v));
-        const uint4 lo = pp[0];
-        const uint2 hi = *reinterpret_cast<const uint2*>(pp + 1);
-        t[0] += lo.x;
-        t[1] += lo.y;
-        t[2] += lo.z;
-        t[3] += lo.w;
-        t[4] += hi.x;
-        t[5] += hi.y;
-    }
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        for (int o = 32; o > 0; o >>= 1) t[k] += __shfl_xor(t[k], o, 64);
-        if (lane == 0) s_sum[wave][k] = t[k];
-    }
-    __syncthreads();
-    if (threadIdx.x < kViewCounters) {   // one thread per counter
-        // its sum, and whether the counter is that sum's upper half
-        const int k = threadIdx.x, of = k == 0 ? 0 : (k == 1 ? 2 : (k < 4 ? 1 : (k < 6 ? 4 : (k < 8 ? 5 : 3))));
-        unsigned long long sum = 0;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) sum += s_sum[w][of];
-        uint32_t c = (k == 3 || k == 5 || k == 7) ? (uint32_t)(sum >> 32) : (uint32_t)sum;
-        const uint32_t moved = !changed || k != 8 ? 0u : (sum > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)sum);
-        if (k >= 8) c = moved;   // the last counter is spare
-        view_counts[(int64_t)kViewCounters * v + k] = c;
-        // may be pinned host memory, read after an event past the kernel
-        if (counts_out) counts_out[(int64_t)kViewCounters * v + k] = c;
-        if (moved) {
-            // views add their counts; any change clears the flag (all
-            // writers store the same 0)
-            atomicAdd(&changed[0], moved);
-            changed[1] = 0u;
-        }
-    }
-}
+__global__ __launch_bounds__(1024) void reduce_partials_kernel(PartialSums a) { sum_partials<1024>(a, blockIdx.x); }
 
 template <int DT, bool kOneView>
 void launch_project_dt(const ProjectArgs& a, unsigned blocks, hipStream_t s)
@@ -679,7 +630,12 @@ hipError_t launch_project_backward(const ProjectBackArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_project(const ProjectArgs& a, hipStream_t s)
+PartialSums partial_sums(const ProjectArgs& a)
+{
+    return PartialSums{a.partials, (int)((a.n + 255) / 256), a.n_views, a.view_counts, a.counts_out, a.changed};
+}
+
+hipError_t launch_project(const ProjectArgs& a, bool sum, hipStream_t s)
 {
     if (a.n_views <= 0) return hipSuccess;
     if (a.n == 0) return launch_fill_u32(a.view_counts, 0u, (int64_t)kViewCounters * a.n_views, s);
@@ -690,8 +646,8 @@ hipError_t launch_project(const ProjectArgs& a, hipStream_t s)
     case 1: launch_project_views<1>(a, grid, s); break;
     default: launch_project_views<2>(a, grid, s); break;
     }
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)a.n_views), dim3(1024), 0, s,
-                       (const uint32_t*)a.partials, (int)blocks, a.n_views, a.view_counts, a.counts_out, a.changed);
+    if (sum)
+        hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)a.n_views), dim3(1024), 0, s, partial_sums(a));
     return hipGetLastError();
 }
 
