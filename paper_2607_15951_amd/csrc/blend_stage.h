@@ -1,5 +1,5 @@
 // blend_stage.h -- staging of one list entry for the per-tile blend, shared
-// by the forward (blend.hip) and backward (backward.hip) kernels so that both
+// by the forward (blend.hip) and backward (blend_backward.hip) kernels so that both
 // see the same per-entry values and take the same inclusion decisions.
 #pragma once
 
