@@ -405,7 +405,7 @@ gs_status gs_get_list_reuse(gs_context* ctx, uint32_t* out2);
  * dealt to the XCDs, change only speed.  Every supported value gives the same
  * image, final T, n_contrib, lists and projection, bit for bit.
  *   sort_items        keys per thread of a depth-sort block: 4, 8 or 16
- *                     (from 1.5M keys on 8 stands for 16; up to 98304 keys
+ *                     (from 800000 keys on 8 stands for 16; up to 98304 keys
  *                     the sort takes shapes of its own)
  *   bin_row_items     scale of the depth-sorted Gaussians per lane of a
  *                     binning wavefront (and of the row lists of

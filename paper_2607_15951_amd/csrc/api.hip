@@ -586,6 +586,8 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     // copy to the host).
     const bool reuse = !noalloc && (o.flags & GS_RENDER_REUSE_ORDER) && V == 1 && n > 0 && prev_order_n == n;
     const bool sort_sums = n > 0 && n <= 1000000 && !try_lists && !reuse && !(eager && !ctx->host_info_dev);
+    pa.clear = static_cast<uint32_t*>(w.hist.p);
+    pa.clear_words = (int64_t)depth_sort_clear_words(n, V, tu.sort_items);
     HIP_TRY(launch_project(pa, !sort_sums, s), "project");
     STAGE_MARK(1);
     ctx->lists_compared = try_lists;

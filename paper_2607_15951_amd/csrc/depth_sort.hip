@@ -12,15 +12,15 @@
 // Several views are sorted at once as segments of one array (one segment per
 // view, items v * n + i); no block straddles two segments.
 //
-// Each 8-bit pass is reduce-then-scan in three launches: an LDS histogram
-// per block, written as the block's 256 contiguous counts (whole cache
-// lines; a digit-major table would take 256 scattered partial-line writes
-// per block); one workgroup per (segment, digit) that gathers its digit's
-// counts over the blocks, scans them into the digit-major
-// [segment][digit][block] offset table and records the digit's total; and a
-// stable scatter that ranks equal digits with wavefront ballots (lower lanes
-// and earlier waves first) and places digit d of segment v at v * n +
-// (totals of the smaller digits) + (its row's exclusive prefix).  Digits are taken from sort_key(key), which orders
+// Each 8-bit pass is an LDS histogram per block, written as the block's 256
+// contiguous counts (whole cache lines; a digit-major table would take 256
+// scattered partial-line writes per block), and a stable scatter that ranks
+// equal digits with wavefront ballots (lower lanes and earlier waves first) and
+// places digit d of segment v at v * n + (the segment's items of smaller
+// digits) + (d's items in the blocks before).  Those come from group sums that
+// the histograms add to (32 blocks of a segment) and the block's own group's
+// counts; for many keys from a launch between the two, one workgroup per
+// (segment, digit) that scans its digit's counts over the blocks.  Digits are taken from sort_key(key), which orders
 // depths as numbers (negative ones, behind the camera, first); keys of
 // Gaussians without a finite depth are 0xFFFFFFFF and sink to the end.
 // Values start as the Gaussian index, so ties in depth stay in index order.
@@ -28,24 +28,35 @@
 #include "partials.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace gsmi {
 namespace {
 
 // Block b sorts part lb = b % bpv of segment v = b / bpv: items
 // [v * n + lb * tile, min(.. + tile, (v + 1) * n)), tile = kSortBlock * kItems.
-// The count buffer holds the digit totals [segment][digit], the offset
-// table [segment][digit][part], then the block histograms [block][digit].
+// The count buffer holds two tables of group sums [segment][group][digit]
+// (passes use them in turn), then the block histograms [block][digit]; or the
+// digit totals [segment][digit], the offset table [segment][digit][part], then
+// the block histograms.
 template <int kItems>
-__device__ __forceinline__ void sort_block_range(unsigned block, int64_t n, int bpv, int64_t* begin, int64_t* end,
-                                                 int64_t* row)
+__device__ __forceinline__ void sort_block_range(unsigned block, int64_t n, int bpv, int64_t* begin, int64_t* end)
 {
     constexpr int64_t tile = (int64_t)kSortBlock * kItems;
     const int v = (int)(block / (unsigned)bpv), lb = (int)(block % (unsigned)bpv);
     *begin = (int64_t)v * n + (int64_t)lb * tile;
     const int64_t seg_end = (int64_t)(v + 1) * n;
     *end = (*begin + tile < seg_end) ? *begin + tile : seg_end;
-    *row = (int64_t)v * 256 * bpv + lb;   // table index of digit 0; digit d adds d * bpv
+}
+
+// Consecutive parts of a segment whose counts are also kept as one sum: a
+// block then finds where its digits go from the sums of its segment's groups
+// and the counts of its own group's parts (51 rows of 1 KB at 2.5M keys).
+constexpr int kGroupParts = 32;
+__host__ __device__ __forceinline__ int sort_groups(int bpv) { return (bpv + kGroupParts - 1) / kGroupParts; }
+__device__ __forceinline__ int sort_group(unsigned block, int bpv)
+{
+    return (int)(block / (unsigned)bpv) * sort_groups(bpv) + (int)(block % (unsigned)bpv) / kGroupParts;
 }
 
 // Order-preserving map of a depth key to the sort key: float bits compare as
@@ -74,7 +85,8 @@ __device__ __forceinline__ uint64_t same_digit_lanes(uint32_t d, bool valid)
 
 template <int kItems>
 __global__ __launch_bounds__(kSortBlock) void radix_hist_kernel(const uint32_t* __restrict__ keys, int64_t n,
-                                                                 int shift, uint32_t* __restrict__ hist, int bpv,
+                                                                 int shift, uint32_t* __restrict__ hist,
+                                                                 uint32_t* __restrict__ groups, int bpv,
                                                                  const uint32_t* skip, PartialSums sums)
 {
     if (skip && *skip) return;   // the previous frame's order was reused
@@ -89,8 +101,8 @@ __global__ __launch_bounds__(kSortBlock) void radix_hist_kernel(const uint32_t* 
 #pragma unroll
     for (int w = 0; w < 4; ++w) h[w][tid] = 0;
     __syncthreads();
-    int64_t begin, end, row;
-    sort_block_range<kItems>(block, n, bpv, &begin, &end, &row);
+    int64_t begin, end;
+    sort_block_range<kItems>(block, n, bpv, &begin, &end);
     // every key load issued before any is used (a load under its own branch
     // is waited for before the next one issues); past end, key begin is
     // loaded and dropped
@@ -118,8 +130,9 @@ __global__ __launch_bounds__(kSortBlock) void radix_hist_kernel(const uint32_t* 
         }
     }
     __syncthreads();
-    (void)row;   // the histogram goes to the block's own row of 256 counts, not to the offset table
-    hist[(int64_t)block * 256 + tid] = h[0][tid] + h[1][tid] + h[2][tid] + h[3][tid];
+    const uint32_t count = h[0][tid] + h[1][tid] + h[2][tid] + h[3][tid];
+    hist[(int64_t)block * 256 + tid] = count;
+    if (groups && count) atomicAdd(&groups[(int64_t)sort_group(block, bpv) * 256 + tid], count);
 }
 
 // Workgroup (v, d): exclusive scan of digit d's counts over the bpv blocks of
@@ -186,14 +199,16 @@ __global__ __launch_bounds__(256) void radix_row_scan_kernel(const uint32_t* __r
 // the first pass (pay_in null) packed from rect_in, and written to pay_out
 // beside its value.  keys_out may be null (the last pass: the sorted keys
 // are not needed).
-template <int kItems, bool kPay, int kThreads = kSortBlock>
+template <int kItems, bool kPay, bool kGrouped, int kThreads = kSortBlock>
 __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
     const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in, uint32_t* __restrict__ keys_out,
     uint32_t* __restrict__ vals_out, const ushort4* __restrict__ rect_in, const uint32_t* __restrict__ pay_in,
-    uint32_t* __restrict__ pay_out, int64_t n, int shift, const uint32_t* __restrict__ offsets,
+    uint32_t* __restrict__ pay_out, int64_t n, int shift, const uint32_t* __restrict__ hist,
+    const uint32_t* __restrict__ groups, uint32_t* __restrict__ next_groups, const uint32_t* __restrict__ offsets,
     const uint32_t* __restrict__ totals, int bpv, const uint32_t* skip)
 {
     constexpr int kWaves = kThreads / 64;
+    constexpr int kParts = kThreads / 256;   // threads that share a digit's rows
     constexpr int kBlockItems = kItems * kThreads;   // = kSortBlock * (kBlockItems / kSortBlock): the block's part
     static_assert(kThreads % kSortBlock == 0, "whole 256-thread groups");
     if (skip && *skip) return;
@@ -205,9 +220,10 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
     static_assert(kItems * kWaves * 256 * sizeof(uint16_t) <= sizeof(s_buf), "ranking counts fit the key buffer");
     static_assert(kBlockItems <= 65535, "16-bit ranking offsets");
     __shared__ uint32_t s_start[256], s_base[256], s_wsum[4], s_ssum[4];
+    __shared__ uint32_t s_total[kGrouped ? kParts : 1][256], s_before[kGrouped ? kParts : 1][256];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int64_t begin, end, row;
-    sort_block_range<kBlockItems / kSortBlock>(blockIdx.x, n, bpv, &begin, &end, &row);
+    int64_t begin, end;
+    sort_block_range<kBlockItems / kSortBlock>(blockIdx.x, n, bpv, &begin, &end);
     for (int i = tid; i < kItems * kWaves * 128; i += kThreads) s_buf[i] = 0u;   // cnt, two counts per word
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     __syncthreads();
@@ -222,6 +238,29 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
         val[k] = vals_in ? vals_in[ic] : (uint32_t)idx;
         if constexpr (kPay) pay[k] = pay_in ? pay_in[ic] : pack_rect(rect_in[ic]);
     }
+    // digit d's count in the segment and in the parts before this one
+    const int v = (int)(blockIdx.x / (unsigned)bpv), lb = (int)(blockIdx.x % (unsigned)bpv);
+    if constexpr (kGrouped) {
+        const int q = tid >> 8, d = tid & 255, ng = sort_groups(bpv), own = lb / kGroupParts;
+        const uint32_t* g = groups + (int64_t)v * ng * 256 + d;
+        uint32_t total = 0u, before = 0u;
+#pragma unroll 4
+        for (int i = q; i < ng; i += kParts) {
+            const uint32_t c = g[i * 256];
+            total += c;
+            before += i < own ? c : 0u;
+        }
+        const uint32_t* h = hist + ((int64_t)v * bpv + own * kGroupParts) * 256 + d;
+#pragma unroll 4
+        for (int i = q; i < lb - own * kGroupParts; i += kParts) before += h[i * 256];
+        s_total[q][d] = total;
+        s_before[q][d] = before;
+    }
+    // the next pass's group sums start at zero
+    if (kGrouped && next_groups)
+        for (int64_t i = (int64_t)blockIdx.x * kThreads + tid; i < (int64_t)(gridDim.x / bpv) * sort_groups(bpv) * 256;
+             i += (int64_t)gridDim.x * kThreads)
+            next_groups[i] = 0u;
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
         const int64_t idx = begin + k * kThreads + tid;
@@ -238,7 +277,6 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
     // threads d < 256: exclusive offsets of digit d over (round, wave), its
     // total, and the block's digit start (exclusive prefix of the totals);
     // then the segment's start of digit d (exclusive prefix of its totals)
-    const int v = (int)(blockIdx.x / (unsigned)bpv);
     uint32_t run = 0u, seg_total = 0u, incl = 0u, seg_incl = 0u;
     if (tid < 256) {
 #pragma unroll
@@ -249,7 +287,13 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
                 cnt[k][w][tid] = (uint16_t)run;
                 run += c;
             }
-        seg_total = totals[v * 256 + tid];   // the segment's count of digit d
+        // the segment's count of digit d
+        if constexpr (kGrouped) {
+#pragma unroll
+            for (int q = 0; q < kParts; ++q) seg_total += s_total[q][tid];
+        } else {
+            seg_total = totals[v * 256 + tid];
+        }
         incl = run;
         seg_incl = seg_total;
 #pragma unroll
@@ -273,7 +317,13 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
             seg_before += s_ssum[w];
         }
         s_start[tid] = before + incl - run;
-        s_base[tid] = seg_before + seg_incl - seg_total + offsets[row + (int64_t)tid * bpv];
+        if constexpr (kGrouped) {
+#pragma unroll
+            for (int q = 0; q < kParts; ++q) seg_before += s_before[q][tid];
+        } else {
+            seg_before += offsets[((int64_t)v * 256 + tid) * bpv + lb];
+        }
+        s_base[tid] = seg_before + seg_incl - seg_total;
     }
     __syncthreads();
     uint32_t local[kItems];
@@ -304,37 +354,39 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
     }
 }
 
-// One 8-bit pass: histogram, row scans, scatter.  counts = totals
-// [n_views][256], the offset table [n_views][256][bpv], the block
-// histograms [nblocks][256].
-template <int kItems>
+// One 8-bit pass: histogram, for many keys a scan of the counts, scatter.
+template <int kItems, bool kGrouped>
 void launch_sort_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, const ushort4* rect,
                       const uint32_t* pin, uint32_t* pout, uint32_t* counts, int64_t n, int n_views, int shift,
                       int bpv, unsigned nblocks, const uint32_t* skip, hipStream_t s, const PartialSums& sums,
                       hipEvent_t sums_done)
 {
-    uint32_t* totals = counts;
-    uint32_t* table = counts + (int64_t)256 * n_views;
-    uint32_t* hist = table + (int64_t)256 * nblocks;
+    const int pass = shift / 8;
+    const int64_t table = (int64_t)n_views * sort_groups(bpv) * 256;
+    uint32_t* groups = kGrouped ? counts + (pass & 1) * table : nullptr;
+    uint32_t* next = kGrouped && pass < 3 ? counts + ((pass + 1) & 1) * table : nullptr;
+    uint32_t* totals = kGrouped ? nullptr : counts;
+    uint32_t* offsets = kGrouped ? nullptr : counts + (int64_t)256 * n_views;
+    uint32_t* hist = kGrouped ? counts + 2 * table : offsets + (int64_t)256 * nblocks;
     hipLaunchKernelGGL(radix_hist_kernel<kItems>, dim3(nblocks + (unsigned)sums.n_views), dim3(kSortBlock), 0, s, kin,
-                       n, shift, hist, bpv, skip, sums);
+                       n, shift, hist, groups, bpv, skip, sums);
     if (sums_done) (void)hipEventRecord(sums_done, s);
-    hipLaunchKernelGGL(radix_row_scan_kernel, dim3(256u * (unsigned)n_views), dim3(256), 0, s, (const uint32_t*)hist,
-                       table, totals, bpv, skip);
+    if (!kGrouped)
+        hipLaunchKernelGGL(radix_row_scan_kernel, dim3(256u * (unsigned)n_views), dim3(256), 0, s,
+                           (const uint32_t*)hist, offsets, totals, bpv, skip);
     // the scatter of a 16-key part runs as 1024 threads of 4 keys: the same
     // part, ranked by 16 waves of 4 rounds instead of 4 waves of 16 (0.161
     // against 0.165 ms for the four passes at 3M keys; parts of 8192 keys,
     // one 100 KB block per CU, took 0.20 ms)
     constexpr int kThreads = kItems == 16 ? 1024 : kSortBlock;
     constexpr int kPer = kItems * kSortBlock / kThreads;
-    if (pout)
-        hipLaunchKernelGGL((radix_scatter_kernel<kPer, true, kThreads>), dim3(nblocks), dim3(kThreads), 0, s, kin, vin,
-                           kout, vout, rect, pin, pout, n, shift, (const uint32_t*)table, (const uint32_t*)totals, bpv,
-                           skip);
-    else
-        hipLaunchKernelGGL((radix_scatter_kernel<kPer, false, kThreads>), dim3(nblocks), dim3(kThreads), 0, s, kin,
-                           vin, kout, vout, rect, pin, pout, n, shift, (const uint32_t*)table, (const uint32_t*)totals,
-                           bpv, skip);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kThreads), 0, s, kin, vin, kout, vout, rect, pin, pout, n,
+                           shift, (const uint32_t*)hist, (const uint32_t*)groups, next, (const uint32_t*)offsets,
+                           (const uint32_t*)totals, bpv, skip);
+    };
+    if (pout) go(radix_scatter_kernel<kPer, true, kGrouped, kThreads>);
+    else go(radix_scatter_kernel<kPer, false, kGrouped, kThreads>);
 }
 
 // ------------------------------------------------------- few keys
@@ -492,8 +544,8 @@ __global__ __launch_bounds__(kFusedThreads) void radix_first_hist_kernel(const u
     const int tid = threadIdx.x;
     h[tid >> 8][tid & 255] = 0u;
     __syncthreads();
-    int64_t begin, end, row;
-    sort_block_range<kFusedThreads / kSortBlock>(block, n, bpv, &begin, &end, &row);
+    int64_t begin, end;
+    sort_block_range<kFusedThreads / kSortBlock>(block, n, bpv, &begin, &end);
     if (begin + tid < end) atomicAdd(&h[tid >> 8][sort_key(keys[begin + tid]) & 255u], 1u);
     __syncthreads();
     const int64_t at = (int64_t)block * 256, table = (int64_t)(gridDim.x - (unsigned)sums.n_views) * 256;
@@ -516,8 +568,8 @@ __global__ __launch_bounds__(kFusedThreads) void radix_fused_kernel(
     __shared__ FusedLds<1, kPay> L;
     __shared__ uint32_t s_total[4][256], s_before[4][256], s_base[256], s_ssum[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int64_t begin, end, row;
-    sort_block_range<kPart / kSortBlock>(blockIdx.x, n, bpv, &begin, &end, &row);
+    int64_t begin, end;
+    sort_block_range<kPart / kSortBlock>(blockIdx.x, n, bpv, &begin, &end);
     const int v = (int)(blockIdx.x / (unsigned)bpv), lb = (int)(blockIdx.x % (unsigned)bpv);
     const int count = (int)(end - begin);
     const int64_t ic = tid < count ? begin + tid : begin;
@@ -801,9 +853,20 @@ bool depth_sort_items_supported(int items) { return items == 4 || items == 8 || 
 
 size_t order_reuse_words(int64_t n) { return (size_t)(kReuseWords + (n + 255) / 256); }
 
+// From here on 8 keys per thread, the default, stand for 16: a digit's runs
+// are twice as long.  Four passes of 8 and of 16: 74 and 75 us at 500K keys, 89
+// and 82 at 1M, 100 and 97 at 1.2M, 180 and 165 at 3M, 699 and 588 at 16M.
+constexpr int64_t kWideKeys = 800000;
+// Up to here a pass goes without a launch that scans the counts: group sums
+// take their place.  Four passes with the scan and with the group sums: 91 and
+// 82 us at 1M keys, 123 and 114 at 2M, 170 and 170 at 3M, 268 and 278 at 6M, 610
+// and 615 at 16M; and four launches less when the lists of the last frame hold
+// (4.4 us each).
+constexpr int64_t kGroupedKeys = 2500000;
+
 size_t depth_sort_hist_elems(int64_t n, int n_views)
 {
-    // digit totals, then the offset table and the block histograms, both
+    // the block histograms, and the group sums in less than as much again,
     // sized for the smallest block (the most blocks) any supported width uses
     const int64_t tile = (int64_t)kSortBlock * 4;
     const int64_t bpv = (n + tile - 1) / tile;
@@ -812,6 +875,16 @@ size_t depth_sort_hist_elems(int64_t n, int n_views)
     const size_t passes = (size_t)(256 * (V + 2 * (nb > 0 ? nb : 1)));
     // few keys: one table per pass
     return fused_sort(n, V) ? std::max(passes, (size_t)(4 * 256 * V * ((n + kFusedThreads - 1) / kFusedThreads))) : passes;
+}
+
+// Items per thread that a sort of that many keys takes.
+static int sort_width(int64_t keys, int items) { return items == 8 && keys >= kWideKeys ? 16 : items; }
+
+size_t depth_sort_clear_words(int64_t n, int n_views, int items)
+{
+    if (n == 0 || segment_items(n) || fused_sort(n, n_views) || n * n_views > kGroupedKeys) return 0;
+    const int64_t tile = (int64_t)kSortBlock * sort_width(n * n_views, items);
+    return (size_t)(256 * n_views) * (size_t)sort_groups((int)((n + tile - 1) / tile));
 }
 
 hipError_t launch_order_reuse(const uint32_t* keys, uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
@@ -840,11 +913,6 @@ hipError_t launch_order_reuse(const uint32_t* keys, uint32_t* keys_a, uint32_t* 
     return hipGetLastError();
 }
 
-// From here on 8 keys per thread, the default, stand for 16: a digit's runs
-// are twice as long.  Four passes of 8 and of 16: 104 and 108 us at 1.2M keys,
-// 130 and 118 at 2M, 180 and 165 at 3M, 699 and 588 at 16M.
-constexpr int64_t kWideKeys = 1500000;
-
 // Sorts each of the n_views segments keys_in[v * n .. (v + 1) * n) (not
 // modified) with values v * n + i, items keys per thread of a block.  Four
 // passes: in -> a -> b -> a -> b, so the sorted values (and payloads) end in
@@ -859,7 +927,7 @@ hipError_t launch_depth_sort(const uint32_t* keys_in, uint32_t* keys_a, uint32_t
     if (n == 0 || n_views <= 0) return hipSuccess;
     if (!depth_sort_items_supported(items) || (sums && reuse_words)) return hipErrorInvalidValue;
     const PartialSums no_sums{};
-    if (items == 8 && n * n_views >= kWideKeys) items = 16;
+    items = sort_width(n * n_views, items);
     const int64_t tile = (int64_t)kSortBlock * items;
     const int bpv = (int)((n + tile - 1) / tile);
     const unsigned nblocks = (unsigned)bpv * (unsigned)n_views;
@@ -890,10 +958,18 @@ hipError_t launch_depth_sort(const uint32_t* keys_in, uint32_t* keys_a, uint32_t
         uint32_t* pout = rect ? (to_b ? pay_b : pay_a) : nullptr;
         const PartialSums& ps = pass == 0 && sums ? *sums : no_sums;
         const hipEvent_t ev = pass == 0 ? sums_done : nullptr;
+        const auto pass_of = [&](auto W, auto G) {
+            launch_sort_pass<decltype(W)::value, decltype(G)::value>(kin, vin, kout, vout, rect, pin, pout, counts, n,
+                                                                     n_views, shift, bpv, nblocks, skip, s, ps, ev);
+        };
+        const auto grouped = [&](auto W) {
+            if (n * n_views <= kGroupedKeys) pass_of(W, std::true_type{});
+            else pass_of(W, std::false_type{});
+        };
         switch (items) {
-        case 4: launch_sort_pass<4>(kin, vin, kout, vout, rect, pin, pout, counts, n, n_views, shift, bpv, nblocks, skip, s, ps, ev); break;
-        case 8: launch_sort_pass<8>(kin, vin, kout, vout, rect, pin, pout, counts, n, n_views, shift, bpv, nblocks, skip, s, ps, ev); break;
-        default: launch_sort_pass<16>(kin, vin, kout, vout, rect, pin, pout, counts, n, n_views, shift, bpv, nblocks, skip, s, ps, ev); break;
+        case 4: grouped(std::integral_constant<int, 4>{}); break;
+        case 8: grouped(std::integral_constant<int, 8>{}); break;
+        default: grouped(std::integral_constant<int, 16>{}); break;
         }
         kin = kout;
         vin = vout;

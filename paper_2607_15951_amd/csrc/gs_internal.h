@@ -106,6 +106,8 @@ struct ProjectArgs {
     // when not null, a second copy of view_counts: pinned host memory or a
     // buffer of the caller's, complete when the launch's kernels are
     uint32_t* counts_out;
+    uint32_t* clear;              // clear_words words to set to zero for a later launch, or null
+    int64_t clear_words;
     uint32_t* partials;           // [blocks][n_views][kPartials] per-block counts: on screen, pairs, keyed,
                                   // changed, row entries, bin entries
     // when order is not null, one extra workgroup of the launch writes the
@@ -161,6 +163,7 @@ __device__ __forceinline__ ushort4 unpack_rect(uint32_t p)
 // event sums_done, if any, is recorded behind it.
 bool depth_sort_items_supported(int items);
 size_t depth_sort_hist_elems(int64_t n, int n_views);   // enough for every supported width
+size_t depth_sort_clear_words(int64_t n, int n_views, int items);   // first words of counts that have to be zero
 hipError_t launch_depth_sort(const uint32_t* keys_in, uint32_t* keys_a, uint32_t* vals_a,
                              uint32_t* keys_b, uint32_t* vals_b, const ushort4* rect, uint32_t* pay_a, uint32_t* pay_b,
                              uint32_t* counts, int64_t n, int n_views, int items, const uint32_t* reuse_words,

@@ -194,6 +194,8 @@ template <int DT, int DEG, bool kOneView>
 __global__ __launch_bounds__(256) void project_kernel(ProjectArgs a)
 {
     constexpr int ncoef = (DEG + 1) * (DEG + 1);
+    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < a.clear_words; k += (int64_t)gridDim.x * 256)
+        a.clear[k] = 0u;
     // the blend's dispatch order, when asked for, is workgroup 0's work: it
     // needs only the previous frame's per-tile costs, so it runs beside the
     // projection; the Gaussians go to workgroups 1 and up

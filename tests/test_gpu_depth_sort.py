@@ -1,7 +1,7 @@
 """The depth order at the edges of the sort's shapes: one launch (up to 4096
 keys a view, in steps of 1024), five launches (up to 98304 keys over all
-views), three per pass, and the wide parts from 1.5M keys on; packed
-rectangles and grids wider than 255 tiles; depths that are mostly distinct, in
+views), two per pass up to 2.5M keys and three beyond, with the wide parts from
+800000 on; packed rectangles and grids wider than 255 tiles; depths that are mostly distinct, in
 a few values (stable ties), and of Gaussians behind the camera.  The order
 must be the stable sort of the keys by depth, then index: the lists of one
 large tile hold every visible Gaussian in that order."""
@@ -21,7 +21,8 @@ def order_of(lists, t):
 @pytest.mark.parametrize("views,n,width,items", [
     (1, 1, 32, 8), (1, 1023, 32, 8), (1, 1025, 32, 4), (2, 2049, 32, 8), (1, 4096, 4112, 8), (3, 4097, 32, 16),
     (1, 20000, 4112, 8), (1, 98304, 32, 8), (1, 98305, 32, 8), (3, 40000, 32, 4), (1, 600001, 32, 4),
-    (1, 600001, 32, 8), (1, 600001, 32, 16), (1, 1500001, 32, 8),
+    (1, 600001, 32, 8), (1, 600001, 32, 16), (2, 400001, 32, 8), (1, 2500000, 32, 8), (1, 2500001, 32, 8),
+    (1, 2500001, 32, 4),
 ])
 def test_depth_order(views, n, width, items):
     torch = pytest.importorskip("torch")
