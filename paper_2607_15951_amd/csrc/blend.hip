@@ -82,13 +82,14 @@ struct BlendLds {
 // once every thread has returned.
 //
 // kFew: the form for grids of few tiles, where a SIMD has one wave or two and
-// a wave waits for each entry's LDS reads, masks and branches.  Four entries
+// a wave waits for each entry's LDS reads, masks and branches.  Eight entries
 // at a time are read and their alphas computed together, and a pixel's state
 // holds its termination (Tr = 0, the kept transmittance in Tf), so that
 // compositing an entry is a chain of vector selects without scalar masks: 33
-// vector instructions an entry, not 27, but about 140 cycles, not 260.  At 273
-// tiles (40K Gaussians, 333x197) 123 us, 146 in the plain form; at 240 tiles
-// (20K, 317x179) 80 and 97; at 64 tiles (1000, 128x128) 16 and 20.
+// vector instructions an entry, not 27, but about 130 cycles, not 260.  At 273
+// tiles (40K Gaussians, 333x197) 109 us, 146 in the plain form (118 by groups of
+// four, 108 of twelve, which takes 30% more at 2560 tiles); at 240 tiles (20K,
+// 317x179) 71 and 97; at 64 tiles (1000, 128x128) 15 and 20.
 template <bool kStats, int kBatch, bool kFew = false>
 __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, int tile, BlendLds<kBatch>& L)
 {
@@ -232,7 +233,7 @@ __device__ __forceinline__ void blend_tile_walk(const BlendArgs& a, int tile, Bl
             tc.fill(L.pick, b0 + 3 * kBatch, wave, lane);
         }
         if constexpr (kFew) {
-            constexpr int kGroup = 4;
+            constexpr int kGroup = 8;
             for (int q = 0; q < nk; q += 64) {
                 const int jj = q + lane;
                 uint64_t bits = __builtin_amdgcn_ballot_w64(jj < nk && ((s_mask[jj] >> wave) & 1u));
@@ -369,13 +370,13 @@ blend_kernel(BlendArgs a)
     blend_tile_walk<kStats, kBatch>(a, blend_tile(a.order, a.group), lds);
 }
 
-// The form for grids of few tiles.  The line: plain and few, 131 and 114 us at
-// 2560 tiles (300K, 1024x640), 186 and 169 (500K), 105 and 107 at 3600 (500K,
-// 1280x720), 151 and 145 (1M), 129 and 154 at 5700 (1M, 1600x900), 214 and 253
-// at 8160 (1M, 1920x1080): more tiles fill the SIMDs, and the plain form's
-// fewer instructions count.
+// The form for grids of few tiles.  The line: plain and few, 131 and 110 us at
+// 2560 tiles (300K, 1024x640), 186 and 147 (500K); by groups of four, 105 and
+// 107 at 3600 (500K, 1280x720), 151 and 145 (1M), 129 and 154 at 5700 (1M,
+// 1600x900), 214 and 253 at 8160 (1M, 1920x1080): more tiles fill the SIMDs, and
+// the plain form's fewer instructions count.
 constexpr int64_t kFewTiles = 3072;
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void blend_few_kernel(BlendArgs a)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void blend_few_kernel(BlendArgs a)
 {
     __shared__ BlendLds<256> lds;
     blend_tile_walk<false, 256, true>(a, blend_tile(a.order, a.group), lds);

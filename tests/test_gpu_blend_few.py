@@ -1,6 +1,6 @@
-"""Grids of few tiles are blended by a kernel that composites four entries at a
+"""Grids of few tiles are blended by a kernel that composites eight entries at a
 time with vector selects; the kernel that counts its work keeps the plain
-loop.  Both must give the same bits: list lengths around the groups of four
+loop.  Both must give the same bits: list lengths around the groups of eight
 and the batches of 256, faint and opaque splats (early termination inside a
 group), cut tiles, and colours that are infinite or NaN, which reach only the
 pixels that composite their splat."""
@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("W,H,n,logit,odd", [
     (16, 16, 1, -1.0, False), (16, 16, 3, -1.0, False), (17, 33, 4, 2.0, False), (40, 24, 5, -3.0, True),
+    (24, 16, 8, -1.0, False), (24, 16, 9, 3.0, True),
     (40, 24, 257, -4.0, False), (40, 24, 600, 6.0, False), (40, 24, 600, -4.5, True), (200, 120, 5000, 0.0, True),
     (880, 880, 20000, 0.0, False),    # 3025 tiles
     (896, 896, 20000, 0.0, False),    # 3136: past the line
