@@ -68,7 +68,7 @@ struct Workspace {
     DevBuf bin_table, bin_items, bin_spans, partials, sorted_rect, readback;
     DevBuf views;                // device view table
     DevBuf view_counts;          // [n_views][kViewCounters]
-    DevBuf counters;             // [1] capacity overflow flag
+    DevBuf counters;             // [kCounterWords]: [1] capacity overflow flag
     DevBuf tile_work;   // per-tile blend trace [T][kTileWorkFields] u64 (GS_PROFILE_BLEND_WORK)
     DevBuf reuse_words;       // [kReuseWords] outcome of an order-reuse attempt
     // per-tile blend work of the last render, and the blend's dispatch order
@@ -122,6 +122,8 @@ struct gs_context {
     int64_t lists_n = -1;
     std::vector<int> lists_sizes, lists_shifts;
     uint64_t lists_cap = 0;
+    int lists_chunk = 0, lists_chunks1 = 0;   // chunks their offset table is laid out by (BinShape)
+    uint32_t lists_layout = 0;   // id of that layout: another one when any of these changes
     // bin edges (log2 tiles) for the next render of bins_n Gaussians in views of
     // bins_sizes, and whether the counters they come from are still under way
     // to host_info (marked by sizes_ev)
@@ -259,10 +261,17 @@ constexpr int kViewsPerLaunch = 16;
 // counters[kCounterChanged]: the projection's count of (view, Gaussian)
 // items whose depth key or rectangle differ from the last render's (list
 // reuse), and after it the flag that none did: set to 1 at frame set-up when
-// the comparison runs, cleared by any view that finds a change
+// the comparison runs and the lists are laid out as this render reads them,
+// cleared by any view that finds a change
 constexpr int kCounterChanged = 2;
 // counters[kCounterBlendQueue]: head of the blend's work queue (blend_group -1)
 constexpr int kCounterBlendQueue = 4;
+constexpr int kFrameCounters = 16;   // words cleared at frame set-up
+// counters[kCounterLayout], kept between frames: the layout id
+// (gs_context::lists_layout) of the lists in the workspace.  It is compared
+// on the device: a captured render is replayed after whatever ran last.
+constexpr int kCounterLayout = kFrameCounters;
+constexpr int kCounterWords = kFrameCounters + 1;
 
 struct ViewBatch {
     ViewParams v[kViewsPerLaunch];
@@ -277,13 +286,19 @@ __global__ void write_views_kernel(ViewBatch b, int count, ViewParams* dst)
     for (int k = threadIdx.x; k < words; k += blockDim.x) out[k] = src[k];
 }
 
-// The start of a frame of at most kViewsPerLaunch views in one launch: the
-// overflow counters cleared and the view table written (when `write`) from
-// the views in the arguments.
+// The start of a frame: the counters cleared and (when `write`, at most
+// kViewsPerLaunch views) the view table written from the views in the
+// arguments.  hold: the kept lists may be this render's, if their layout is
+// the one with that id.
 __global__ void frame_setup_kernel(ViewBatch b, int count, ViewParams* dst, int write, uint32_t* counters,
-                                   uint32_t hold_init)
+                                   uint32_t hold, uint32_t layout)
 {
-    if (threadIdx.x < 16) counters[threadIdx.x] = threadIdx.x == kCounterChanged + 1 ? hold_init : 0u;
+    if (threadIdx.x == kCounterChanged + 1) {
+        counters[threadIdx.x] = counters[kCounterLayout] == layout ? hold : 0u;
+        counters[kCounterLayout] = layout;
+    } else if (threadIdx.x < kFrameCounters) {
+        counters[threadIdx.x] = 0u;
+    }
     if (write) {
         const uint32_t* src = reinterpret_cast<const uint32_t*>(&b.v[0]);
         uint32_t* out = reinterpret_cast<uint32_t*>(dst);
@@ -482,7 +497,7 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     if ((st = ensure(ctx, w.views, (size_t)V * sizeof(ViewParams))) != GS_OK) return st;
     if ((st = ensure(ctx, w.view_counts, (size_t)V * kViewCounters * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.bin_table, bs.table_elems() * 4)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.counters, 64)) != GS_OK) return st;
+    if ((st = ensure(ctx, w.counters, kCounterWords * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.scan_scratch, scan_scratch_elems(bs.bins * bs.chunks1) * 8)) != GS_OK) return st;
     // every blend records its tiles' work; with blend_group 0 it is dispatched
     // (with -1 queued for a persistent grid) heaviest first, by the last
@@ -506,25 +521,27 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     // way); the projection counts the items whose depth key or rectangle
     // changed since, and when none did those lists are this frame's (they
     // depend on nothing else): the sort and the binning then skip on the
-    // device
-    const std::vector<int> sizes = view_sizes(hv);
-    const bool try_lists = !noalloc && (o.flags & GS_RENDER_REUSE_LISTS) && n > 0 && prev_lists_n == n &&
-                           ctx->lists_sizes == sizes && ctx->lists_cap == o.pair_capacity &&
-                           ctx->lists_shifts == view_shifts(hv);
+    // device.  Lists of other bins or chunks (the tuning sets those) are not
+    // read as this render's: the comparison runs, with the flag that they hold
+    // cleared from the start.  The host compares what it recorded last, the
+    // device the layout's id with that of the lists it holds.
+    const std::vector<int> sizes = view_sizes(hv), shifts = view_shifts(hv);
+    const bool same_render = prev_lists_n == n && ctx->lists_sizes == sizes && ctx->lists_cap == o.pair_capacity;
+    const bool same_layout = same_render && ctx->lists_shifts == shifts && ctx->lists_chunk == bs.chunk &&
+                             ctx->lists_chunks1 == bs.chunks1;
+    const bool try_lists = !noalloc && (o.flags & GS_RENDER_REUSE_LISTS) && n > 0 && same_render;
+    if (!same_layout) ++ctx->lists_layout;
 
     ViewParams* views = static_cast<ViewParams*>(w.views.p);
     uint32_t* counters = static_cast<uint32_t*>(w.counters.p);
     uint32_t* view_counts = static_cast<uint32_t*>(w.view_counts.p);
-    if (V <= kViewsPerLaunch) {
-        ViewBatch b;
-        std::memcpy(b.v, hv.data(), (size_t)V * sizeof(ViewParams));
-        hipLaunchKernelGGL(frame_setup_kernel, dim3(1), dim3(256), 0, s, b, V, views, write_table ? 1 : 0, counters,
-                           try_lists ? 1u : 0u);
-    } else {
-        HIP_TRY(launch_fill_u32(counters, 0u, 16, s), "clear counters");
-        if (try_lists) HIP_TRY(launch_fill_u32(counters + kCounterChanged + 1, 1u, 1, s), "list reuse flag");
-        if (write_table) HIP_TRY(write_view_table(hv, views, s), "view table");
-    }
+    const bool one_launch = V <= kViewsPerLaunch;
+    ViewBatch vb;
+    if (one_launch) std::memcpy(vb.v, hv.data(), (size_t)V * sizeof(ViewParams));
+    hipLaunchKernelGGL(frame_setup_kernel, dim3(1), dim3(256), 0, s, vb, one_launch ? V : 0, views,
+                       one_launch && write_table ? 1 : 0, counters, try_lists && same_layout ? 1u : 0u,
+                       ctx->lists_layout);
+    if (!one_launch && write_table) HIP_TRY(write_view_table(hv, views, s), "view table");
     HIP_TRY(hipGetLastError(), "frame set-up");
     STAGE_MARK(0);
 
@@ -756,8 +773,10 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     ctx->last_reuse = reuse;
     ctx->lists_n = n;
     ctx->lists_sizes = sizes;
-    ctx->lists_shifts = view_shifts(hv);
+    ctx->lists_shifts = shifts;
     ctx->lists_cap = o.pair_capacity;
+    ctx->lists_chunk = bs.chunk;
+    ctx->lists_chunks1 = bs.chunks1;
     ctx->last_views = hv;
     ctx->last_g = *g;
     for (int k = 0; k < 3; ++k) ctx->last_bg[k] = bl.bg[k];
@@ -820,7 +839,7 @@ size_t carve_noalloc(Workspace* w, unsigned char* base, int64_t n, const std::ve
     take(ws.views, (size_t)V * sizeof(ViewParams));
     take(ws.view_counts, (size_t)V * kViewCounters * 4);
     take(ws.bin_table, bs.table_elems() * 4);
-    take(ws.counters, 64);
+    take(ws.counters, kCounterWords * 4);
     take(ws.scan_scratch, scan_scratch_elems(bs.bins * bs.chunks1) * 8);
     take(ws.bin_items, (size_t)((std::max<uint64_t>(capacity, 4) + 3) & ~uint64_t(3)) * 4);
     take(ws.bin_spans, (size_t)((std::max<uint64_t>(capacity, 4) + 3) & ~uint64_t(3)) * 2);
