@@ -671,7 +671,9 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     // Gaussian touches no more bins than tiles); an eager render scatters
     // into the buffers of earlier renders, which mostly have room, before
     // the host has read the sizes, and again into grown ones where they had
-    // not (stores past the buffers are dropped)
+    // not (stores past the buffers are dropped).  Grids whose cursors live in
+    // the count table are scattered once, when the sizes are here: the scatter
+    // moves those cursors, so it cannot run again.
     uint64_t capacity = o.pair_capacity, room = capacity;
     if (eager) room = std::min<uint64_t>(w.bin_items.bytes / 4, w.bin_spans.bytes / 2) & ~uint64_t(3);
     else if ((st = ensure_bin_entries(ctx, w, room)) != GS_OK) return st;
@@ -681,7 +683,8 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
         ba.capacity = room;
         return launch_bins_scatter(ba, s);
     };
-    if (room > 0) HIP_TRY(scatter(), "bin scatter");
+    const bool early = !eager || (room > 0 && bins_in_lds(bs.max_bins));
+    if (early) HIP_TRY(scatter(), "bin scatter");
     STAGE_MARK(4);
     if (eager) {
         uint64_t K64 = 0, entries = 0;
@@ -696,10 +699,13 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
         if (K64 > 0xFFFFFFFFull) return fail(ctx, GS_ERR_CAPACITY, "more than 2^32-1 (Gaussian, tile) pairs");
         capacity = K64;
         if (n > 0) ctx->next_shifts = suggested_shifts(hv, ctx->host_info);
-        if (entries > room || !w.bin_items.p) {
+        const bool grow = entries > room || !w.bin_items.p;
+        if (grow) {
             HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");   // the buffers are grown
             if ((st = ensure_bin_entries(ctx, w, entries)) != GS_OK) return st;
             room = entries;
+        }
+        if (grow || !early) {
             STAGE_MARK(3);
             HIP_TRY(scatter(), "bin scatter");
             STAGE_MARK(4);
