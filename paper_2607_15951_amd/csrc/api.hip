@@ -336,12 +336,14 @@ __global__ void row_table_kernel(const ViewParams* views, int n_views, uint32_t*
 }
 
 
+int bins_along(int tiles, int shift) { return ((tiles - 1) >> shift) + 1; }
+
 void set_bins(ViewParams& v, uint32_t bin_base, int shift)
 {
     v.bin_base = bin_base;
     v.bin_shift = shift;
-    v.bins_x = ((v.tiles_x - 1) >> shift) + 1;
-    v.bins_y = ((v.tiles_y - 1) >> shift) + 1;
+    v.bins_x = bins_along(v.tiles_x, shift);
+    v.bins_y = bins_along(v.tiles_y, shift);
 }
 
 // Edge of the bins each view's counters suggest, staying at the present one
@@ -377,11 +379,21 @@ std::vector<int> view_shifts(const std::vector<ViewParams>& hv)
     return shifts;
 }
 
+// Whether the stream is being captured (also where the runtime will not say).
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // Edges of the bins of a render (make_view chose them by resolution): those
 // of the lists in the workspace where it may keep them, else those that the
 // last render of as many Gaussians in views of the same sizes suggested.
-// Any choice gives the same image.
-void choose_bins(gs_context* ctx, int64_t n, const gs_render_opts* opts, std::vector<ViewParams>& hv)
+// Any choice gives the same image.  Counters still under way are not asked for
+// during a capture, which an event query may end.
+void choose_bins(gs_context* ctx, int64_t n, const gs_render_opts* opts, std::vector<ViewParams>& hv, hipStream_t s)
 {
     const std::vector<int> sizes = view_sizes(hv);
     if (ctx->bins_n != n || ctx->bins_sizes != sizes) {
@@ -390,7 +402,7 @@ void choose_bins(gs_context* ctx, int64_t n, const gs_render_opts* opts, std::ve
         ctx->next_shifts.clear();
         ctx->counts_pending = false;
     }
-    if (ctx->counts_pending && hipEventQuery(ctx->sizes_ev) == hipSuccess) {
+    if (ctx->counts_pending && !capturing(s) && hipEventQuery(ctx->sizes_ev) == hipSuccess) {
         ctx->counts_pending = false;
         ctx->next_shifts = suggested_shifts(hv, ctx->host_info);
     }
@@ -411,12 +423,20 @@ struct BinShape {
     int items1 = 0, chunk = 0, chunks1 = 0;
     bool packed = true;   // the grids fit packed rectangles
     size_t table_elems() const { return (size_t)(bins * chunks1 + 2); }
+    // and with any edges that the views' counters may suggest: a context's
+    // table is sized for those, so that frames of one scene and size allocate
+    // it once (a capture after one warm-up not at all)
+    int64_t any_counts = 0;
+    size_t any_table_elems() const { return std::max((size_t)any_counts + 2, table_elems()); }
 };
 
 BinShape bin_shape(const std::vector<ViewParams>& hv, int64_t n, int tuned)
 {
     BinShape b;
+    int64_t most_bins = 0;
     for (const ViewParams& v : hv) {
+        const int finest = bin_shift_of(v.tiles_x, v.tiles_y, 1.f);
+        most_bins += (int64_t)bins_along(v.tiles_x, finest) * bins_along(v.tiles_y, finest);
         b.bins += (int64_t)v.bins_x * v.bins_y;
         b.max_bins = std::max(b.max_bins, v.bins_x * v.bins_y);
         b.max_diff = std::max(b.max_diff, (v.bins_x + 1) * (v.bins_y + 1));
@@ -424,6 +444,7 @@ BinShape bin_shape(const std::vector<ViewParams>& hv, int64_t n, int tuned)
         b.packed = b.packed && v.tiles_x <= kPackedRectTiles && v.tiles_y <= kPackedRectTiles;
     }
     bins_chunk_shape(n, (int)hv.size(), b.bins, b.max_bins, tuned, &b.items1, &b.chunk, &b.chunks1);
+    b.any_counts = bins_count_bound(n, (int)hv.size(), most_bins, tuned);
     return b;
 }
 
@@ -496,9 +517,11 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     if ((st = ensure(ctx, w.partials, project_partials_elems(n, V) * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.views, (size_t)V * sizeof(ViewParams))) != GS_OK) return st;
     if ((st = ensure(ctx, w.view_counts, (size_t)V * kViewCounters * 4)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.bin_table, bs.table_elems() * 4)) != GS_OK) return st;
+    // (the no-allocation scratch holds just what this render needs)
+    const size_t table = noalloc ? bs.table_elems() : bs.any_table_elems();
+    if ((st = ensure(ctx, w.bin_table, table * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.counters, kCounterWords * 4)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.scan_scratch, scan_scratch_elems(bs.bins * bs.chunks1) * 8)) != GS_OK) return st;
+    if ((st = ensure(ctx, w.scan_scratch, scan_scratch_elems((int64_t)table - 2) * 8)) != GS_OK) return st;
     // every blend records its tiles' work; with blend_group 0 it is dispatched
     // (with -1 queued for a persistent grid) heaviest first, by the last
     // render's work when that render had the same tile layout (the history:
@@ -580,9 +603,7 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     bool learn = false;
     if (!eager && !noalloc && write_table && ctx->host_info_dev && n > 0 && ctx->next_shifts.empty() &&
         !ctx->counts_pending) {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        HIP_TRY(hipStreamIsCapturing(s, &cap), "hipStreamIsCapturing");
-        learn = cap == hipStreamCaptureStatusNone;
+        learn = !capturing(s);
         if (learn) counts_out = ctx->host_info_dev;
     }
     if (eager) ctx->counts_pending = false;   // host_info is this render's from here
@@ -969,7 +990,7 @@ gs_status gs_render(gs_context* ctx, const gs_gaussians* g, const gs_camera* cam
     gs_status st = validate(ctx, g, cam, width, height, opts, out_rgb);
     if (st != GS_OK) return st;
     std::vector<ViewParams> hv(1, make_view(cam, width, height, out_rgb, out_final_T, out_n_contrib, 0u, 0u, 0u));
-    choose_bins(ctx, g->n, opts, hv);
+    choose_bins(ctx, g->n, opts, hv, static_cast<hipStream_t>(stream));
     return render_views(ctx, g, hv, opts, static_cast<hipStream_t>(stream));
 }
 
@@ -1024,7 +1045,7 @@ gs_status gs_render_batched(gs_context* ctx, const gs_gaussians* g, const gs_vie
     std::vector<ViewParams> hv;
     gs_status st = build_views(ctx, g, views, n_views, opts, hv);
     if (st != GS_OK) return st;
-    choose_bins(ctx, g->n, opts, hv);
+    choose_bins(ctx, g->n, opts, hv, static_cast<hipStream_t>(stream));
     return render_views(ctx, g, hv, opts, static_cast<hipStream_t>(stream));
 }
 
@@ -1042,12 +1063,12 @@ gs_status gs_graph_create(gs_context* ctx, const gs_gaussians* g, const gs_view*
     hipStream_t s = static_cast<hipStream_t>(stream);
     // an eager render sizes every buffer (capture must not allocate) and
     // writes the view table
-    choose_bins(ctx, g->n, nullptr, hv);
+    choose_bins(ctx, g->n, nullptr, hv, s);
     if ((st = render_views(ctx, g, hv, opts, s)) != GS_OK) return st;
     HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
     // again where that render suggests other bins: the graph keeps its own
     const std::vector<int> shifts = view_shifts(hv);
-    choose_bins(ctx, g->n, nullptr, hv);
+    choose_bins(ctx, g->n, nullptr, hv, s);
     if (view_shifts(hv) != shifts) {
         if ((st = render_views(ctx, g, hv, opts, s)) != GS_OK) return st;
         HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
@@ -1373,9 +1394,7 @@ gs_status write_lists(gs_context* ctx, const gs_list_info& info, uint32_t* value
     uint64_t* scan_scratch = static_cast<uint64_t*>(l.scan_scratch.p);
     // (a stream under capture takes no part in that order: its caller orders
     // the replays)
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIP_TRY(hipStreamIsCapturing(s, &cap), "hipStreamIsCapturing");
-    const bool ordered = cap == hipStreamCaptureStatusNone;
+    const bool ordered = !capturing(s);
     if (ordered) HIP_TRY(hipStreamWaitEvent(s, l.done, 0), "hipStreamWaitEvent");
     hipLaunchKernelGGL(row_table_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, la.views, la.n_views,
                        row_table, row_table + rows, rows);
@@ -1513,7 +1532,7 @@ gs_status gs_autotune(gs_context* ctx, const gs_gaussians* g, const gs_view* vie
     const uint32_t saved_flags = ctx->profiling;
     const Tuning start = ctx->tuning;
     Tuning cur = start;
-    choose_bins(ctx, g->n, nullptr, hv);
+    choose_bins(ctx, g->n, nullptr, hv, s);
     if ((st = gs_set_profiling(ctx, GS_PROFILE_STAGES)) != GS_OK) return st;   // creates the stage events
     int k_out = 0;
     for (const TuneParam& p : kTuneParams) {

@@ -685,7 +685,7 @@ int bin_shift_of(int tiles_x, int tiles_y, float footprint)
 // the count table (bins x chunks words) at about one word per (view,
 // Gaussian): a wave works through its 64-Gaussian batches one after another.
 // The tuned width (8 the default) scales it.
-constexpr int64_t kFullWaves = 16384;
+constexpr int64_t kFullWaves = 16384, kTableSlack = 16384;
 void bins_chunk_shape(int64_t n, int n_views, int64_t bins, int max_bins, int tuned, int* items1, int* chunk,
                       int* chunks1)
 {
@@ -694,7 +694,7 @@ void bins_chunk_shape(int64_t n, int n_views, int64_t bins, int max_bins, int tu
         const int64_t size = (int64_t)batches * 64 * waves;
         return std::max<int64_t>((n + size - 1) / size, 1);
     };
-    auto fits = [&](int batches) { return chunks(batches) == 1 || bins * chunks(batches) <= n * n_views + 16384; };
+    auto fits = [&](int batches) { return chunks(batches) == 1 || bins * chunks(batches) <= n * n_views + kTableSlack; };
     int batches = 1;   // per wave
     while (batches < 8 && n * n_views / (64 * batches) > kFullWaves) batches *= 2;
     while (!fits(batches)) batches *= 2;
@@ -703,6 +703,14 @@ void bins_chunk_shape(int64_t n, int n_views, int64_t bins, int max_bins, int tu
     *items1 = std::min(batches, 8);
     *chunk = batches * 64 * waves;
     *chunks1 = (int)chunks(batches);
+}
+
+// Most count table words (bins x chunks) that bins_chunk_shape leaves for any
+// bins up to that many: what fits, or a chunk a view; twice that at half the
+// chunk size.
+int64_t bins_count_bound(int64_t n, int n_views, int64_t bins, int tuned)
+{
+    return std::max<int64_t>(n * n_views + kTableSlack, bins) * (tuned < 8 ? 2 : 1);
 }
 
 bool bins_in_lds(int max_bins) { return bin_waves(max_bins) > 0; }

@@ -220,6 +220,7 @@ struct BinArgs {
 int bin_shift_of(int tiles_x, int tiles_y, float footprint);
 void bins_chunk_shape(int64_t n, int n_views, int64_t bins, int max_bins, int tuned, int* items1, int* chunk,
                       int* chunks1);
+int64_t bins_count_bound(int64_t n, int n_views, int64_t bins, int tuned);
 bool bins_in_lds(int max_bins);
 hipError_t launch_bins_count(const BinArgs& a, uint64_t* scan_scratch, hipStream_t s);
 hipError_t launch_bins_scatter(const BinArgs& a, hipStream_t s);
