@@ -271,7 +271,10 @@ constexpr int kFrameCounters = 16;   // words cleared at frame set-up
 // (gs_context::lists_layout) of the lists in the workspace.  It is compared
 // on the device: a captured render is replayed after whatever ran last.
 constexpr int kCounterLayout = kFrameCounters;
-constexpr int kCounterWords = kFrameCounters + 1;
+// counters[kCounterTable], likewise kept: where the offset table starts and
+// the words from one bin to the next (BinLists)
+constexpr int kCounterTable = kFrameCounters + 1;
+constexpr int kCounterWords = kFrameCounters + 3;
 
 struct ViewBatch {
     ViewParams v[kViewsPerLaunch];
@@ -291,11 +294,13 @@ __global__ void write_views_kernel(ViewBatch b, int count, ViewParams* dst)
 // arguments.  hold: the kept lists may be this render's, if their layout is
 // the one with that id.
 __global__ void frame_setup_kernel(ViewBatch b, int count, ViewParams* dst, int write, uint32_t* counters,
-                                   uint32_t hold, uint32_t layout)
+                                   uint32_t hold, uint32_t layout, uint32_t table_first, uint32_t table_stride)
 {
     if (threadIdx.x == kCounterChanged + 1) {
         counters[threadIdx.x] = counters[kCounterLayout] == layout ? hold : 0u;
         counters[kCounterLayout] = layout;
+        counters[kCounterTable] = table_first;
+        counters[kCounterTable + 1] = table_stride;
     } else if (threadIdx.x < kFrameCounters) {
         counters[threadIdx.x] = 0u;
     }
@@ -563,7 +568,7 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     if (one_launch) std::memcpy(vb.v, hv.data(), (size_t)V * sizeof(ViewParams));
     hipLaunchKernelGGL(frame_setup_kernel, dim3(1), dim3(256), 0, s, vb, one_launch ? V : 0, views,
                        one_launch && write_table ? 1 : 0, counters, try_lists && same_layout ? 1u : 0u,
-                       ctx->lists_layout);
+                       ctx->lists_layout, (uint32_t)bins_table_first(bs.max_bins), (uint32_t)bs.chunks1);
     if (!one_launch && write_table) HIP_TRY(write_view_table(hv, views, s), "view table");
     HIP_TRY(hipGetLastError(), "frame set-up");
     STAGE_MARK(0);
@@ -1224,7 +1229,12 @@ gs_status gs_render_backward(gs_context* ctx, const gs_gaussians* g, const float
     HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t*>(grad2d), 0u, items * kGrad2d, s), "clear gradients");
     BlendBackArgs bb{};
     bb.splats = static_cast<const Splat*>(ctx->ws.splats.p);
+    // the layout of the bins from the device, where the render wrote it: a
+    // captured backward follows whichever render ran before it
     bb.lists = ctx->bins;
+    bb.lists.off = static_cast<const uint32_t*>(ctx->ws.bin_table.p);
+    bb.table = static_cast<const uint32_t*>(ctx->ws.counters.p) + kCounterTable;
+    bb.bin_views = static_cast<const ViewParams*>(ctx->ws.views.p);
     bb.views = views;
     bb.n_views = V;
     bb.tiles = ctx->tiles;

@@ -111,7 +111,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void b
     int tile = blend_tile(a.order, a.group);
     if (tile >= a.tiles) return;
     tile = __builtin_amdgcn_readfirstlane(tile);   // uniform: it and what follows from it stay scalar
-    const ViewParams& vp = a.views[view_of_tile(a.views, a.n_views, (uint32_t)tile)];
+    const int view = view_of_tile(a.views, a.n_views, (uint32_t)tile);
+    const ViewParams& vp = a.views[view];
     const int width = vp.width, height = vp.height;
     const int local = tile - (int)vp.tile_base;
     const int tx = local % vp.tiles_x, ty = local / vp.tiles_x;
@@ -120,7 +121,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void b
     const int px = tx * kTile + lx, py = ty * kTile + ly;
     const bool inside = px < width && py < height;
     TileCursor tc;
-    tc.start(a.lists, vp, tx, ty);
+    BinLists lists = a.lists;
+    lists.off += a.table[0];
+    lists.stride = a.table[1];
+    tc.start(lists, a.bin_views[view], tx, ty);
     const double ox = (double)(tx * kTile), oy = (double)(ty * kTile);
     const float fx = (float)lx, fy = (float)ly;
 

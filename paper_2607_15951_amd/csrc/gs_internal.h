@@ -233,11 +233,13 @@ struct BinLists {
     int64_t stride;
     uint64_t capacity;
 };
+// First word of the offsets in the table: where the cursors live in the table
+// (large grids) the scatter moved every chunk's cursor to its end, the start
+// of the next.
+inline int bins_table_first(int max_bins) { return bins_in_lds(max_bins) ? 1 : 0; }
 inline BinLists bin_lists(const BinArgs& a)
 {
-    // where the cursors live in the table (large grids) the scatter moved
-    // every chunk's cursor to its end, the start of the next
-    return {a.items, a.spans, a.table + (bins_in_lds(a.max_bins) ? 1 : 0), a.chunks1, a.capacity};
+    return {a.items, a.spans, a.table + bins_table_first(a.max_bins), a.chunks1, a.capacity};
 }
 
 // The per-tile lists (tile_bin.hip), written on request.
@@ -327,7 +329,9 @@ hipError_t launch_blend_order(const uint32_t* cost, const BinLists& lists, const
 constexpr int kGrad2d = 9;
 struct BlendBackArgs {
     const Splat* splats;
-    BinLists lists;
+    BinLists lists;                // off: the whole table; the render's device words say how it is laid out:
+    const uint32_t* table;         // first word of the offsets, stride
+    const ViewParams* bin_views;   // the render's table: the views' bins
     const ViewParams* views;
     int n_views;
     int64_t tiles;
