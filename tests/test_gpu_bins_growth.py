@@ -3,6 +3,7 @@ context left: the entries are scattered again into grown buffers, which must
 give what a fresh context gives, bit for bit.  Grids of each kind: cursors of
 four waves or of one in LDS, and in the count table (more than 4096 bins),
 which the scatter itself moves."""
+import numpy as np
 import pytest
 
 import scenes
