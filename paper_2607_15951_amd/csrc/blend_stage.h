@@ -133,7 +133,10 @@ struct Pick4 {
 struct TileCursor {
     const uint32_t* items;
     const uint16_t* spans;
-    uint32_t begin, end;   // the bin's list
+    // The bin's list: entries begin to end past base, a multiple of 4.  A bin
+    // lists a Gaussian once, so end stays below 2^31 where base may be 2^32 less
+    // a few, and nothing below (two rounds past the end at most) wraps.
+    uint32_t base, begin, end;
     uint32_t cur;          // next round's first entry (a multiple of 4: whole groups are loaded)
     uint32_t tail;         // entries picked so far
     uint32_t key;          // the tile's place in the bin, guard bits set, twice
@@ -149,11 +152,11 @@ struct TileCursor {
     }
     __device__ __forceinline__ uint2 load_spans(uint32_t c) const
     {
-        return *reinterpret_cast<const uint2*>(spans + group(c));
+        return *reinterpret_cast<const uint2*>(spans + (base + group(c)));
     }
     __device__ __forceinline__ uint4 load_items(uint32_t c) const
     {
-        return *reinterpret_cast<const uint4*>(items + group(c));
+        return *reinterpret_cast<const uint4*>(items + (base + group(c)));
     }
 
     __device__ __forceinline__ void start(const BinLists& lists, const ViewParams& vp, int tx, int ty)
@@ -165,9 +168,10 @@ struct TileCursor {
         items = lists.items;
         spans = lists.spans;
         // uniform values, kept scalar
-        begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-        end = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)e);
-        cur = begin < end ? begin & ~3u : end;
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)b & ~3u));
+        begin = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)b & 3u));
+        end = begin + (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(e - b));
+        cur = begin < end ? 0u : end;
         tail = 0;
         const uint32_t edge = (1u << vp.bin_shift) - 1u, x = (uint32_t)tx & edge, y = (uint32_t)ty & edge;
         const uint32_t k = 0x8888u | x | (y << 4) | ((edge - x) << 8) | ((edge - y) << 12);
