@@ -65,7 +65,8 @@ struct Workspace {
     DevBuf splats, depth_key, radius, tiles_touched, rect;
     DevBuf sort_ka, sort_va, sort_kb, sort_vb, hist, scan_scratch;
     DevBuf sort_pa, sort_pb;     // packed rectangles carried by the depth sort
-    DevBuf bin_table, bin_items, bin_spans, partials, sorted_rect, readback;
+    DevBuf bin_table;   // a context's: behind the splats, not an allocation
+    DevBuf bin_items, bin_spans, partials, sorted_rect, readback;
     DevBuf views;                // device view table
     DevBuf view_counts;          // [n_views][kViewCounters]
     DevBuf counters;             // [kCounterWords]: [1] capacity overflow flag
@@ -160,7 +161,9 @@ gs_status hip_fail(gs_context* ctx, hipError_t e, const char* what)
     return fail(ctx, GS_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-gs_status ensure(gs_context* ctx, DevBuf& b, size_t bytes)
+// At least that many bytes; a buffer that has to grow gets a quarter more, or
+// (spare) that many of the bytes asked for count as its quarter.
+gs_status ensure(gs_context* ctx, DevBuf& b, size_t bytes, size_t spare = 0)
 {
     if (bytes == 0) bytes = 256;
     if (b.bytes >= bytes) return GS_OK;
@@ -170,7 +173,7 @@ gs_status ensure(gs_context* ctx, DevBuf& b, size_t bytes)
     if (b.p) (void)hipFree(b.p);
     b.p = nullptr;
     b.bytes = 0;
-    const size_t want = bytes + bytes / 4;
+    const size_t want = std::max(bytes, (bytes - spare) + (bytes - spare) / 4);
     hipError_t e = hipMalloc(&b.p, want);
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -297,7 +300,7 @@ __global__ void frame_setup_kernel(ViewBatch b, int count, ViewParams* dst, int 
                                    uint32_t hold, uint32_t layout, uint32_t table_first, uint32_t table_stride)
 {
     if (threadIdx.x == kCounterChanged + 1) {
-        counters[threadIdx.x] = counters[kCounterLayout] == layout ? hold : 0u;
+        counters[threadIdx.x] = hold && counters[kCounterLayout] == layout ? 1u : 0u;   // no load without hold
         counters[kCounterLayout] = layout;
         counters[kCounterTable] = table_first;
         counters[kCounterTable + 1] = table_stride;
@@ -429,8 +432,9 @@ struct BinShape {
     bool packed = true;   // the grids fit packed rectangles
     size_t table_elems() const { return (size_t)(bins * chunks1 + 2); }
     // and with any edges that the views' counters may suggest: a context's
-    // table is sized for those, so that frames of one scene and size allocate
-    // it once (a capture after one warm-up not at all)
+    // table is sized for those, so that frames of one scene and size keep it
+    // (a capture after one warm-up allocates nothing, and what it captured
+    // stays valid when later frames take other edges)
     int64_t any_counts = 0;
     size_t any_table_elems() const { return std::max((size_t)any_counts + 2, table_elems()); }
 };
@@ -496,7 +500,21 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     const Tuning tu = ctx->tuning;
     const BinShape bs = bin_shape(hv, n, tu.bin1_items);
 
-    if ((st = ensure(ctx, w.splats, ni * sizeof(Splat))) != GS_OK) return st;
+    // The bins' count table, sized for any edges (the no-allocation scratch: just
+    // what this render needs).  A context's lies behind the splats, in what
+    // their allocation holds to spare: with 8 MB of its own at 2M Gaussians the
+    // first frame took 190 us more (the runtime's memory pool grows once more).
+    const size_t table = noalloc ? bs.table_elems() : bs.any_table_elems(), splats_before = w.splats.bytes;
+    if (noalloc) {
+        if ((st = ensure(ctx, w.splats, ni * sizeof(Splat))) != GS_OK) return st;
+        if ((st = ensure(ctx, w.bin_table, table * 4)) != GS_OK) return st;
+    } else {
+        const size_t at = (ni * sizeof(Splat) + 255) & ~size_t(255);
+        if ((st = ensure(ctx, w.splats, at + table * 4, table * 4)) != GS_OK) return st;
+        w.bin_table.p = static_cast<unsigned char*>(w.splats.p) + at;
+        w.bin_table.bytes = table * 4;
+    }
+    const bool table_kept = w.splats.bytes == splats_before;   // not allocated again
     if ((st = ensure(ctx, w.depth_key, ni * 4)) != GS_OK) return st;
     if (!noalloc) {   // read only by gs_copy_projection and the backward
         if ((st = ensure(ctx, w.radius, ni * 4)) != GS_OK) return st;
@@ -522,9 +540,6 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     if ((st = ensure(ctx, w.partials, project_partials_elems(n, V) * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.views, (size_t)V * sizeof(ViewParams))) != GS_OK) return st;
     if ((st = ensure(ctx, w.view_counts, (size_t)V * kViewCounters * 4)) != GS_OK) return st;
-    // (the no-allocation scratch holds just what this render needs)
-    const size_t table = noalloc ? bs.table_elems() : bs.any_table_elems();
-    if ((st = ensure(ctx, w.bin_table, table * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.counters, kCounterWords * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.scan_scratch, scan_scratch_elems((int64_t)table - 2) * 8)) != GS_OK) return st;
     // every blend records its tiles' work; with blend_group 0 it is dispatched
@@ -556,7 +571,7 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     const std::vector<int> sizes = view_sizes(hv), shifts = view_shifts(hv);
     const bool same_render = prev_lists_n == n && ctx->lists_sizes == sizes && ctx->lists_cap == o.pair_capacity;
     const bool same_layout = same_render && ctx->lists_shifts == shifts && ctx->lists_chunk == bs.chunk &&
-                             ctx->lists_chunks1 == bs.chunks1;
+                             ctx->lists_chunks1 == bs.chunks1 && table_kept;
     const bool try_lists = !noalloc && (o.flags & GS_RENDER_REUSE_LISTS) && n > 0 && same_render;
     if (!same_layout) ++ctx->lists_layout;
 
@@ -960,7 +975,7 @@ void gs_destroy(gs_context* ctx)
     ListSpace& l = ctx->lists;
     DevBuf* bufs[] = {&ctx->grad2d, &ctx->back_views, &w.splats, &w.depth_key, &w.radius, &w.tiles_touched, &w.rect,
                       &w.sort_ka, &w.sort_va, &w.sort_kb, &w.sort_vb, &w.hist, &w.scan_scratch, &w.sort_pa, &w.sort_pb,
-                      &w.bin_table, &w.bin_items, &w.bin_spans, &w.partials, &w.sorted_rect, &w.readback, &w.views,
+                      &w.bin_items, &w.bin_spans, &w.partials, &w.sorted_rect, &w.readback, &w.views,
                       &w.view_counts, &w.counters, &w.tile_work, &w.reuse_words, &w.tile_cost, &w.tile_order,
                       &l.row_tiles_x, &l.info, &l.counts1, &l.rows_off, &l.row_ent, &l.counts2, &l.scan_scratch,
                       &l.tile_offsets, &l.overflow};

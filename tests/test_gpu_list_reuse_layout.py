@@ -49,6 +49,24 @@ def test_tuning_between_kept_frames(case, first, capacity):
         r.close()
 
 
+def test_a_smaller_shape_that_is_no_other_layout():
+    """100000 Gaussians over 60 bins: bin_row_items 4 and 8 are one shape, but 4
+    asks for a larger table, which must not lose the kept lists."""
+    import paper_2607_15951_amd as gs
+    dev, cam = gs.scene_to_device(scenes.make_scene("C3", n=100_000, seed=6, sh_degree=0)), scenes.default_camera(1280, 720)
+    want = plain(dev, cam, 1280, 720)
+    r = gs.Renderer(0)
+    try:
+        for _ in range(2):
+            r.render(dev, cam, 1280, 720)
+        for items in (4, 8, 4):
+            r.set_tuning(bin_row_items=items)
+            same(snapshot(r, r.render(dev, cam, 1280, 720, reuse_lists=True)), want, f"bin_row_items {items}")
+            assert r.list_reuse()["changed"] == 0
+    finally:
+        r.close()
+
+
 def test_autotune_with_the_flag(case):
     import torch
     import paper_2607_15951_amd as gs
