@@ -405,8 +405,9 @@ gs_status gs_get_list_reuse(gs_context* ctx, uint32_t* out2);
  * dealt to the XCDs, change only speed.  Every supported value gives the same
  * image, final T, n_contrib, lists and projection, bit for bit.
  *   sort_items        keys per thread of a depth-sort block: 4, 8 or 16
- *                     (from 800000 keys on 8 stands for 16; up to 98304 keys
- *                     the sort takes shapes of its own)
+ *                     (up to 98304 keys the sort takes shapes of its own; a
+ *                     context that was never given a tuning reports 8 and
+ *                     takes 16 from 800000 keys on)
  *   bin_row_items     scale of the depth-sorted Gaussians per lane of a
  *                     binning wavefront (and of the row lists of
  *                     gs_copy_lists): 4, 8 or 16

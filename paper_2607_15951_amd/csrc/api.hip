@@ -1498,7 +1498,7 @@ Tuning from_abi(const gs_tuning& t)
 gs_tuning to_abi(const Tuning& t)
 {
     gs_tuning o;
-    o.sort_items = t.sort_items;
+    o.sort_items = t.sort_items ? t.sort_items : 8;
     o.bin_row_items = t.bin1_items;
     o.bin_tile_items = t.bin2_items;
     o.blend_tile_group = t.blend_group;

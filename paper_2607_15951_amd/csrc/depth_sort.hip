@@ -853,8 +853,8 @@ bool depth_sort_items_supported(int items) { return items == 4 || items == 8 || 
 
 size_t order_reuse_words(int64_t n) { return (size_t)(kReuseWords + (n + 255) / 256); }
 
-// From here on 8 keys per thread, the default, stand for 16: a digit's runs
-// are twice as long.  Four passes of 8 and of 16: 74 and 75 us at 500K keys, 89
+// From here on a sort whose width nobody set takes 16 keys per thread instead
+// of 8: a digit's runs are twice as long.  Four passes of 8 and of 16: 74 and 75 us at 500K keys, 89
 // and 82 at 1M, 100 and 97 at 1.2M, 180 and 165 at 3M, 699 and 588 at 16M.
 constexpr int64_t kWideKeys = 800000;
 // Up to here a pass goes without a launch that scans the counts: group sums
@@ -877,8 +877,8 @@ size_t depth_sort_hist_elems(int64_t n, int n_views)
     return fused_sort(n, V) ? std::max(passes, (size_t)(4 * 256 * V * ((n + kFusedThreads - 1) / kFusedThreads))) : passes;
 }
 
-// Items per thread that a sort of that many keys takes.
-static int sort_width(int64_t keys, int items) { return items == 8 && keys >= kWideKeys ? 16 : items; }
+// Items per thread that a sort of that many keys takes (items 0: not set).
+static int sort_width(int64_t keys, int items) { return items ? items : (keys >= kWideKeys ? 16 : 8); }
 
 size_t depth_sort_clear_words(int64_t n, int n_views, int items)
 {
@@ -914,7 +914,8 @@ hipError_t launch_order_reuse(const uint32_t* keys, uint32_t* keys_a, uint32_t* 
 }
 
 // Sorts each of the n_views segments keys_in[v * n .. (v + 1) * n) (not
-// modified) with values v * n + i, items keys per thread of a block.  Four
+// modified) with values v * n + i, items keys per thread of a block (0: by
+// their number).  Four
 // passes: in -> a -> b -> a -> b, so the sorted values (and payloads) end in
 // vals_b (pay_b); the last pass writes no keys.  With reuse_words (one view,
 // after launch_order_reuse) every pass reads words[0] on the device and does
@@ -925,9 +926,9 @@ hipError_t launch_depth_sort(const uint32_t* keys_in, uint32_t* keys_a, uint32_t
                              hipStream_t s, const PartialSums* sums, hipEvent_t sums_done)
 {
     if (n == 0 || n_views <= 0) return hipSuccess;
+    items = sort_width(n * n_views, items);
     if (!depth_sort_items_supported(items) || (sums && reuse_words)) return hipErrorInvalidValue;
     const PartialSums no_sums{};
-    items = sort_width(n * n_views, items);
     const int64_t tile = (int64_t)kSortBlock * items;
     const int bpv = (int)((n + tile - 1) / tile);
     const unsigned nblocks = (unsigned)bpv * (unsigned)n_views;

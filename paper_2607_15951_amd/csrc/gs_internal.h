@@ -18,7 +18,7 @@ constexpr int kTileWorkFields = 6;        // u64 fields of a per-tile blend trac
 // Launch shapes that change speed but never results (every choice gives the
 // same image, lists and counts): chosen per workload by the autotuner.
 struct Tuning {
-    int sort_items;    // keys per thread of a depth-sort block: 4, 8, 16
+    int sort_items;    // keys per thread of a depth-sort block: 4, 8, 16; 0, until a caller sets it: 8 or 16 by their number
     int bin1_items;    // depth-sorted Gaussians per lane of a binning wave: 4, 8, 16
     int bin2_items;    // row entries per lane of a wave that writes the per-tile lists: 8, 16, 32
     int blend_group;   // consecutive tiles dealt to one XCD by the blend: 1 .. 64;
@@ -26,7 +26,7 @@ struct Tuning {
                        // -1: the same order as a work queue that a persistent grid drains
     int blend_batch;   // list entries the blend stages per batch: 128, 256, 512
 };
-constexpr Tuning kDefaultTuning = {8, 8, 16, 0, 256};
+constexpr Tuning kDefaultTuning = {0, 8, 16, 0, 256};
 bool tuning_supported(const Tuning& t);
 constexpr int kMaxRows = 2048;            // tile rows per image (height <= 32768)
 constexpr int kMaxTotalRows = 16384;      // tile rows over all views of one render
@@ -161,7 +161,7 @@ __device__ __forceinline__ ushort4 unpack_rect(uint32_t p)
 // passes, which ends in pay_b in the sorted order.  With sums (and no
 // reuse_words) the first launch also sums the projection's partials; the
 // event sums_done, if any, is recorded behind it.
-bool depth_sort_items_supported(int items);
+bool depth_sort_items_supported(int items);   // of a caller: 4, 8, 16
 size_t depth_sort_hist_elems(int64_t n, int n_views);   // enough for every supported width
 size_t depth_sort_clear_words(int64_t n, int n_views, int items);   // first words of counts that have to be zero
 hipError_t launch_depth_sort(const uint32_t* keys_in, uint32_t* keys_a, uint32_t* vals_a,
