@@ -21,7 +21,7 @@
 // per lane, entries staged through LDS with the same per-quad reach masks.
 // Vector instructions bound it (92% of their issue rate), so an entry's sums
 // over a wave are taken before what they share (the opacity, the factors, for
-// the conic all but the second moments of dL/dp), summed with as few
+// the conic all but the second moments), summed with as few
 // cross-lane instructions as they need (below) and added into an LDS row of
 // the staged entry; the rest is applied once per tile and entry, after the
 // batch, on the way to nine atomic adds in HBM.  At 3M Gaussians and
@@ -42,9 +42,9 @@ constexpr float kLn2 = 0.69314718055994531f;
 constexpr int kBackBatch = 128;
 constexpr int kFlush = 256 / kGrad2d;   // entries whose sums are flushed at once
 
-// The sums of an entry over a tile's pixels, with gp = dL/dp and w = a T, in
-// the order in which wave_sum9 leaves them in the lanes.
-enum { kS1, kSv, kSu, kSxx, kSxy, kSr, kSyy, kSg, kSb };   // gp, gp dp/dv / ln2, gp dp/du / ln2, gp dx^2, ...
+// The sums of an entry over a tile's pixels, with go = dL/d(opacity) and w =
+// a T, in the order in which wave_sum9 leaves them in the lanes.
+enum { kSo, kSv, kSu, kSxx, kSxy, kSr, kSyy, kSg, kSb };   // go, go dp/dv / ln2, go dp/du / ln2, go dx^2, ...
 
 struct BackLds {
     float4 s0[kBackBatch];   // du_hi, dv_hi, du_lo, dv_lo
@@ -81,7 +81,7 @@ __device__ __forceinline__ float half_sums16(float a, float b)
 // and five LDS exchanges, whole-row rotations of three registers 30.)
 __device__ __forceinline__ float wave_sum9(const float (&g)[9])
 {
-    const float h0 = half_sums32(g[kS1], g[kSu]), h1 = half_sums32(g[kSv], g[kSxx]), h2 = half_sums32(g[kSxy], g[kSyy]),
+    const float h0 = half_sums32(g[kSo], g[kSu]), h1 = half_sums32(g[kSv], g[kSxx]), h2 = half_sums32(g[kSxy], g[kSyy]),
                 h3 = half_sums32(g[kSr], g[kSg]);
     const float q0 = half_sums16(h0, h1), q1 = half_sums16(h2, h3);
     float t, u = g[kSb];
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void b
     // the thread's gradient when the sums are flushed: which one, from which
     // sum, times what
     const int flush_j = tid / kGrad2d, flush_c = tid % kGrad2d;
-    constexpr int kOf[kGrad2d] = {kSu, kSv, kSxx, kSxy, kSyy, kS1, kSr, kSg, kSb};
+    constexpr int kOf[kGrad2d] = {kSu, kSv, kSxx, kSxy, kSyy, kSo, kSr, kSg, kSb};
     int flush_of = 0;
 #pragma unroll
     for (int c = 0; c < kGrad2d; ++c) flush_of = flush_c == c ? kOf[c] : flush_of;
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void b
                 // not past the pixel's last entry, and visible
                 const bool take = (uint32_t)__float_as_int(e2.w) <= nc && al >= 1.0f / 255.0f;
                 if (__builtin_amdgcn_ballot_w64(take) == 0) continue;
-                float gp = 0.f;   // dL/dp, p the exponent of exp
+                float go = 0.f;   // dL/d(opacity); times the opacity: dL/dp
                 float g[9];
                 g[kSr] = g[kSg] = g[kSb] = 0.f;
                 if (take) {
@@ -250,20 +250,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void b
                     Tr = fmaf(-al, Tr, Tr);   // as the forward: Tr (1 - al), rounded once
                     const float inv = __builtin_amdgcn_rcpf(1.0f - al);   // 1 - al >= 0.01
                     const float ga = fmaf(gc, Tr, -X) * inv;
-                    gp = e1.w * E <= 0.99f ? ga * al : 0.f;
+                    go = e1.w * E <= 0.99f ? ga * E : 0.f;
                     g[kSr] = G0 * w;
                     g[kSg] = G1 * w;
                     g[kSb] = G2 * w;
                 }
-                g[kS1] = gp;
+                g[kSo] = go;
                 // dp/d(dx) = -(A dx + B dy) = ln2 (2 A' dx + B' dy): formed per
                 // pixel, since for a needle its two terms cancel (from the sums
                 // of dx and dy, 25 us less at 3M, the centres' errors are 2%
                 // larger)
                 const float cy = e1.z * dy;
-                g[kSu] = gp * fmaf(e1.x, dx, fmaf(e1.x, dx, e1.y * dy));
-                g[kSv] = gp * fmaf(e1.y, dx, cy + cy);
-                const float gx = gp * dx, gy = gp * dy;
+                g[kSu] = go * fmaf(e1.x + e1.x, dx, e1.y * dy);
+                g[kSv] = go * fmaf(e1.y, dx, cy + cy);
+                const float gx = go * dx, gy = go * dy;
                 g[kSxx] = gx * dx;
                 g[kSxy] = gx * dy;
                 g[kSyy] = gy * dy;
@@ -281,8 +281,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void b
         if (tid < kFlush * kGrad2d) {
             for (int j = flush_j; j < nk; j += kFlush) {
                 float v = L.s_acc[j][flush_of];
-                if (flush_c == 5) v = v != 0.f ? v / L.s1[j].w : 0.f;   // sum of dL/dp over the opacity
-                else v *= flush_by;
+                v *= flush_c < 5 ? flush_by * L.s1[j].w : flush_by;
                 if (v != 0.f) unsafeAtomicAdd(&a.grad2d[(int64_t)L.s_item[j] * kGrad2d + flush_c], v);
             }
         }
