@@ -649,11 +649,13 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     // previous lists hold, which every kernel of the sort and the binning
     // reads on the device
     pa.changed = try_lists ? counters + kCounterChanged : nullptr;
-    // the first launch of the sort sums the projection's counts: 5 us less a
-    // frame up to 500K Gaussians, while at 3M its one workgroup of 256 threads
-    // takes 8 us more than the launch of 1024 that it saves.  Not where
-    // something reads them before it (list reuse: the flag; order reuse; a
-    // copy to the host).
+    // the first launch of the sort sums the projection's counts.  Frames of
+    // the mixture at 1080p by a launch of its own and so: 293 and 287 us at 1M
+    // Gaussians, 378 and 374 at 2M, 483 and 481 at 3M, 742 and 736 at 6M, 1244
+    // and 1245 at 12M.  (The line was drawn from 500K and 3M, at which
+    // 8 us more were measured before other launches changed; by these it could
+    // lie at 6M.)  Not where something reads them before it (list reuse: the
+    // flag; order reuse; a copy to the host).
     const bool reuse = !noalloc && (o.flags & GS_RENDER_REUSE_ORDER) && V == 1 && n > 0 && prev_order_n == n;
     const bool sort_sums = n > 0 && n <= 1000000 && !try_lists && !reuse && !(eager && !ctx->host_info_dev);
     pa.clear = static_cast<uint32_t*>(w.hist.p);

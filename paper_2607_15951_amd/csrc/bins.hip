@@ -44,10 +44,19 @@ constexpr int kMaxBins4 = 768, kMaxBins1 = 4096;
 // Entries that a round of the scatter stages in LDS, and its Gaussians, as
 // multiples of these.  Twice as many where the bins are at their largest (so
 // Gaussians take several each) and more than kLongBins: eight entries a bin and
-// round are runs of half a cache line.  At 6M Gaussians and 3840x2160 (510
-// bins of 8x8 tiles) 480 us so, 412 with twice as many; elsewhere the LDS costs
-// more than the runs give (3M at 1080p, 135 bins, 75 and 76 us; 2M small ones,
-// 510 bins of 4x4 tiles, 72 and 94).
+// round are runs of half a cache line; but it leaves three workgroups a CU where
+// there were five, two where there were three or four, and past 636 bins one
+// where there were two.  Bins of
+// 8x8 tiles, with 1M, 3M and 6M Gaussians of the power-law scene, once and
+// twice as many, us:
+//   135 bins  33  45 |  75  77 | 146 145      432 bins 100  75 | 192 177 | 398 352
+//   240       46  74 | 101 123 | 199 232      510      116  88 | 227 213 | 509 420
+//   260       50  79 | 108 129 | 211 246      570      222 171 | 300 228 | 609 447
+//   299       81  62 | 153 137 | 302 268      627      318 217 | 357 253 | 751 507
+//   375       92  69 | 176 160 | 358 309      680      369 233 | 387 479 | 803 964
+// The line was drawn from 135 and 510 alone; by these it could lie at 280, and
+// past 636 bins 1M Gaussians still gain and more lose.
+// 510 bins of 4x4 tiles (2M small ones at 1080p): 72 and 94.
 constexpr int kStage0 = 4096, kRoundItems0 = 512;
 constexpr int kLongBins = 384;
 static_assert(kWaves * kMaxBins4 <= kStage0, "one Gaussian per wave fits a round");

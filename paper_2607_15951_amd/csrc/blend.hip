@@ -370,11 +370,19 @@ blend_kernel(BlendArgs a)
     blend_tile_walk<kStats, kBatch>(a, blend_tile(a.order, a.group), lds);
 }
 
-// The form for grids of few tiles.  The line: plain and few, 131 and 110 us at
-// 2560 tiles (300K, 1024x640), 186 and 147 (500K); by groups of four, 105 and
-// 107 at 3600 (500K, 1280x720), 151 and 145 (1M), 129 and 154 at 5700 (1M,
-// 1600x900), 214 and 253 at 8160 (1M, 1920x1080): more tiles fill the SIMDs, and
-// the plain form's fewer instructions count.
+// The form for grids of few tiles: more tiles fill the SIMDs, and the plain
+// form's fewer instructions count.  Plain and few, in us, with 300K and 1M
+// Gaussians of a mixture, 1M of the power-law scene, 300K small ones:
+//   1920 tiles (768x640)     91  76 | 127 108 | 163 133 | 253 200
+//   2240 tiles (896x640)     82  82 | 103  89 | 140 134 | 199 161
+//   2560 tiles (1024x640)    83  93 | 127 115 | 123 148 | 164 132
+//   2720 tiles (1088x640)    86  97 | 104 114 | 123 152 | 143 114
+//   3096 tiles (1152x680)    78 104 | 113 117 | 117 160 | 143 115
+//   3600 tiles (1280x720)    79 116 |  99 129 | 116 177 | 124 107
+//   8160 tiles (1920x1080)  130 214 | 143 233 | 194 315 | 102 171
+// The line was drawn with groups of four entries, which break even near 3600
+// tiles; with eight the sums over these scenes are equal at 2560, scenes of many
+// small splats gain up to the line and past it, the others lose from 2720 on.
 constexpr int64_t kFewTiles = 3072;
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void blend_few_kernel(BlendArgs a)
 {

@@ -110,7 +110,7 @@ __device__ __forceinline__ float entry_alpha(const float4& e0, const float4& e1,
 // span on that side).  The picked items go to a ring in LDS; an entry's index
 // in the ring's sequence is its position in the tile's list of Sec. 3.1.  A
 // round is about 30 VALU instructions per wave and 256 entries, where staging
-// takes 380 per 64 picked ones.
+// takes 255 per 64 picked ones.
 constexpr int kRound = 1024;
 constexpr int kRing = 2048;
 
