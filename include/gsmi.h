@@ -129,8 +129,10 @@ typedef struct {
  * differ.  None (a static camera; colour, SH
  * or opacity edits): every kernel of the depth sort and the binning finds
  * that on the device and does nothing, and the blend reads the lists kept
- * in the context, which are the ones this frame would build.  Otherwise the
- * render goes on as usual (with GS_RENDER_REUSE_ORDER, trying the order).
+ * in the context, which are the ones this frame would build.  Otherwise --
+ * also in the frame after a change of bin_row_items, which lays the lists out
+ * differently -- the render goes on as usual (with GS_RENDER_REUSE_ORDER,
+ * trying the order).
  * The decision needs no host read, so a captured graph can carry the flag.
  * Every output is the same as without the flag.  Applies to gs_render,
  * gs_render_batched and graphs alike; ignored for the first render on a
