@@ -168,7 +168,7 @@ def stage_kernel(stage: str, dtype: int, deg: int, tuning: dict) -> str:
     if stage == "project":
         return f"project_kernel<{dtype}, {deg}, true>"
     if stage == "bin_row_scatter":
-        return "bins_scatter_kernel<1>"   # <2> for 4K grids
+        return "bins_scatter_kernel<1, false>"   # <2, ...> for 4K grids, <..., true> for larger ones
     if stage == "blend":
         if tuning["blend_tile_group"] < 0:   # the persistent grid over the work queue
             return f"blend_queue_kernel<{tuning['blend_batch']}>"

@@ -275,10 +275,10 @@ constexpr int kFrameCounters = 16;   // words cleared at frame set-up
 // (gs_context::lists_layout) of the lists in the workspace.  It is compared
 // on the device: a captured render is replayed after whatever ran last.
 constexpr int kCounterLayout = kFrameCounters;
-// counters[kCounterTable], likewise kept: where the offset table starts and
-// the words from one bin to the next (BinLists)
-constexpr int kCounterTable = kFrameCounters + 1;
-constexpr int kCounterWords = kFrameCounters + 3;
+// counters[kCounterStride], likewise kept: the words of their offset table
+// from one bin to the next (BinLists)
+constexpr int kCounterStride = kFrameCounters + 1;
+constexpr int kCounterWords = kFrameCounters + 2;
 
 struct ViewBatch {
     ViewParams v[kViewsPerLaunch];
@@ -298,13 +298,12 @@ __global__ void write_views_kernel(ViewBatch b, int count, ViewParams* dst)
 // arguments.  hold: the kept lists may be this render's, if their layout is
 // the one with that id.
 __global__ void frame_setup_kernel(ViewBatch b, int count, ViewParams* dst, int write, uint32_t* counters,
-                                   uint32_t hold, uint32_t layout, uint32_t table_first, uint32_t table_stride)
+                                   uint32_t hold, uint32_t layout, uint32_t stride)
 {
     if (threadIdx.x == kCounterChanged + 1) {
         counters[threadIdx.x] = hold && counters[kCounterLayout] == layout ? 1u : 0u;   // no load without hold
         counters[kCounterLayout] = layout;
-        counters[kCounterTable] = table_first;
-        counters[kCounterTable + 1] = table_stride;
+        counters[kCounterStride] = stride;
     } else if (threadIdx.x < kFrameCounters) {
         counters[threadIdx.x] = 0u;
     }
@@ -432,16 +431,16 @@ void choose_bins(gs_context* ctx, int64_t n, const gs_render_opts* opts, std::ve
 // The bins of a render's views and the chunks its binning cuts them from.
 struct BinShape {
     int64_t bins = 0;
-    int max_bins = 0, max_diff = 0, min_shift = 3;
+    int bands = 1, max_bins = 0, max_diff = 0, min_shift = 3;
     int items1 = 0, chunk = 0, chunks1 = 0;
     bool packed = true;   // the grids fit packed rectangles
-    size_t table_elems() const { return (size_t)(bins * chunks1 + 2); }
+    size_t table_elems() const { return (size_t)(bins * chunks1 + 1); }
     // and with any edges that the views' counters may suggest: a context's
     // table is sized for those, so that frames of one scene and size keep it
     // (a capture after one warm-up allocates nothing, and what it captured
     // stays valid when later frames take other edges)
     int64_t any_counts = 0;
-    size_t any_table_elems() const { return std::max((size_t)any_counts + 2, table_elems()); }
+    size_t any_table_elems() const { return std::max((size_t)any_counts + 1, table_elems()); }
 };
 
 BinShape bin_shape(const std::vector<ViewParams>& hv, int64_t n, int tuned)
@@ -452,12 +451,14 @@ BinShape bin_shape(const std::vector<ViewParams>& hv, int64_t n, int tuned)
         const int finest = bin_shift_of(v.tiles_x, v.tiles_y, 1.f);
         most_bins += (int64_t)bins_along(v.tiles_x, finest) * bins_along(v.tiles_y, finest);
         b.bins += (int64_t)v.bins_x * v.bins_y;
-        b.max_bins = std::max(b.max_bins, v.bins_x * v.bins_y);
-        b.max_diff = std::max(b.max_diff, (v.bins_x + 1) * (v.bins_y + 1));
+        const BandShape band = bins_band_shape(v.bins_x, v.bins_y);
+        b.bands = std::max(b.bands, band.bands);
+        b.max_bins = std::max(b.max_bins, band.bins);
+        b.max_diff = std::max(b.max_diff, band.diff);
         b.min_shift = std::min(b.min_shift, v.bin_shift);
         b.packed = b.packed && v.tiles_x <= kPackedRectTiles && v.tiles_y <= kPackedRectTiles;
     }
-    bins_chunk_shape(n, (int)hv.size(), b.bins, b.max_bins, tuned, &b.items1, &b.chunk, &b.chunks1);
+    bins_chunk_shape(n, (int)hv.size(), b.bins, tuned, &b.items1, &b.chunk, &b.chunks1);
     b.any_counts = bins_count_bound(n, (int)hv.size(), most_bins, tuned);
     return b;
 }
@@ -546,7 +547,7 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     if ((st = ensure(ctx, w.views, (size_t)V * sizeof(ViewParams))) != GS_OK) return st;
     if ((st = ensure(ctx, w.view_counts, (size_t)V * kViewCounters * 4)) != GS_OK) return st;
     if ((st = ensure(ctx, w.counters, kCounterWords * 4)) != GS_OK) return st;
-    if ((st = ensure(ctx, w.scan_scratch, scan_scratch_elems((int64_t)table - 2) * 8)) != GS_OK) return st;
+    if ((st = ensure(ctx, w.scan_scratch, scan_scratch_elems((int64_t)table - 1) * 8)) != GS_OK) return st;
     // every blend records its tiles' work; with blend_group 0 it is dispatched
     // (with -1 queued for a persistent grid) heaviest first, by the last
     // render's work when that render had the same tile layout (the history:
@@ -588,7 +589,7 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     if (one_launch) std::memcpy(vb.v, hv.data(), (size_t)V * sizeof(ViewParams));
     hipLaunchKernelGGL(frame_setup_kernel, dim3(1), dim3(256), 0, s, vb, one_launch ? V : 0, views,
                        one_launch && write_table ? 1 : 0, counters, try_lists && same_layout ? 1u : 0u,
-                       ctx->lists_layout, (uint32_t)bins_table_first(bs.max_bins), (uint32_t)bs.chunks1);
+                       ctx->lists_layout, (uint32_t)bs.chunks1);
     if (!one_launch && write_table) HIP_TRY(write_view_table(hv, views, s), "view table");
     HIP_TRY(hipGetLastError(), "frame set-up");
     STAGE_MARK(0);
@@ -683,6 +684,7 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     ba.n_views = V;
     ba.views = views;
     ba.bins = bs.bins;
+    ba.bands = bs.bands;
     ba.max_bins = bs.max_bins;
     ba.max_diff = bs.max_diff;
     ba.min_shift = bs.min_shift;
@@ -726,9 +728,7 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
     // Gaussian touches no more bins than tiles); an eager render scatters
     // into the buffers of earlier renders, which mostly have room, before
     // the host has read the sizes, and again into grown ones where they had
-    // not (stores past the buffers are dropped).  Grids whose cursors live in
-    // the count table are scattered once, when the sizes are here: the scatter
-    // moves those cursors, so it cannot run again.
+    // not (stores past the buffers are dropped)
     uint64_t capacity = o.pair_capacity, room = capacity;
     if (eager) room = std::min<uint64_t>(w.bin_items.bytes / 4, w.bin_spans.bytes / 2) & ~uint64_t(3);
     else if ((st = ensure_bin_entries(ctx, w, room)) != GS_OK) return st;
@@ -738,8 +738,7 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
         ba.capacity = room;
         return launch_bins_scatter(ba, s);
     };
-    const bool early = !eager || (room > 0 && bins_in_lds(bs.max_bins));
-    if (early) HIP_TRY(scatter(), "bin scatter");
+    if (room > 0) HIP_TRY(scatter(), "bin scatter");
     STAGE_MARK(4);
     if (eager) {
         uint64_t K64 = 0, entries = 0;
@@ -754,13 +753,10 @@ gs_status render_views(gs_context* ctx, const gs_gaussians* g, const std::vector
         if (K64 > 0xFFFFFFFFull) return fail(ctx, GS_ERR_CAPACITY, "more than 2^32-1 (Gaussian, tile) pairs");
         capacity = K64;
         if (n > 0) ctx->next_shifts = suggested_shifts(hv, ctx->host_info);
-        const bool grow = entries > room || !w.bin_items.p;
-        if (grow) {
+        if (entries > room || !w.bin_items.p) {
             HIP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");   // the buffers are grown
             if ((st = ensure_bin_entries(ctx, w, entries)) != GS_OK) return st;
             room = entries;
-        }
-        if (grow || !early) {
             STAGE_MARK(3);
             HIP_TRY(scatter(), "bin scatter");
             STAGE_MARK(4);
@@ -1262,8 +1258,7 @@ gs_status gs_render_backward(gs_context* ctx, const gs_gaussians* g, const float
     // the layout of the bins from the device, where the render wrote it: a
     // captured backward follows whichever render ran before it
     bb.lists = ctx->bins;
-    bb.lists.off = static_cast<const uint32_t*>(ctx->ws.bin_table.p);
-    bb.table = static_cast<const uint32_t*>(ctx->ws.counters.p) + kCounterTable;
+    bb.stride = static_cast<const uint32_t*>(ctx->ws.counters.p) + kCounterStride;
     bb.bin_views = static_cast<const ViewParams*>(ctx->ws.views.p);
     bb.views = views;
     bb.n_views = V;

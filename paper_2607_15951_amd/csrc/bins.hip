@@ -27,6 +27,8 @@
 //            bin.  Large ones (most of them in most bins of their common
 //            rectangle): bin by bin, a ballot of the Gaussians that touch it.
 //            Either way each bin's list keeps the depth order.
+// Grids of more bins than the waves' cursors fit in LDS are cut into bands of
+// bin rows, and a workgroup takes one band of its chunk.
 #include "gs_internal.h"
 
 #include <type_traits>
@@ -35,11 +37,15 @@ namespace gsmi {
 namespace {
 
 // Bin grids whose cursors (12 bytes per bin and wave) a workgroup of kWaves
-// waves keeps in LDS: four waves up to 1080p at 4x4 tiles a bin and 4K at
-// 8x8, one wave up to about 8192 x 8192.  Larger grids keep their cursors in
-// the count table.
+// waves keeps in LDS: up to 1080p at 4x4 tiles a bin and 4K at 8x8.  Larger
+// grids are cut into bands of at most kBandBins bins (two workgroups a CU with
+// the long rounds below), each workgroup going through its chunk's Gaussians
+// for the part of them in its band.  One wave a chunk with its cursors in LDS
+// up to 4096 bins, in the count table beyond, took 2.6 ms of scatter where the
+// bands take 0.45 (1M Gaussians, 7680x4320), 41 where they take 0.26 (1M,
+// 9216x9216) and 168 where they take 0.39 (100K, 16384x16384).
 constexpr int kWaves = 4;
-constexpr int kMaxBins4 = 768, kMaxBins1 = 4096;
+constexpr int kMaxBins = 768, kBandBins = 608;
 
 // Entries that a round of the scatter stages in LDS, and its Gaussians, as
 // multiples of these.  Twice as many where the bins are at their largest (so
@@ -59,8 +65,9 @@ constexpr int kMaxBins4 = 768, kMaxBins1 = 4096;
 // 510 bins of 4x4 tiles (2M small ones at 1080p): 72 and 94.
 constexpr int kStage0 = 4096, kRoundItems0 = 512;
 constexpr int kLongBins = 384;
-static_assert(kWaves * kMaxBins4 <= kStage0, "one Gaussian per wave fits a round");
-static_assert(kMaxBins4 <= 1024 && 2 * kRoundItems0 <= 1024, "staged words hold 10 bits of each");
+static_assert(kBandBins >= ((kMaxBandTiles - 1) >> 3) + 1, "a band holds a row of bins of 8x8 tiles");
+static_assert(kWaves * kMaxBins <= kStage0, "one Gaussian per wave fits a round");
+static_assert(kMaxBins <= 1024 && 2 * kRoundItems0 <= 1024, "staged words hold 10 bits of each");
 
 // A batch of 64 items goes bin by bin when each bin of its common rectangle
 // is touched by more than this many of them on average.
@@ -164,26 +171,53 @@ __device__ __forceinline__ void clip_span(uint32_t w, uint32_t b, int shift, uin
     at_last = (uint32_t)max(t0 + (1 << shift) - hi, 0);
 }
 
-// Clears the count table of a large grid and its leading word.
-__global__ __launch_bounds__(256) void bins_clear_kernel(uint32_t* table, int64_t n, const uint32_t* skip)
+// Bands of a grid of bins_x by bins_y bins, and the bin rows of each (the
+// last one's may be fewer).
+__host__ __device__ __forceinline__ int bin_bands(int bins_x, int bins_y)
 {
-    if (skip && *skip) return;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) table[i] = 0u;
+    if (bins_x * bins_y <= kMaxBins) return 1;
+    const int most = kBandBins / bins_x;
+    return (bins_y + most - 1) / most;
+}
+__host__ __device__ __forceinline__ int band_rows(int bins_x, int bins_y)
+{
+    const int bands = bin_bands(bins_x, bins_y);
+    return (bins_y + bands - 1) / bands;
 }
 
-// The bins of one item: [bx0, bx0 + nbx) x [by0, by0 + nby); none for an
-// empty rectangle.
+// The rows of a view's bins that a workgroup takes: [y0, y0 + rows).
+struct Band {
+    int y0, rows;
+};
+template <bool kBanded>
+__device__ __forceinline__ Band band_of_block(const ViewParams& vp)
+{
+    if constexpr (!kBanded) return {0, vp.bins_y};
+    const int rows = band_rows(vp.bins_x, vp.bins_y), y0 = (int)blockIdx.y * rows;
+    return {y0, min(rows, vp.bins_y - y0)};   // none past the view's last band
+}
+
+// The bins of one item, [bx0, bx0 + nbx) x [by0, by0 + nby), of a band with the
+// rows counted from its first; none for an empty rectangle.
+template <bool kBanded>
 struct BinRect {
     uint32_t bx0, nbx, by0, nby;
-    __device__ __forceinline__ BinRect(uint2 w, int shift)
+    __device__ __forceinline__ BinRect(uint2 w, int shift, Band band)
     {
         bin_span(w.x, shift, bx0, nbx);
         bin_span(w.y, shift, by0, nby);
+        if constexpr (kBanded) {
+            const int lo = max((int)by0 - band.y0, 0), hi = min((int)(by0 + nby) - band.y0, band.rows);
+            by0 = hi > lo ? (uint32_t)lo : 0u;
+            nby = hi > lo ? (uint32_t)(hi - lo) : 0u;
+            nbx = hi > lo ? nbx : 0u;
+        }
     }
 };
 
 // Adds the item to a difference array over the grid, `wide` words a row.
-__device__ __forceinline__ void diff_add(uint32_t* diff, int wide, const BinRect& r)
+template <bool kBanded>
+__device__ __forceinline__ void diff_add(uint32_t* diff, int wide, const BinRect<kBanded>& r)
 {
     if (r.nbx) {
         uint32_t* p = diff + r.by0 * wide + r.bx0;
@@ -262,7 +296,8 @@ struct EntryWalk {
     uint32_t carry;         // owner + 1 of the entry before the next window (uniform)
     bool some;
 
-    __device__ __forceinline__ EntryWalk(const BinRect& r)
+    template <bool kBanded>
+    __device__ __forceinline__ EntryWalk(const BinRect<kBanded>& r)
     {
         const uint32_t cnt = r.nbx * r.nby, incl = wave_sum_scan(cnt);
         first = incl - cnt;
@@ -313,51 +348,32 @@ __global__ __launch_bounds__(256) void bins_gather_kernel(BinArgs a)
     if (k < a.n * a.n_views) a.sorted_rect[k] = a.rect[a.sorted_idx[k]];
 }
 
-// counts[bin][chunk] of one chunk.  kW: waves of the workgroup with the
-// difference array in LDS; 0: one wave that counts into the cleared table.
-template <int kItems, int kW>
-__global__ __launch_bounds__(64 * (kW ? kW : 1)) void bins_count_kernel(BinArgs a)
+// counts[bin][chunk] of one chunk, for the bins of one band.
+template <int kItems, bool kBanded>
+__global__ __launch_bounds__(64 * kWaves) void bins_count_kernel(BinArgs a)
 {
-    constexpr int kN = kW ? kW : 1;
     if (a.skip && *a.skip) return;   // the last render's lists hold
-    extern __shared__ uint32_t s_diff[];   // [bins_y + 1][bins_x + 1] of the largest view
-    __shared__ uint32_t s_flag[kW ? 1 : 64];
+    extern __shared__ uint32_t s_diff[];   // [rows + 1][bins_x + 1] of the largest band
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (blockIdx.x == 0 && tid == 0) a.table[0] = 0u;
     Chunk ck;
     if (!chunk_range(a, chunk_of_block(), ck)) return;
     const ViewParams& vp = a.views[ck.view];
-    const int bx = vp.bins_x, by = vp.bins_y, wide = bx + 1, shift = vp.bin_shift;
-    uint32_t* counts = a.table + 1 + (int64_t)vp.bin_base * a.chunks1 + ck.part;
-    if constexpr (kW > 0) {
-        for (int i = tid; i < wide * (by + 1); i += 64 * kN) s_diff[i] = 0u;
-    } else {
-        s_flag[lane] = 0u;
-    }
+    const Band band = band_of_block<kBanded>(vp);
+    if (kBanded && band.rows <= 0) return;
+    const int bx = vp.bins_x, by = band.rows, wide = bx + 1, shift = vp.bin_shift;
+    uint32_t* counts = a.table + ((int64_t)vp.bin_base + (int64_t)band.y0 * bx) * a.chunks1 + ck.part;
+    for (int i = tid; i < wide * (by + 1); i += 64 * kWaves) s_diff[i] = 0u;
     __syncthreads();
-    for (int64_t k0 = ck.start + wave * (kItems * 64); k0 < ck.end; k0 += kN * kItems * 64) {
+    for (int64_t k0 = ck.start + wave * (kItems * 64); k0 < ck.end; k0 += kWaves * kItems * 64) {
         uint2 w[kItems];
         load_rects(a, k0, ck.end, lane, w);
 #pragma unroll
-        for (int b = 0; b < kItems; ++b) {
-            const BinRect r(w[b], shift);
-            if constexpr (kW > 0) {
-                diff_add(s_diff, wide, r);
-            } else {
-                EntryWalk ew(r);
-                for (uint32_t e0 = 0; e0 < ew.total; e0 += 64) {
-                    const Entry e = ew.window(e0, bx, lane, s_flag);
-                    if (e0 + lane < ew.total) atomicAdd(counts + (int64_t)e.bin * a.chunks1, 1u);
-                }
-            }
-        }
+        for (int b = 0; b < kItems; ++b) diff_add(s_diff, wide, BinRect<kBanded>(w[b], shift, band));
     }
-    if constexpr (kW > 0) {
-        __syncthreads();
-        if (wave == 0) diff_sum(s_diff, wide, by, lane);
-        __syncthreads();
-        for (int i = tid; i < bx * by; i += 64 * kN) counts[(int64_t)i * a.chunks1] = s_diff[i / bx * wide + i % bx];
-    }
+    __syncthreads();
+    if (wave == 0) diff_sum(s_diff, wide, by, lane);
+    __syncthreads();
+    for (int i = tid; i < bx * by; i += 64 * kWaves) counts[(int64_t)i * a.chunks1] = s_diff[i / bx * wide + i % bx];
 }
 
 // Span word of the blend: the part of bin (ex, ey) that the rectangle w covers.
@@ -378,11 +394,10 @@ __device__ __forceinline__ uint32_t bin_row(uint32_t bin, float inv_bx)
 // Positions of a batch's entries by the wave's cursors cur[bin], handed to
 // put(position, lane of the item, bin) by the lanes that hold one; the
 // cursors move on.  mask: a word per bin, zero between calls.
-template <typename Put>
-__device__ __forceinline__ void place_batch(uint2 w, int bx, int shift, int lane, uint64_t lt, uint32_t* flag,
+template <bool kBanded, typename Put>
+__device__ __forceinline__ void place_batch(const BinRect<kBanded>& r, int bx, int lane, uint64_t lt, uint32_t* flag,
                                             uint64_t* mask, uint32_t* cur, Put put)
 {
-    const BinRect r(w, shift);
     EntryWalk ew(r);
     // bin by bin where the items touch most bins of their common rectangle: a
     // bin takes about a third of a window's issue and no LDS round trip
@@ -442,15 +457,14 @@ __device__ __forceinline__ void place_batch(uint2 w, int bx, int shift, int lane
     }
 }
 
-// The chunk's entries to their places, four waves and grids of at most
-// kMaxBins4 bins.  The chunk is taken in rounds of at most kStage entries
+// The chunk's entries of one band to their places.  The chunk is taken in rounds of at most kStage entries
 // that are put in bin order in LDS and written from there, consecutive lanes
 // on consecutive places of a bin's list: written from the windows, every
 // entry had a cache line of its own, and those partial-line stores bound the
 // kernel (10M entries in 0.12 ms, 46M in 0.75 ms).  A round is 4 p
 // consecutive Gaussians, p per wave; p halves while they do not fit and
 // doubles while they would.
-template <int kTimes>
+template <int kTimes, bool kBanded = false>
 __global__ __launch_bounds__(64 * kWaves) void bins_scatter_kernel(BinArgs a)
 {
     constexpr int kStage = kTimes * kStage0, kRoundItems = kTimes * kRoundItems0;
@@ -468,8 +482,10 @@ __global__ __launch_bounds__(64 * kWaves) void bins_scatter_kernel(BinArgs a)
     if (!chunk_range(a, chunk_of_block(), ck)) return;
     if (ck.start >= ck.end) return;
     const ViewParams& vp = a.views[ck.view];
-    const int bx = vp.bins_x, by = vp.bins_y, bins = bx * by, shift = vp.bin_shift, wide = bx + 1;
-    const uint32_t* counts = a.table + 1 + (int64_t)vp.bin_base * a.chunks1 + ck.part;
+    const Band band = band_of_block<kBanded>(vp);
+    if (kBanded && band.rows <= 0) return;
+    const int bx = vp.bins_x, by = band.rows, bins = bx * by, shift = vp.bin_shift, wide = bx + 1;
+    const uint32_t* counts = a.table + ((int64_t)vp.bin_base + (int64_t)band.y0 * bx) * a.chunks1 + ck.part;
     uint64_t* mask = s_dyn + (int64_t)wave * a.lds_mask;
     uint32_t* diff = reinterpret_cast<uint32_t*>(mask);
     uint32_t* all = reinterpret_cast<uint32_t*>(s_dyn + (int64_t)kWaves * a.lds_mask);
@@ -499,14 +515,20 @@ __global__ __launch_bounds__(64 * kWaves) void bins_scatter_kernel(BinArgs a)
                 g[b] = a.sorted_idx[kc];
                 if (!in) w[b] = make_uint2(0u, 0u);
             }
-            const BinRect r(w[b], shift);
+            const BinRect<kBanded> r(w[b], shift, band);
             sum += r.nbx * r.nby;
         }
         const uint32_t incl = wave_sum_scan(sum);
         if (lane == 63) s_sum[wave] = incl;
         __syncthreads();
         const uint32_t total = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
-        if (total > (uint32_t)kStage) {   // uniform; p = 1 fits, 4 kMaxBins4 <= kStage
+        if (kBanded && total == 0u) {   // uniform: nothing of these in the band
+            pos += (int64_t)kWaves * p;
+            if (p < kRoundItems / kWaves) p *= 2;
+            __syncthreads();   // s_sum is written again
+            continue;
+        }
+        if (total > (uint32_t)kStage) {   // uniform; p = 1 fits, 4 kMaxBins <= kStage
             p /= 2;
             __syncthreads();   // s_sum is written again
             continue;
@@ -517,7 +539,7 @@ __global__ __launch_bounds__(64 * kWaves) void bins_scatter_kernel(BinArgs a)
 #pragma unroll
         for (int b = 0; b < kB; ++b) {
             if (b * 64 >= p) break;
-            diff_add(diff, wide, BinRect(w[b], shift));
+            diff_add(diff, wide, BinRect<kBanded>(w[b], shift, band));
             if (b * 64 + lane < p) {
                 s_item[wave * p + b * 64 + lane] = g[b];
                 s_rect[wave * p + b * 64 + lane] = w[b];
@@ -559,9 +581,8 @@ __global__ __launch_bounds__(64 * kWaves) void bins_scatter_kernel(BinArgs a)
         for (int b = 0; b < kB; ++b) {
             if (b * 64 >= p) break;
             const uint32_t first = (uint32_t)(wave * p + b * 64);
-            place_batch(w[b], bx, shift, lane, lt, flag, mask, cur, [&](uint32_t at, uint32_t owner, uint32_t bin) {
-                s_stage[at] = (first + owner) | (bin << 10);
-            });
+            place_batch(BinRect<kBanded>(w[b], shift, band), bx, lane, lt, flag, mask, cur,
+                        [&](uint32_t at, uint32_t owner, uint32_t bin) { s_stage[at] = (first + owner) | (bin << 10); });
         }
         __syncthreads();
         for (uint32_t i = tid; i < total; i += 64 * kWaves) {
@@ -569,7 +590,7 @@ __global__ __launch_bounds__(64 * kWaves) void bins_scatter_kernel(BinArgs a)
             const uint32_t ey = bin_row(bin, inv_bx);
             if ((uint64_t)at < a.capacity) {
                 a.items[at] = s_item[k];
-                a.spans[at] = span_word(s_rect[k], bin - ey * (uint32_t)bx, ey, shift);
+                a.spans[at] = span_word(s_rect[k], bin - ey * (uint32_t)bx, ey + (uint32_t)band.y0, shift);
             }
         }
         __syncthreads();
@@ -579,95 +600,26 @@ __global__ __launch_bounds__(64 * kWaves) void bins_scatter_kernel(BinArgs a)
     }
 }
 
-// The same for larger grids: one wave, its cursors in LDS (kLds) or in the
-// chunk's column of the table.
-template <bool kLds>
-__global__ __launch_bounds__(64) void bins_scatter_large_kernel(BinArgs a)
-{
-    if (a.skip && *a.skip) return;   // the last render's lists hold
-    extern __shared__ uint64_t s_dyn[];   // masks, then cursors
-    __shared__ uint32_t s_flag[64];
-    const int lane = threadIdx.x;
-    Chunk ck;
-    if (!chunk_range(a, chunk_of_block(), ck)) return;
-    if (ck.start >= ck.end) return;
-    const ViewParams& vp = a.views[ck.view];
-    const int bx = vp.bins_x, bins = bx * vp.bins_y, shift = vp.bin_shift;
-    uint32_t* counts = a.table + 1 + (int64_t)vp.bin_base * a.chunks1 + ck.part;
-    uint32_t* cur = reinterpret_cast<uint32_t*>(s_dyn + bins);
-    const float inv_bx = 1.0f / (float)bx;
-    s_flag[lane] = 0u;
-    if constexpr (kLds)
-        for (int i = lane; i < bins; i += 64) {
-            s_dyn[i] = 0ull;
-            cur[i] = counts[(int64_t)i * a.chunks1];
-        }
-    __syncthreads();
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int64_t k0 = ck.start; k0 < ck.end; k0 += 64) {
-        uint2 w[1];
-        load_rects(a, k0, ck.end, lane, w);
-        // the owner's item and rectangle are loaded again: its lane may hold
-        // no entry here
-        auto put = [&](uint32_t at, uint32_t owner, uint32_t bin) {
-            if ((uint64_t)at >= a.capacity) return;
-            const int64_t o = k0 + owner;
-            const uint32_t ey = bin_row(bin, inv_bx);
-            const uint2 ow = a.sorted_pack ? rect_words(unpack_rect(a.sorted_pack[o])) : rect_words(a.sorted_rect[o]);
-            a.items[at] = a.sorted_idx[o];
-            a.spans[at] = span_word(ow, bin - ey * (uint32_t)bx, ey, shift);
-        };
-        if constexpr (kLds) {
-            place_batch(w[0], bx, shift, lane, lt, s_flag, s_dyn, cur, put);
-        } else {
-            EntryWalk ew(BinRect(w[0], shift));
-            for (uint32_t e0 = 0; e0 < ew.total; e0 += 64) {
-                const Entry e = ew.window(e0, bx, lane, s_flag);
-                const bool on = e0 + (uint32_t)lane < ew.total;
-                // bins one by one; the chunk owns its column of the table,
-                // so its first lane moves the cursor there
-                uint32_t at = 0u;
-                uint64_t todo = __ballot(on);
-                while (todo) {
-                    const int lead = __ffsll((long long)todo) - 1;
-                    const uint32_t b1 = (uint32_t)__builtin_amdgcn_readlane((int)e.bin, lead);
-                    const uint64_t m = __ballot(on && e.bin == b1);
-                    uint32_t c = 0u;
-                    if (lane == lead) c = atomicAdd(counts + (int64_t)b1 * a.chunks1, (uint32_t)__popcll(m));
-                    c = (uint32_t)__builtin_amdgcn_readlane((int)c, lead);
-                    if (on && e.bin == b1) at = c + (uint32_t)__popcll(m & lt);
-                    todo &= ~m;
-                }
-                if (on) put(at, e.owner, e.bin);
-            }
-        }
-    }
-}
-
 unsigned grid_of(int64_t chunks)
 {
     constexpr int64_t all = 8 * kGroup;
     return (unsigned)((chunks + all - 1) / all * all);
 }
 
-int bin_waves(int max_bins) { return max_bins <= kMaxBins4 ? kWaves : (max_bins <= kMaxBins1 ? 1 : 0); }
-
+// f with the items per lane of the count and whether the grids are cut in bands.
 template <typename F>
 void with_shape(const BinArgs& a, F f)
 {
-    auto items = [&](auto W) {
+    auto items = [&](auto B) {
         switch (a.items1) {
-        case 1: f(std::integral_constant<int, 1>{}, W); break;
-        case 2: f(std::integral_constant<int, 2>{}, W); break;
-        case 4: f(std::integral_constant<int, 4>{}, W); break;
-        default: f(std::integral_constant<int, 8>{}, W); break;
+        case 1: f(std::integral_constant<int, 1>{}, B); break;
+        case 2: f(std::integral_constant<int, 2>{}, B); break;
+        case 4: f(std::integral_constant<int, 4>{}, B); break;
+        default: f(std::integral_constant<int, 8>{}, B); break;
         }
     };
-    switch (bin_waves(a.max_bins)) {
-    case kWaves: items(std::integral_constant<int, kWaves>{}); break;
-    case 1: items(std::integral_constant<int, 1>{}); break;
-    default: items(std::integral_constant<int, 0>{}); break;
-    }
+    if (a.bands > 1) items(std::true_type{});
+    else items(std::false_type{});
 }
 
 }  // namespace
@@ -686,7 +638,7 @@ int bin_shift_of(int tiles_x, int tiles_y, float footprint)
         footprint = edge * edge;
     }
     int shift = footprint >= 24.f ? 3 : (footprint >= 6.f ? 2 : (footprint >= 2.f ? 1 : 0));
-    while (shift < 3 && (((tiles_x - 1) >> shift) + 1) * (((tiles_y - 1) >> shift) + 1) > kMaxBins4) ++shift;
+    while (shift < 3 && (((tiles_x - 1) >> shift) + 1) * (((tiles_y - 1) >> shift) + 1) > kMaxBins) ++shift;
     return shift;
 }
 
@@ -695,12 +647,10 @@ int bin_shift_of(int tiles_x, int tiles_y, float footprint)
 // Gaussian): a wave works through its 64-Gaussian batches one after another.
 // The tuned width (8 the default) scales it.
 constexpr int64_t kFullWaves = 16384, kTableSlack = 16384;
-void bins_chunk_shape(int64_t n, int n_views, int64_t bins, int max_bins, int tuned, int* items1, int* chunk,
-                      int* chunks1)
+void bins_chunk_shape(int64_t n, int n_views, int64_t bins, int tuned, int* items1, int* chunk, int* chunks1)
 {
-    const int waves = std::max(bin_waves(max_bins), 1);
     auto chunks = [&](int batches) {
-        const int64_t size = (int64_t)batches * 64 * waves;
+        const int64_t size = (int64_t)batches * 64 * kWaves;
         return std::max<int64_t>((n + size - 1) / size, 1);
     };
     auto fits = [&](int batches) { return chunks(batches) == 1 || bins * chunks(batches) <= n * n_views + kTableSlack; };
@@ -710,7 +660,7 @@ void bins_chunk_shape(int64_t n, int n_views, int64_t bins, int max_bins, int tu
     if (tuned > 8) batches *= 2;
     else if (tuned < 8 && batches > 1) batches /= 2;
     *items1 = std::min(batches, 8);
-    *chunk = batches * 64 * waves;
+    *chunk = batches * 64 * kWaves;
     *chunks1 = (int)chunks(batches);
 }
 
@@ -722,27 +672,26 @@ int64_t bins_count_bound(int64_t n, int n_views, int64_t bins, int tuned)
     return std::max<int64_t>(n * n_views + kTableSlack, bins) * (tuned < 8 ? 2 : 1);
 }
 
-bool bins_in_lds(int max_bins) { return bin_waves(max_bins) > 0; }
+BandShape bins_band_shape(int bins_x, int bins_y)
+{
+    const int rows = band_rows(bins_x, bins_y);
+    return {bin_bands(bins_x, bins_y), rows * bins_x, (rows + 1) * (bins_x + 1)};
+}
 
 hipError_t launch_bins_count(const BinArgs& a, uint64_t* scan_scratch, hipStream_t s)
 {
     const int64_t elems = a.bins * a.chunks1;
-    if (a.n == 0) return launch_fill_u32(a.table, 0u, elems + 2, s);
+    if (a.n == 0) return launch_fill_u32(a.table, 0u, elems + 1, s);
     if (!a.sorted_pack)
         hipLaunchKernelGGL(bins_gather_kernel, dim3((unsigned)((a.n * a.n_views + 255) / 256)), dim3(256), 0, s, a);
-    if (!bins_in_lds(a.max_bins)) {
-        const unsigned cg = (unsigned)std::min<int64_t>((elems + 2 + 255) / 256, 16384);
-        hipLaunchKernelGGL(bins_clear_kernel, dim3(cg), dim3(256), 0, s, a.table, elems + 2, a.skip);
-    }
-    const unsigned grid = grid_of((int64_t)a.chunks1 * a.n_views);
-    with_shape(a, [&](auto I, auto W) {
-        constexpr int w = decltype(W)::value;
-        hipLaunchKernelGGL((bins_count_kernel<decltype(I)::value, w>), dim3(grid), dim3(64 * (w ? w : 1)),
-                           w ? (size_t)a.max_diff * sizeof(uint32_t) : 0, s, a);
+    const dim3 grid(grid_of((int64_t)a.chunks1 * a.n_views), (unsigned)a.bands);
+    with_shape(a, [&](auto I, auto B) {
+        hipLaunchKernelGGL((bins_count_kernel<decltype(I)::value, decltype(B)::value>), grid, dim3(64 * kWaves),
+                           (size_t)a.max_diff * sizeof(uint32_t), s, a);
     });
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_scan_exclusive(a.table + 1, elems, scan_scratch, nullptr, a.table + 1 + elems, a.overflow, s, nullptr,
+    return launch_scan_exclusive(a.table, elems, scan_scratch, nullptr, a.table + elems, a.overflow, s, nullptr,
                                  a.skip);
 }
 
@@ -752,18 +701,11 @@ hipError_t launch_bins_scatter(const BinArgs& a0, hipStream_t s)
     BinArgs a = a0;
     // 8-byte words of a wave's masks, which also hold its difference array
     a.lds_mask = std::max(a.max_bins, (a.max_diff + 1) / 2);
-    const dim3 grid(grid_of((int64_t)a.chunks1 * a.n_views));
-    switch (bin_waves(a.max_bins)) {
-    case kWaves:
-        hipLaunchKernelGGL(a.min_shift == 3 && a.max_bins > kLongBins ? bins_scatter_kernel<2> : bins_scatter_kernel<1>,
-                           grid, dim3(64 * kWaves),
-                           (size_t)kWaves * a.lds_mask * 8 + (size_t)(kWaves + 2) * a.max_bins * 4, s, a);
-        break;
-    case 1:
-        hipLaunchKernelGGL(bins_scatter_large_kernel<true>, grid, dim3(64), (size_t)a.max_bins * 12, s, a);
-        break;
-    default: hipLaunchKernelGGL(bins_scatter_large_kernel<false>, grid, dim3(64), 0, s, a); break;
-    }
+    const bool wide_rounds = a.min_shift == 3 && a.max_bins > kLongBins;
+    const auto kernel = a.bands > 1 ? (wide_rounds ? bins_scatter_kernel<2, true> : bins_scatter_kernel<1, true>)
+                                    : (wide_rounds ? bins_scatter_kernel<2> : bins_scatter_kernel<1>);
+    hipLaunchKernelGGL(kernel, dim3(grid_of((int64_t)a.chunks1 * a.n_views), (unsigned)a.bands), dim3(64 * kWaves),
+                       (size_t)kWaves * a.lds_mask * 8 + (size_t)(kWaves + 2) * a.max_bins * 4, s, a);
     return hipGetLastError();
 }
 

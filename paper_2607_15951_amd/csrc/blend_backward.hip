@@ -122,8 +122,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void b
     const bool inside = px < width && py < height;
     TileCursor tc;
     BinLists lists = a.lists;
-    lists.off += a.table[0];
-    lists.stride = a.table[1];
+    lists.stride = *a.stride;
     tc.start(lists, a.bin_views[view], tx, ty);
     const double ox = (double)(tx * kTile), oy = (double)(ty * kTile);
     const float fx = (float)lx, fy = (float)ly;

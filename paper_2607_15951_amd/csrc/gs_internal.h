@@ -199,13 +199,14 @@ struct BinArgs {
     int n_views;
     const ViewParams* views;      // device table
     int64_t bins;                 // bins over all views
-    int max_bins;                 // bins of the largest grid
-    int max_diff;                 // largest (bins_x + 1) (bins_y + 1)
+    int bands;                    // most bands of a view (bins_band_shape)
+    int max_bins;                 // bins of the largest band
+    int max_diff;                 // largest (bins_x + 1) (rows + 1) of a band
     int min_shift;                // smallest bin edge (log2 tiles)
     int items1, chunk, chunks1;   // chunk shape (bins_chunk_shape): items per lane and round, Gaussians, chunks per view
     int lds_mask;                 // set by the launch
-    // [1 + bins * chunks1 + 1]: a zero, then counts[bin][chunk], scanned to
-    // the chunks' cursors in place, then the total
+    // [bins * chunks1 + 1]: counts[bin][chunk], scanned to the chunks' cursors
+    // in place, then the total
     uint32_t* table;
     uint32_t* items;              // [capacity, in whole groups of 4] entry: item
     uint16_t* spans;              // likewise: its part of the bin: tiles clear of the bin's left, top, right and bottom edge, 4 bits each
@@ -218,10 +219,14 @@ struct BinArgs {
 };
 
 int bin_shift_of(int tiles_x, int tiles_y, float footprint);
-void bins_chunk_shape(int64_t n, int n_views, int64_t bins, int max_bins, int tuned, int* items1, int* chunk,
-                      int* chunks1);
+// A view's grid as the binning takes it: bands of bin rows, the bins and the
+// difference array of the largest.
+struct BandShape {
+    int bands, bins, diff;
+};
+BandShape bins_band_shape(int bins_x, int bins_y);
+void bins_chunk_shape(int64_t n, int n_views, int64_t bins, int tuned, int* items1, int* chunk, int* chunks1);
 int64_t bins_count_bound(int64_t n, int n_views, int64_t bins, int tuned);
-bool bins_in_lds(int max_bins);
 hipError_t launch_bins_count(const BinArgs& a, uint64_t* scan_scratch, hipStream_t s);
 hipError_t launch_bins_scatter(const BinArgs& a, hipStream_t s);
 
@@ -233,13 +238,9 @@ struct BinLists {
     int64_t stride;
     uint64_t capacity;
 };
-// First word of the offsets in the table: where the cursors live in the table
-// (large grids) the scatter moved every chunk's cursor to its end, the start
-// of the next.
-inline int bins_table_first(int max_bins) { return bins_in_lds(max_bins) ? 1 : 0; }
 inline BinLists bin_lists(const BinArgs& a)
 {
-    return {a.items, a.spans, a.table + bins_table_first(a.max_bins), a.chunks1, a.capacity};
+    return {a.items, a.spans, a.table, a.chunks1, a.capacity};
 }
 
 // The per-tile lists (tile_bin.hip), written on request.
@@ -329,8 +330,8 @@ hipError_t launch_blend_order(const uint32_t* cost, const BinLists& lists, const
 constexpr int kGrad2d = 9;
 struct BlendBackArgs {
     const Splat* splats;
-    BinLists lists;                // off: the whole table; the render's device words say how it is laid out:
-    const uint32_t* table;         // first word of the offsets, stride
+    BinLists lists;                // but for the stride, which the render left on the device:
+    const uint32_t* stride;
     const ViewParams* bin_views;   // the render's table: the views' bins
     const ViewParams* views;
     int n_views;

@@ -1,8 +1,7 @@
 """Frames whose bin entries outgrow the buffers that earlier frames on the
 context left: the entries are scattered again into grown buffers, which must
-give what a fresh context gives, bit for bit.  Grids of each kind: cursors of
-four waves or of one in LDS, and in the count table (more than 4096 bins),
-which the scatter itself moves."""
+give what a fresh context gives, bit for bit.  Grids of one band of bin rows,
+of two and of nine: no scatter may depend on what an earlier one left."""
 import numpy as np
 import pytest
 
