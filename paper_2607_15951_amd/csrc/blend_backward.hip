@@ -20,8 +20,8 @@
 // Layout as the forward: one workgroup of four waves per 16x16 tile, one pixel
 // per lane, entries staged through LDS with the same per-quad reach masks.
 // Vector instructions bound it (92% of their issue rate), so an entry's sums
-// over a wave are taken before what they share (the opacity, the factors, for
-// the conic all but the second moments), summed with as few
+// over a wave are taken before what they share (the factors, for the conic all
+// but the second moments of dL/dp), summed with as few
 // cross-lane instructions as they need (below) and added into an LDS row of
 // the staged entry; the rest is applied once per tile and entry, after the
 // batch, on the way to nine atomic adds in HBM.  At 3M Gaussians and
@@ -42,9 +42,9 @@ constexpr float kLn2 = 0.69314718055994531f;
 constexpr int kBackBatch = 128;
 constexpr int kFlush = 256 / kGrad2d;   // entries whose sums are flushed at once
 
-// The sums of an entry over a tile's pixels, with go = dL/d(opacity) and w =
-// a T, in the order in which wave_sum9 leaves them in the lanes.
-enum { kSo, kSv, kSu, kSxx, kSxy, kSr, kSyy, kSg, kSb };   // go, go dp/dv / ln2, go dp/du / ln2, go dx^2, ...
+// The sums of an entry over a tile's pixels, with gp = dL/dp and w = a T, in
+// the order in which wave_sum9 leaves them in the lanes.
+enum { kSo, kSv, kSu, kSxx, kSxy, kSr, kSyy, kSg, kSb };   // dL/d(opacity), gp dp/dv / ln2, gp dp/du / ln2, gp dx^2, ...
 
 struct BackLds {
     float4 s0[kBackBatch];   // du_hi, dv_hi, du_lo, dv_lo
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void b
                 // not past the pixel's last entry, and visible
                 const bool take = (uint32_t)__float_as_int(e2.w) <= nc && al >= 1.0f / 255.0f;
                 if (__builtin_amdgcn_ballot_w64(take) == 0) continue;
-                float go = 0.f;   // dL/d(opacity); times the opacity: dL/dp
+                float gp = 0.f, go = 0.f;   // dL/dp, p the exponent of exp, and dL/d(opacity)
                 float g[9];
                 g[kSr] = g[kSg] = g[kSb] = 0.f;
                 if (take) {
@@ -249,7 +249,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void b
                     Tr = fmaf(-al, Tr, Tr);   // as the forward: Tr (1 - al), rounded once
                     const float inv = __builtin_amdgcn_rcpf(1.0f - al);   // 1 - al >= 0.01
                     const float ga = fmaf(gc, Tr, -X) * inv;
-                    go = e1.w * E <= 0.99f ? ga * E : 0.f;
+                    const float gm = e1.w * E <= 0.99f ? ga : 0.f;
+                    gp = gm * al;
+                    go = gm * E;
                     g[kSr] = G0 * w;
                     g[kSg] = G1 * w;
                     g[kSb] = G2 * w;
@@ -259,12 +261,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void b
                 // pixel and in one fused step, since for a needle its two terms
                 // cancel (from the sums of dx and dy, 25 us less at 3M, the
                 // centres' errors are 2% larger; A' dx added to the sum that
-                // the alpha holds already, 570 against 586 us there and one
-                // rounding more)
+                // the alpha holds already, and dL/d(opacity) as the sum of gp
+                // over the opacity, are two instructions less, 577 against 583
+                // us there, and a rounding or two more)
                 const float cy = e1.z * dy;
-                g[kSu] = go * fmaf(e1.x + e1.x, dx, e1.y * dy);
-                g[kSv] = go * fmaf(e1.y, dx, cy + cy);
-                const float gx = go * dx, gy = go * dy;
+                g[kSu] = gp * fmaf(e1.x + e1.x, dx, e1.y * dy);
+                g[kSv] = gp * fmaf(e1.y, dx, cy + cy);
+                const float gx = gp * dx, gy = gp * dy;
                 g[kSxx] = gx * dx;
                 g[kSxy] = gx * dy;
                 g[kSyy] = gy * dy;
@@ -282,7 +285,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void b
         if (tid < kFlush * kGrad2d) {
             for (int j = flush_j; j < nk; j += kFlush) {
                 float v = L.s_acc[j][flush_of];
-                v *= flush_c < 5 ? flush_by * L.s1[j].w : flush_by;
+                v *= flush_by;
                 if (v != 0.f) unsafeAtomicAdd(&a.grad2d[(int64_t)L.s_item[j] * kGrad2d + flush_c], v);
             }
         }
